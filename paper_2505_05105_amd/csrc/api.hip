@@ -350,6 +350,8 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
   if (rc != MGFEM_OK) return bail(rc);
   rc = build_coarse_map(c, member);  // batch members run forward float cycles only
   if (rc != MGFEM_OK) return bail(rc);
+  rc = build_fused(c);
+  if (rc != MGFEM_OK) return bail(rc);
   SETUP_TRY(hipStreamSynchronize(c->s));
   mgfem_info& I = c->info;
   I.N = N;
@@ -484,16 +486,22 @@ void enqueue_iteration(mgfem_ctx* c, const IterKind& k) {
   }
 }
 
-// host-side state that an iteration reads and advances: the ping-pong parity
-// of every level and of the float64 level-0 iterate of the mixed solve
+// host-side state that an iteration reads and advances: the ping-pong parities
+// of every level, whether its iterate has cut sweeps pending or is zero, and of the float64 level-0 iterate of the mixed solve
 std::vector<int> loop_state(const mgfem_ctx* c) {
   std::vector<int> st;
-  for (const Level& L : c->lv) st.push_back(L.cur);
+  for (const Level& L : c->lv) st.push_back(L.cur | L.rp << 1 | (int)L.pend << 2 | (int)L.zero << 3);
   st.push_back(c->u_cur);
   return st;
 }
 void set_loop_state(mgfem_ctx* c, const std::vector<int>& st) {
-  for (size_t l = 0; l < c->lv.size(); ++l) c->lv[l].cur = st[l];
+  for (size_t l = 0; l < c->lv.size(); ++l) {
+    Level& L = c->lv[l];
+    L.cur = st[l] & 1;
+    L.rp = st[l] >> 1 & 1;
+    L.pend = (st[l] >> 2 & 1) != 0;
+    L.zero = (st[l] >> 3 & 1) != 0;
+  }
   c->u_cur = st[c->lv.size()];
 }
 
@@ -600,6 +608,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   L0.b = const_cast<double*>(b);
   L0.cur = 0;
   c->u_cur = 0;
+  for (Level& L : c->lv) L.pend = L.zero = false;
   launch_box_copy(c, c->x0, warm ? x : nullptr);
   int rc;
   if (bnorm < 0.0) {
@@ -643,11 +652,13 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   struct Pending {
     double seq;          // the iteration's last reduction: the norm of `result`
     double* result;      // the iterate that norm belongs to
+    bool patch;          // its cut vertices hold their values in the level's xs, not in the array
     const GraphEntry* g;
   };
   Pending pend[2];
   int queued = 0;
   double* result = c->x0;  // the iterate returned when the loop stops
+  bool patch = false;
   // The queue-ahead test with i norms read: the last factor applied once more
   // leaves the residual 4x above the target, so the iteration after the one
   // in flight will most likely be needed.
@@ -690,6 +701,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
     out.g = g;
     // fused: the closing sweep read the next iterate and wrote the other buffer
     out.result = mixed ? L0.X[c->u_cur] : fused ? L0.X[1 - L0.cur] : L0.X[L0.cur];
+    out.patch = fused && L0.fp.ok && L0.fp.ncut > 0;
     return MGFEM_OK;
   };
   if (status == MGFEM_OK && !conv && m < max_cycles) {
@@ -712,6 +724,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
       if (rc) return rc;
     }
     result = pend[0].result;
+    patch = pend[0].patch;
     pend[0] = pend[1];
     --queued;
     ++m;
@@ -739,6 +752,8 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   // export below is ordered after it on the stream)
   c->step_cycles.assign(step_inner.begin(), step_inner.begin() + std::min<size_t>(m, step_inner.size()));
   launch_export(c, x, result);
+  if (patch) fused_patch(c, x);
+  for (Level& L : c->lv) L.pend = L.zero = false;
   MGFEM_HIP_TRY(hipGetLastError());
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
   prof_collect(c);

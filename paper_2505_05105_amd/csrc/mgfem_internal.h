@@ -82,6 +82,40 @@ __host__ __device__ inline CutLds cut_lds_layout(int cl, int ext, int ts) {
   return L;
 }
 
+// The fused smoothing steps of the small levels (fused.hip).
+// the cut vertices of one cell and the columns of their rows (set-up only)
+struct FBlock {
+  int d, row, col, n;  // first value, first position, first column, rows | columns << 8
+};
+// one row of a tile's D: region index | core << 16, first segment | segments
+// << 16, and the vertex's position
+struct FRow {
+  int at, seg, pos;
+};
+// one tile: origin, stored rows; the rows, columns (positions) and segments
+// of the D of its region, and of the coarser level's nodes under it
+struct FTile {
+  static constexpr int kRows = 384, kCols = 1024, kCRows = 256, kSegs = 2048;
+  int x0, y0, st, nst;
+  int seg, nseg, nrow, ncol;
+  int cseg, ncseg, ncrow, nccol;
+  int inner, pad[3];  // inner: every region node is active with the interior row
+  int cols[kCols], ccols[kCols];
+  FRow rows[kRows], crows[kCRows];
+};
+struct FusedPlan {
+  bool ok = false;
+  int ntiles = 0, ncut = 0;
+  FTile* tiles = nullptr;
+  int* st_idx = nullptr;
+  void* st_coef = nullptr;   // float64 or float32
+  double2* D = nullptr;      // float64: segments of 16 values, fine then coarse
+  uint4* Didx = nullptr;     // their local columns
+  int* rows = nullptr;       // per position: i | j << 16
+  double* r[2] = {nullptr, nullptr};  // ping-pong residual at the cut vertices, by position
+  double* xs = nullptr;               // their values after the pending sweeps
+};
+
 struct Level {
   int N = 0;
   int stride = 0;  // N + 1
@@ -125,6 +159,10 @@ struct Level {
   int* tc_idx = nullptr;
   int* tc_pos = nullptr;
   int tp_max = 0, tc_max = 0;
+  FusedPlan fp;
+  int rp = 0;         // which fp.r belongs to the current iterate (host-side state, as the next two)
+  bool pend = false;  // the current iterate's last cut sweeps are not applied yet: x + D fp.r[rp]
+  bool zero = false;  // the current iterate is zero and its buffer is not cleared
   bool empty() const { return bbox[0] > bbox[1]; }
 };
 
@@ -431,6 +469,22 @@ int scratch_init(int* device);
 // mgfem_setup for one problem of a batched handle (forward coarse map only)
 int setup_member(const double* psi_dev, int32_t N, const mgfem_params* p, void* stream, mgfem_handle* out);
 int build_tile_lists(mgfem_ctx* c);
+// fused smoothing steps (fused.hip): plans, one sweep (of x, or with `up` of
+// x + P x_c; norm: the residual norm of its incoming iterate), residual and
+// restriction, the pending cut sweeps applied in place (no-op when none are),
+// and the cut vertices of a level-0 array from the values the last sweep with
+// a norm started from
+int build_fused(mgfem_ctx* c);
+void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up);
+void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse);
+void fused_apply(mgfem_ctx* c, int l);
+void fused_patch(mgfem_ctx* c, double* x);
+// the same for the problems of a batch (kinds kTeamSweep, kTeamRR)
+size_t fused_entry_bytes();
+void fused_entry(mgfem_ctx* m, int l, void* out);
+int fused_units(mgfem_ctx* m, int l);
+void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, int nwork, int par, int parc, bool zero,
+                  bool up);
 // sweep tile shapes, all with 512 threads (a workgroup's load phase is bound
 // by the memory instructions each wave issues, so more waves per tile start
 // the phases sooner): 64 x 32 on a finest level with N >= 2048, 64 x 16 on

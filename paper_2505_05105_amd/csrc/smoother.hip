@@ -1609,8 +1609,34 @@ void coarse_wg(mgfem_ctx* c, bool reverse, int reps) {
   Lc.cur = 0;
 }
 
+// one cycle of a level with the fused kernels (fused.hip): in float64 the cut
+// sweeps of each step are applied by whatever reads its result
 template <class T>
-void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = false) {
+void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = false);
+template <class T>
+void cycle_fused(mgfem_ctx* c, int l, bool first_sweep_done) {
+  constexpr bool f32 = sizeof(T) == 4;
+  const int cl = coarse_level(c);
+  Level& C = c->lv[l + 1];
+  auto step = [&](bool up) {
+    fused_sweep(c, l, f32, false, up);
+    if (f32) cut_sweeps<T>(c, l, false);
+  };
+  for (int s = first_sweep_done ? 1 : 0; s < c->p.nu1; ++s) step(false);
+  fused_restrict(c, l, f32, l + 1 != cl && !C.fp.ok);
+  C.pend = false;
+  C.zero = l + 1 != cl && C.fp.ok;
+  const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
+  const int visits = two_grid ? c->p.coarse_cycles : (c->p.cycle == MGFEM_CYCLE_W ? 2 : 1);
+  if (l + 1 == cl) coarse_wg<T>(c, false, visits);
+  else
+    for (int g = 0; g < visits; ++g) cycle_level<T>(c, l + 1, false);
+  step(true);
+  for (int s = 1; s < c->p.nu2; ++s) step(false);
+}
+
+template <class T>
+void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   const int nl = (int)c->lv.size();
   const int cl = coarse_level(c);
   if (cl >= 0 && l == cl) {
@@ -1618,6 +1644,10 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = fals
     return;
   }
   if (l == nl - 1) return;  // unreachable: the coarse plan always covers the coarsest level
+  if (!reverse && c->lv[l].fp.ok) {
+    cycle_fused<T>(c, l, first_sweep_done);
+    return;
+  }
   const int pre = reverse ? c->p.nu2 : c->p.nu1;
   const int post = reverse ? c->p.nu1 : c->p.nu2;
   for (int s = 0; s < pre; ++s) {
@@ -1626,6 +1656,8 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = fals
   }
   if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
   else launch_resrestrict<T, 16, 8, 512>(c, l);
+  c->lv[l + 1].pend = false;  // the iterate there is zero now (in memory too)
+  c->lv[l + 1].zero = !reverse && l + 1 != cl && c->lv[l + 1].fp.ok;
   // coarse-grid visits: gamma* (section 3.2); the two-grid scheme instead
   // solves the first coarse problem with coarse_cycles V-cycles from zero
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
@@ -1633,6 +1665,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = fals
   if (l + 1 == cl) coarse_wg<T>(c, reverse, visits);  // runs its visits itself
   else
     for (int g = 0; g < visits; ++g) cycle_level<T>(c, l + 1, reverse);
+  fused_apply(c, l + 1);  // the prolongation below reads the iterate from memory
   if (reverse || post == 0) {
     prolong<T>(c, l);
     for (int s = 0; s < post; ++s) smooth<T>(c, l, reverse);
@@ -1650,7 +1683,16 @@ void run_cycle(mgfem_ctx* c, const CycleOpts& o) {
   else cycle_level<double>(c, 0, o.reverse, o.first_sweep_done);
 }
 
-void first_sweep_with_norm(mgfem_ctx* c) { sweep<double>(c, 0, false, true); }
+void first_sweep_with_norm(mgfem_ctx* c) {
+  if (!c->lv[0].fp.ok) {
+    sweep<double>(c, 0, false, true);
+    return;
+  }
+  fused_sweep(c, 0, false, true, false);
+  c->red_seq += 1.0;
+  hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, (const double*)c->sweep_part, c->lv[0].fp.ntiles,
+                     c->red_out, c->red_host, c->red_seq_dev);
+}
 
 // ---- batched solves on the tiled kernels: float-cycle entries and launches.
 // Every level a batch member smooths must use the small tile shapes (16 x 16

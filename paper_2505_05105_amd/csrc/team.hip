@@ -27,6 +27,7 @@ namespace mgfem {
 
 struct TeamPlan {
   bool ok = false;
+  bool fused = false;                // every smoothed level of every member has its 16 x 16 fused tiles
   int P = 0;
   int depth = 0;                     // largest first coarse level over the members
   std::vector<int> lc;               // first coarse level per member
@@ -48,6 +49,7 @@ struct TeamPlan {
 namespace {
 
 int seg(const TeamPlan& T, int kind, int d) { return kind * T.depth + d; }
+bool fused_kind(const TeamPlan& T, int kind) { return T.fused && (kind == kTeamSweep || kind == kTeamRR); }
 
 // work lists of the active problems (all float-cycle and level-0 kinds)
 int team_lists(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, bool with_export) {
@@ -63,7 +65,7 @@ int team_lists(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, bool w
         const bool smooths = d < T.lc[p];
         const bool maps = T.lc[p] == d + 1;
         if ((kind == kTeamMap && !maps) || (kind != kTeamMap && !smooths)) continue;
-        const int u = team_units(m, kind, d);
+        const int u = fused_kind(T, kind) ? fused_units(m, d) : team_units(m, kind, d);
         for (int q = 0; q < u; ++q) w.push_back(make_int2(p, q));
       }
       T.seg_cnt[seg(T, kind, d)] = (int)w.size() - T.seg_off[seg(T, kind, d)];
@@ -93,8 +95,13 @@ int team_lists(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, bool w
   return MGFEM_OK;
 }
 
-void launch_kind(mgfem_ctx* b, TeamPlan& T, int kind, int d, int par, int parc, int prolong) {
+// zero: the iterate is zero (its buffer is only cleared by the separate kernels)
+void launch_kind(mgfem_ctx* b, TeamPlan& T, int kind, int d, int par, int parc, int prolong, bool zero = false) {
   const int k = seg(T, kind, d);
+  if (fused_kind(T, kind)) {
+    fused_launch(b->s, kind, T.tab[kind][d], T.work + T.seg_off[k], T.seg_cnt[k], par, parc, zero, prolong != 0);
+    return;
+  }
   const int lds = kind == kTeamCut ? T.cut_lds : kind == kTeamMap ? T.map_lds : 0;
   team_launch(b->s, kind, T.tab[kind][d], T.work + T.seg_off[k], T.seg_cnt[k], par, parc, prolong, lds);
 }
@@ -108,14 +115,14 @@ void launch_l0(mgfem_ctx* b, TeamPlan& T, int kind, int upar, int epar) {
 void team_level(mgfem_ctx* b, TeamPlan& T, int d, std::vector<int>& par) {
   const int nu1 = b->p.nu1, nu2 = b->p.nu2;
   for (int s = 0; s < nu1; ++s) {
-    launch_kind(b, T, kTeamSweep, d, par[d], 0, 0);
+    launch_kind(b, T, kTeamSweep, d, par[d], 0, 0, T.fused && d > 0 && s == 0);
     par[d] ^= 1;
     launch_kind(b, T, kTeamCut, d, par[d], 0, 0);
   }
-  launch_kind(b, T, kTeamRR, d, par[d], par[d + 1], 0);
+  launch_kind(b, T, kTeamRR, d, par[d], par[d + 1], 0, T.fused && d > 0 && nu1 == 0);
   launch_kind(b, T, kTeamMap, d, 0, 0, 0);
   if (d + 1 < T.depth) team_level(b, T, d + 1, par);
-  launch_kind(b, T, kTeamSweep, d, par[d], par[d + 1], 1);  // x + P x_c, then the sweep
+  launch_kind(b, T, kTeamSweep, d, par[d], par[d + 1], 1, T.fused && d > 0 && nu1 == 0);  // x + P x_c, then the sweep
   par[d] ^= 1;
   launch_kind(b, T, kTeamCut, d, par[d], 0, 0);
   for (int s = 1; s < nu2; ++s) {
@@ -166,15 +173,20 @@ int team_build(mgfem_ctx* b) {
     if (ok) T->depth = std::max(T->depth, lc);
   }
   if (!ok) return MGFEM_OK;  // the persistent kernel serves this batch
+  T->fused = true;
+  for (int p = 0; p < P; ++p)
+    for (int l = 0; l < T->lc[p]; ++l) T->fused = T->fused && fused_units(b->members[p], l) >= 0;
   for (int kind = 0; kind < 4; ++kind) {
-    const size_t eb = team_entry_bytes(kind);
+    const bool fk = fused_kind(*T, kind);
+    const size_t eb = fk ? fused_entry_bytes() : team_entry_bytes(kind);
     for (int d = 0; d < T->depth; ++d) {
       std::vector<unsigned char> host((size_t)P * eb, 0);
       for (int p = 0; p < P; ++p) {
         mgfem_ctx* m = b->members[p];
         const bool use = kind == kTeamMap ? T->lc[p] == d + 1 : d < T->lc[p];
         if (!use) continue;
-        team_entry(m, kind, d, host.data() + (size_t)p * eb);
+        if (fk) fused_entry(m, d, host.data() + (size_t)p * eb);
+        else team_entry(m, kind, d, host.data() + (size_t)p * eb);
         if (kind == kTeamCut) T->cut_lds = std::max(T->cut_lds, team_lds(m, kind, d));
         if (kind == kTeamMap) T->map_lds = std::max(T->map_lds, team_lds(m, kind, d));
       }

@@ -1,0 +1,112 @@
+"""The fused smoothing steps (sweep, residual and prolongation kernels that
+apply the cut sweeps of the step before them as a product) against the oracle
+and against the separate kernels, at the sizes where their tiles end: 16 x 16
+tiles up to N = 512, 32 x 32 tiles to N = 2048."""
+import os
+
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import assembly as oasm
+from oracle import multigrid as omg
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_05105_amd as mg
+    return mg
+
+
+def _separate(mg, psi, N, **kw):
+    """The same solver on the separate kernels (no cut-vertex plans)."""
+    old = os.environ.get("MGFEM_NO_CUT_GROUPS")
+    os.environ["MGFEM_NO_CUT_GROUPS"] = "1"
+    try:
+        return mg.Solver(psi, N, **kw)
+    finally:
+        if old is None:
+            del os.environ["MGFEM_NO_CUT_GROUPS"]
+        else:
+            os.environ["MGFEM_NO_CUT_GROUPS"] = old
+
+
+# tile edges: one tile, whole tiles, one node or three cells beyond, the change
+# of tile size (512 | 640), domains that reach the sides of the box
+@pytest.mark.parametrize("N,coarsest,psi,kw", [
+    (12, 3, lambda N: W.circle(N, radius=0.6), {}),
+    (16, 4, lambda N: W.circle(N, radius=0.6), {"eta": 1}),
+    (48, 3, lambda N: W.ellipse(N, center=(0.05, -0.03)), {"eta": 2, "nu1": 1, "nu2": 2}),
+    (80, 5, lambda N: W.flower(N), {"eta": 3, "nu1": 1, "nu2": 1}),
+    (96, 3, lambda N: W.circle(N, radius=1.1), {}),
+    (128, 4, lambda N: W.flower(N), {"eta": 0}),
+    (320, 5, lambda N: W.circle(N, radius=0.97, center=(0.1, 0.0)), {"nu1": 3}),
+    (512, 4, lambda N: W.flower(N), {"cycle": 2}),
+    (640, 5, lambda N: W.ellipse(N), {}),
+    (768, 3, lambda N: W.circle(N, radius=1.05), {"cycle": 3, "coarse_cycles": 3}),
+])
+def test_fused_iterates(N, coarsest, psi, kw):
+    """Three cycles from zero on random data: the oracle's iterates (and the
+    separate kernels') to 1e-10 of their largest entry, as for the other
+    random draws; the transposed cycle is untouched by the forward state."""
+    mg = _gpu()
+    psi = psi(N)
+    rng = np.random.default_rng(N)
+    f, g = rng.uniform(-1, 1, (N + 1) ** 2), rng.uniform(-1, 1, (N + 1) ** 2)
+    s = mg.Solver(psi, N, coarsest_n=coarsest, **kw)
+    u, h = s.solve(f, g, tol=-1.0, max_cycles=3)
+    u = u.cpu().numpy()
+    sep = _separate(mg, psi, N, coarsest_n=coarsest, **kw)
+    us, hs = sep.solve(f, g, tol=-1.0, max_cycles=3)
+    us = us.cpu().numpy()
+    scale = np.abs(us).max()
+    assert np.abs(u - us).max() <= 1e-10 * scale
+    np.testing.assert_allclose(h, hs, rtol=1e-9, atol=1e-12 * hs[0])
+    # a second solve starts from a clean state, and from a given iterate
+    u2, h2 = s.solve(f, g, tol=-1.0, max_cycles=3)
+    assert np.array_equal(h, h2) and np.array_equal(u, u2.cpu().numpy())
+    uw, _ = s.solve(f, g, tol=-1.0, max_cycles=1, u0=us)
+    usw, _ = sep.solve(f, g, tol=-1.0, max_cycles=1, u0=us)
+    assert np.abs((uw - usw).cpu().numpy()).max() <= 1e-10 * scale
+    if kw.get("cycle", 1) != 3:
+        d = oasm.assemble(psi, N)
+        H = omg.build_hierarchy(d, coarsest_n=coarsest)
+        ref = omg.solve(H, d.rhs(f, g), tol=-1.0, max_cycles=3, nu1=kw.get("nu1", 2), nu2=kw.get("nu2", 1),
+                        eta=kw.get("eta", 4), gamma_star=kw.get("cycle", 1))
+        assert np.abs(u - ref.u).max() <= 1e-10 * np.abs(ref.u).max()
+
+
+@pytest.mark.parametrize("N,coarsest", [(64, 4), (320, 5), (640, 5), (1024, 4), (2048, 4)])
+def test_fused_float_cycles(N, coarsest):
+    """Mixed precision with one float32 cycle per step: the steps and, to 1e-8,
+    the float64 solution of the list smoother (the bound the list smoother's
+    own test has)."""
+    mg = _gpu()
+    p = W.flower_mms(N)
+    s = mg.Solver(p.psi, N, coarsest_n=coarsest, precision=mg.PREC_MIXED, inner_cycles=1)
+    sep = _separate(mg, p.psi, N, coarsest_n=coarsest, precision=mg.PREC_MIXED, inner_cycles=1)
+    u, h = s.solve(p.f, p.g, tol=1e-10)
+    us, hs = sep.solve(p.f, p.g, tol=1e-10)
+    assert s.last_status == 0 and len(h) == len(hs)
+    assert float((u - us).abs().max()) <= 1e-8 * float(us.abs().max())
+
+
+def test_crowded_tiles_keep_the_separate_kernels():
+    """A level set that cuts every cell: more cut vertices in a tile than its
+    record holds, so the level takes the separate kernels and still matches
+    the oracle."""
+    mg = _gpu()
+    N = 64
+    x, y = W.grid_xy(N)
+    psi = np.cos(np.pi * N / 4 * (x + 0.013)) * np.cos(np.pi * N / 4 * (y - 0.007)) - 0.35
+    rng = np.random.default_rng(3)
+    f, g = rng.uniform(-1, 1, psi.size), rng.uniform(-1, 1, psi.size)
+    s = mg.Solver(psi, N)
+    u, _ = s.solve(f, g, tol=-1.0, max_cycles=2, raise_on_fail=False)
+    d = oasm.assemble(psi, N)
+    ref = omg.solve(omg.build_hierarchy(d), d.rhs(f, g), tol=-1.0, max_cycles=2)
+    assert np.abs(u.cpu().numpy() - ref.u).max() <= 1e-10 * np.abs(ref.u).max()
