@@ -72,6 +72,8 @@ struct FArgs {
   const double2* D;
   const uint4* Didx;
   const double* r;
+  const int* rows;     // transposed step from zero: r is b at these nodes (i | j << 16 by position)
+  int reverse;         // colours 3 .. 0
   double* xs_out;
   const double* xs_in;
   // prolongation from the coarser level, and its pending residual
@@ -162,7 +164,7 @@ constexpr int kWideTiles = 512;
 inline int tile_nodes(int N) { return N <= 512 ? 16 : 32; }
 
 // kinds of a tile's work
-constexpr int kSweepK = 0, kRestrictK = 1, kUpK = 2, kApplyK = 3;
+constexpr int kSweepK = 0, kRestrictK = 1, kUpK = 2, kProlongK = 3;
 
 // One tile.  The first threads take the regular rows of a phase (at most 120 of
 // one colour in a 16 x 16 tile, 360 in a 32 x 32 one), the stored rows go to
@@ -179,10 +181,11 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
   static_assert(kFree < BS, "threads for the stored rows");
   __shared__ T su[kRN];
   __shared__ uint8_t sfl[kRN];
-  constexpr bool kD = sizeof(T) == 8;  // cut sweeps as a product
+  constexpr bool kD = sizeof(T) == 8;                            // cut sweeps as a product
+  constexpr bool kUp = KIND == kUpK || KIND == kProlongK;        // adds P x_c
   __shared__ double sr[kD ? GE::cols : 1];
   __shared__ double ps[kD ? FTile::kSegs : 1];
-  __shared__ T sx[KIND == kUpK ? kCRN : 1];
+  __shared__ T sx[kUp ? kCRN : 1];
   constexpr int RR = FT + 1;  // residual region of a restriction
   constexpr int NRR = (RR * RR + BS - 1) / BS;
   static_assert(NRR <= 4, "residual nodes per thread");
@@ -235,14 +238,17 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
     for (int p = 0; p < 10; ++p) cf[p] = a.st_coef[10 * (int64_t)st + p * nst + e];
   }
   const int sq = si >= 0 ? si & 2047 : -1, scol = (si >> 11) & 3, spos = (si >> 13) - 1;
-  // regular rows: one node of each colour, or one residual node
+  // regular rows: one node of each phase, or of the residual.  Phase c takes
+  // colour c, in a reversed sweep colour 3 - c, whose sub-lattice starts one
+  // node further in both directions
+  const int rev = KIND == kSweepK && a.reverse ? 1 : 0;
   int pq[4];
   T pb[4];
   if constexpr (KIND != kRestrictK) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int nx = PH::nx(c), ny = PH::ny(c);
-      const int ri = PH::lox(c) + 2 * (tid % nx), rj = PH::loy(c) + 2 * (tid / nx);
+      const int ri = PH::lox(c) + rev + 2 * (tid % nx), rj = PH::loy(c) + rev + 2 * (tid / nx);
       const int gi = ox + ri, gj = oy + rj;
       const bool ok = tid < nx * ny && gi >= 0 && gj >= 0 && gi <= a.N && gj <= a.N;
       pq[c] = ok ? ri + rj * kRW : -1;
@@ -259,7 +265,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
     }
   }
   T rc = T(0);
-  if constexpr (KIND == kUpK) {
+  if constexpr (kUp) {
     const int Nc = a.N >> 1, cx = x0 / 2 - 3, cy = y0 / 2 - 2;
     const int I = cx + tid % kCRW, J = cy + tid / kCRW;
     const bool in = tid < kCRN && I >= 0 && J >= 0 && I <= Nc && J <= Nc;
@@ -269,7 +275,11 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
   if constexpr (kD)
     if (nseg > 0) {
 #pragma unroll
-      for (int u = 0; u < NC; ++u) rv[u] = rp[colp[u]];
+      for (int u = 0; u < NC; ++u) {
+        // from a zero start the residual is the right-hand side
+        const int ij = KIND == kSweepK && a.rows ? a.rows[colp[u]] : 0;
+        rv[u] = KIND == kSweepK && a.rows ? (double)a.b[(ij & 0xffff) + (int64_t)(ij >> 16) * a.s] : rp[colp[u]];
+      }
     }
   if (sq >= 0) sb = a.b[(ox + sq % kRW) + (int64_t)(oy + sq / kRW) * a.s];
 #pragma unroll
@@ -282,7 +292,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
       sfl[q] = in ? rf[u] : (uint8_t)0;
     }
   }
-  if constexpr (KIND == kUpK)
+  if constexpr (kUp)
     if (tid < kCRN) sx[tid] = rc;
   if constexpr (kD)
     if (nseg > 0) {
@@ -317,7 +327,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
       __syncthreads();
     }
   }
-  if constexpr (KIND == kUpK) {
+  if constexpr (kUp) {
     // + P x_c (for an even index both parents coincide)
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
@@ -425,17 +435,19 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
       const uint8_t f = pq[c] >= 0 ? sfl[pq[c]] : 0;
       if (!(f & kFlagActive) || (f & kFlagStored)) pq[c] = -1;
     }
+    if constexpr (KIND != kProlongK)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
+      const int colour = rev ? 3 - c : c;
       // (the product is fused here as in the separate kernels, wherever the compiler puts it)
       if (pq[c] >= 0) su[pq[c]] = fma_t(T(3), pb[c], q1_sum<T, kRW>(su, pq[c])) * T(0.125);
       auto update = [&](const T* k, int qq, T bv) {
         const T v = bv - row_off<T, kRW>(k, su, qq);
         su[qq] = kD ? v * k[9] : v / k[4];
       };
-      if (sq >= 0 && scol == c) update(cf, sq, sb);
+      if (sq >= 0 && scol == colour) update(cf, sq, sb);
       extra([&](int q2, int c2, int, const T* k2, T b2) {
-        if (c2 == c) update(k2, q2, b2);
+        if (c2 == colour) update(k2, q2, b2);
       });
       __syncthreads();
     }
@@ -732,11 +744,13 @@ __global__ __launch_bounds__(64 * kBuildWaves) void k_delta_build(
 }
 inline int build_lds(int nc) { return 8 * nc * (9 + kBuildWaves) + 4 * nc + 16 * nc + ((nc + 15) & ~15); }
 
-// is region node (ri, rj) in its colour's phase range
+// region nodes whose stored rows a tile keeps: all but the outer ring (a sweep
+// also updates those outside their colour's phase bounds, from values that are
+// not exact there; no node inside the bounds reads them afterwards, in either
+// direction)
 template <int FT>
-__device__ inline bool in_phase(int ri, int rj, int c) {
-  using PH = Phase<FT>;
-  return ri >= PH::lox(c) && ri <= PH::hix(c) && rj >= PH::loy(c) && rj <= PH::hiy(c);
+__device__ inline bool in_region(int ri, int rj) {
+  return ri >= 1 && rj >= 1 && ri < Geo<FT>::RW - 1 && rj < Geo<FT>::RH - 1;
 }
 
 // One level as the tile plan sees it: flags, cut-vertex positions (null: no
@@ -812,7 +826,7 @@ __device__ void plan_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
 }
 
 // tiles: kept when the core holds an active node, or its coarse nodes one;
-// the stored rows of the region's phase ranges, the segments of D, and the
+// the stored rows of the region, the segments of D, and the
 // largest counts a record has to hold
 template <int FT>
 __global__ __launch_bounds__(256) void k_ftile_count(PlanLevel P, PlanLevel C, int nt, int eta, int* __restrict__ keep,
@@ -832,7 +846,7 @@ __global__ __launch_bounds__(256) void k_ftile_count(PlanLevel P, PlanLevel C, i
     const uint8_t f = P.fl[gi + (int64_t)gj * s];
     if (!(f & kFlagActive)) continue;
     if (ri >= kHX && ri < kHX + FT && rj >= kHY && rj < kHY + FT) act = 1;
-    if ((f & kFlagStored) && in_phase<FT>(ri, rj, (gi & 1) + 2 * (gj & 1))) atomicAdd(&cnt, 1);
+    if ((f & kFlagStored) && in_region<FT>(ri, rj)) atomicAdd(&cnt, 1);
   }
   const int Nc = N >> 1;
   for (int q = threadIdx.x; q < FT * FT / 4; q += blockDim.x) {
@@ -859,7 +873,7 @@ __global__ __launch_bounds__(256) void k_ftile_count(PlanLevel P, PlanLevel C, i
 
 // rows, columns and segments of one box into a tile's record
 __device__ void fill_box(const PlanLevel& P, int x, int y, int W, int H, int ex, int ey, BoxPlan& B, int base,
-                         int core_lo_x, int core_lo_y, int core, int* cols, FRow* rows, double* D, uint16_t* idx) {
+                         int core_lo_x, int core_lo_y, int core, int* cols, FRow* rows, double* D, double* DT, uint16_t* idx) {
   const int GW = W + 2 * ex, GH = H + 2 * ey, s = P.N + 1;
   for (int q = threadIdx.x; q < GW * GH; q += blockDim.x)
     if (B.local[q] >= 0) cols[B.local[q]] = P.npos[(x - ex + q % GW) + (int64_t)(y - ey + q / GW) * s];
@@ -878,9 +892,12 @@ __device__ void fill_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nseg = B.nseg;
   double* Db = D + (int64_t)base * 16;
+  double* Tb = DT ? DT + (int64_t)base * 16 : nullptr;
   uint16_t* ib = idx + (int64_t)base * 16;
-  auto put = [&](int sg, int k, double v, int c) {
-    Db[((int64_t)(k / 2) * nseg + sg) * 2 + k % 2] = v;
+  auto put = [&](int sg, int k, double v, double vt, int c) {
+    const int64_t w = ((int64_t)(k / 2) * nseg + sg) * 2 + k % 2;
+    Db[w] = v;
+    if (Tb) Tb[w] = vt;
     ib[((int64_t)(k / 8) * nseg + sg) * 8 + k % 8] = (uint16_t)c;
   };
   for (int e = wave; e < B.nrow; e += (int)blockDim.x / 64) {
@@ -899,12 +916,25 @@ __device__ void fill_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
       const unsigned long long m = __ballot(l >= 0);
       if (l >= 0) {
         const int w = n + __popcll(m & ((1ull << lane) - 1));
-        put(s0 + w / 16, w % 16, P.D[K.d + (int64_t)p * nc + c], l);
+        double vt = 0.0;
+        if (Tb) {
+          // the transposed step's D is the transpose: this row's column in the other node's row
+          const int pc = P.cols[K.col + c], ij = P.rows[pc];
+          const FBlock Q = P.blocks[P.bid[(ij & 0xffff) / kCell + ((ij >> 16) / kCell) * P.ncell]];
+          int lo = 0, hi = (Q.n >> 8) - 1;
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (P.cols[Q.col + mid] < K.row + p) lo = mid + 1;
+            else hi = mid;
+          }
+          if (P.cols[Q.col + lo] == K.row + p) vt = P.D[Q.d + (int64_t)(pc - Q.row) * (Q.n >> 8) + lo];
+        }
+        put(s0 + w / 16, w % 16, P.D[K.d + (int64_t)p * nc + c], vt, l);
       }
       n += __popcll(m);
     }
     const int full = (n + 15) / 16 * 16;
-    if (n + lane < full) put(s0 + (n + lane) / 16, (n + lane) % 16, 0.0, 0);
+    if (n + lane < full) put(s0 + (n + lane) / 16, (n + lane) % 16, 0.0, 0.0, 0);
   }
   __syncthreads();
 }
@@ -918,7 +948,8 @@ __global__ __launch_bounds__(256) void k_ftile_fill(PlanLevel P, PlanLevel C, co
                                                     const int* __restrict__ nstp, const int* __restrict__ segoff,
                                                     FTile* __restrict__ tiles, int* __restrict__ st_idx,
                                                     T* __restrict__ st_coef, const int* __restrict__ cutpos,
-                                                    double* __restrict__ D, uint16_t* __restrict__ idx) {
+                                                    double* __restrict__ D, double* __restrict__ DT,
+                                                    uint16_t* __restrict__ idx) {
   using GE = Geo<FT>;
   constexpr int kRW = GE::RW, kRH = GE::RH, kRN = GE::RN, kCRW = GE::CRW, kCRH = GE::CRH;
   __shared__ BoxPlan B;
@@ -937,7 +968,7 @@ __global__ __launch_bounds__(256) void k_ftile_fill(PlanLevel P, PlanLevel C, co
       const uint8_t f = on ? P.fl[k] : 0;
       inner = inner && (q >= kRN || ((f & kFlagActive) && !(f & kFlagStored)));
       const int c = (gi & 1) + 2 * (gj & 1);
-      on = on && (f & kFlagActive) && (f & kFlagStored) && in_phase<FT>(ri, rj, c);
+      on = on && (f & kFlagActive) && (f & kFlagStored) && in_region<FT>(ri, rj);
       const unsigned long long m = __ballot(on);
       if (on) {
         const int e = w + __popcll(m & ((1ull << lane) - 1));
@@ -968,8 +999,8 @@ __global__ __launch_bounds__(256) void k_ftile_fill(PlanLevel P, PlanLevel C, co
     R->nrow = B.nrow;
     R->ncol = B.ncol;
   }
-  fill_box(P, x0 - kHX, y0 - kHY, kRW, kRH, 4 * eta, 2 * eta, B, base, kHX, kHY, FT, R->cols, R->rows, D,
-              idx);
+  fill_box(P, x0 - kHX, y0 - kHY, kRW, kRH, 4 * eta, 2 * eta, B, base, kHX, kHY, FT, R->cols, R->rows, D, DT,
+           idx);
   plan_box(C, x0 / 2 - 3, y0 / 2 - 2, kCRW, kCRH, 4 * eta, 2 * eta, B);
   if (threadIdx.x == 0) {
     R->cseg = base + nseg;
@@ -978,7 +1009,7 @@ __global__ __launch_bounds__(256) void k_ftile_fill(PlanLevel P, PlanLevel C, co
     R->nccol = B.ncol;
   }
   fill_box(C, x0 / 2 - 3, y0 / 2 - 2, kCRW, kCRH, 4 * eta, 2 * eta, B, base + nseg, 0, 0, 0, R->ccols, R->crows, D,
-              idx);
+           nullptr, idx);
 }
 
 inline unsigned nblk(int64_t n, int tb) { return (unsigned)((n + tb - 1) / tb); }
@@ -1069,13 +1100,50 @@ void launch_sweep(mgfem_ctx* c, int l, bool norm, bool up) {
   L.zero = false;
 }
 
+// transposed cycles (float64): the cut sweeps come first in a step, so a step
+// applies them to the residual the sweep or prolongation before it left, and
+// nothing is pending behind it (L.pend: that residual exists; else the
+// iterate is zero)
+void launch_reverse_sweep(mgfem_ctx* c, int l) {
+  Level& L = c->lv[l];
+  FusedPlan& F = L.fp;
+  FArgs<double> a = fargs<double>(c, l);
+  a.xin = L.zero ? nullptr : L.X[L.cur];
+  a.xout = L.X[1 - L.cur];
+  a.reverse = 1;
+  if (F.ncut > 0) {
+    a.D = F.DT;
+    a.r = F.r[L.rp];
+    a.rows = L.pend ? nullptr : F.rows;
+    a.cut_out = F.r[1 - L.rp];
+  }
+  launch_tiles<double, kSweepK>(a, c->s);
+  L.cur = 1 - L.cur;
+  L.rp = 1 - L.rp;
+  L.pend = F.ncut > 0;
+  L.zero = false;
+}
+void launch_prolong(mgfem_ctx* c, int l) {
+  Level& L = c->lv[l];
+  FusedPlan& F = L.fp;
+  FArgs<double> a = fargs<double>(c, l);
+  a.xin = L.X[L.cur];
+  a.xout = L.X[1 - L.cur];
+  a.xc = c->lv[l + 1].X[c->lv[l + 1].cur];
+  if (F.ncut > 0) a.cut_out = F.r[1 - L.rp];
+  launch_tiles<double, kProlongK>(a, c->s);
+  L.cur = 1 - L.cur;
+  L.rp = 1 - L.rp;
+  L.pend = F.ncut > 0;
+}
+
 template <class T>
-void launch_rr(mgfem_ctx* c, int l, bool clear_coarse) {
+void launch_rr(mgfem_ctx* c, int l, bool clear_coarse, bool reverse) {
   Level& L = c->lv[l];
   Level& C = c->lv[l + 1];
   FArgs<T> a = fargs<T>(c, l);
   a.xin = L.zero ? nullptr : Of<T>::X(L, L.cur);
-  if (L.pend) {
+  if (L.pend && !reverse) {
     a.r = L.fp.r[L.rp];
     a.xs_out = L.fp.xs;
   }
@@ -1093,10 +1161,12 @@ void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up) {
   if (fp32) launch_sweep<float>(c, l, norm, up);
   else launch_sweep<double>(c, l, norm, up);
 }
-void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse) {
-  if (fp32) launch_rr<float>(c, l, clear_coarse);
-  else launch_rr<double>(c, l, clear_coarse);
+void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse, bool reverse) {
+  if (fp32) launch_rr<float>(c, l, clear_coarse, false);
+  else launch_rr<double>(c, l, clear_coarse, reverse);
 }
+void fused_reverse_sweep(mgfem_ctx* c, int l) { launch_reverse_sweep(c, l); }
+void fused_prolong(mgfem_ctx* c, int l) { launch_prolong(c, l); }
 void fused_apply(mgfem_ctx* c, int l) {
   Level& L = c->lv[l];
   FusedPlan& F = L.fp;
@@ -1297,13 +1367,16 @@ int build_fused(mgfem_ctx* c) {
     char* buf = nullptr;
     MGFEM_HIP_TRY(ctx_alloc(c, reinterpret_cast<void**>(&buf),
                             (size_t)F.ncut * (sizeof(int) + 3 * v) + (size_t)F.ntiles * sizeof(FTile) +
-                                nst * (sizeof(int) + 10 * v) + nseg * 160 + 4096));
+                                nst * (sizeof(int) + 10 * v) + nseg * 288 + 4096));
     F.tiles = reinterpret_cast<FTile*>(carve(buf, (size_t)F.ntiles * sizeof(FTile)));
     F.st_coef = carve(buf, nst * 10 * v);
     F.st_idx = reinterpret_cast<int*>(carve(buf, nst * sizeof(int)));
     F.rows = reinterpret_cast<int*>(carve(buf, (size_t)F.ncut * sizeof(int)));
     for (double** q : {&F.r[0], &F.r[1], &F.xs}) *q = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
-    F.D = reinterpret_cast<double2*>(carve(buf, nseg * 128));
+    if (!f32) {
+      F.D = reinterpret_cast<double2*>(carve(buf, nseg * 128));
+      F.DT = reinterpret_cast<double2*>(carve(buf, nseg * 128));
+    }
     F.Didx = reinterpret_cast<uint4*>(carve(buf, nseg * 32));
     if (t.nblk == 0) continue;
     MGFEM_HIP_TRY(hipMemcpyAsync(F.rows, t.rows, (size_t)F.ncut * sizeof(int), hipMemcpyDeviceToDevice, s));
@@ -1326,7 +1399,7 @@ int build_fused(mgfem_ctx* c) {
       using T = decltype(zero);
       hipLaunchKernelGGL(kern, dim3(t.nt * t.nt), dim3(256), 0, s, view(l), coarse_view(l), L.A, L.n, t.nt, eta,
                          t.keep, t.slot, t.stoff, t.nst, t.segoff, F.tiles, F.st_idx, static_cast<T*>(F.st_coef),
-                         (const int*)L.cutpos, f32 ? nullptr : reinterpret_cast<double*>(F.D),
+                         (const int*)L.cutpos, reinterpret_cast<double*>(F.D), reinterpret_cast<double*>(F.DT),
                          reinterpret_cast<uint16_t*>(F.Didx));
     };
     const bool big = tile_nodes(L.N) == 32;

@@ -110,6 +110,7 @@ struct FusedPlan {
   int* st_idx = nullptr;
   void* st_coef = nullptr;   // float64 or float32
   double2* D = nullptr;      // float64: segments of 16 values, fine then coarse
+  double2* DT = nullptr;     // the transposed steps' values (fine rows only)
   uint4* Didx = nullptr;     // their local columns
   int* rows = nullptr;       // per position: i | j << 16
   double* r[2] = {nullptr, nullptr};  // ping-pong residual at the cut vertices, by position
@@ -161,7 +162,8 @@ struct Level {
   int tp_max = 0, tc_max = 0;
   FusedPlan fp;
   int rp = 0;         // which fp.r belongs to the current iterate (host-side state, as the next two)
-  bool pend = false;  // the current iterate's last cut sweeps are not applied yet: x + D fp.r[rp]
+  bool pend = false;  // forward: the current iterate's last cut sweeps are not applied yet, x + D fp.r[rp];
+                      // transposed: fp.r[rp] is its residual at the cut vertices
   bool zero = false;  // the current iterate is zero and its buffer is not cleared
   bool empty() const { return bbox[0] > bbox[1]; }
 };
@@ -476,7 +478,9 @@ int build_tile_lists(mgfem_ctx* c);
 // a norm started from
 int build_fused(mgfem_ctx* c);
 void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up);
-void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse);
+void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse, bool reverse);
+void fused_reverse_sweep(mgfem_ctx* c, int l);  // transposed step: cut sweeps, then the sweep, colours 3 .. 0
+void fused_prolong(mgfem_ctx* c, int l);        // x + P x_c and the residual the next transposed step starts from
 void fused_apply(mgfem_ctx* c, int l);
 void fused_patch(mgfem_ctx* c, double* x);
 // the same for the problems of a batch (kinds kTeamSweep, kTeamRR)

@@ -1614,25 +1614,35 @@ void coarse_wg(mgfem_ctx* c, bool reverse, int reps) {
 template <class T>
 void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = false);
 template <class T>
-void cycle_fused(mgfem_ctx* c, int l, bool first_sweep_done) {
+void cycle_fused(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   constexpr bool f32 = sizeof(T) == 4;
   const int cl = coarse_level(c);
   Level& C = c->lv[l + 1];
   auto step = [&](bool up) {
+    if (reverse) {
+      fused_reverse_sweep(c, l);
+      return;
+    }
     fused_sweep(c, l, f32, false, up);
     if (f32) cut_sweeps<T>(c, l, false);
   };
-  for (int s = first_sweep_done ? 1 : 0; s < c->p.nu1; ++s) step(false);
-  fused_restrict(c, l, f32, l + 1 != cl && !C.fp.ok);
+  const int pre = reverse ? c->p.nu2 : c->p.nu1, post = reverse ? c->p.nu1 : c->p.nu2;
+  for (int s = first_sweep_done ? 1 : 0; s < pre; ++s) step(false);
+  fused_restrict(c, l, f32, l + 1 != cl && !C.fp.ok, reverse);
   C.pend = false;
   C.zero = l + 1 != cl && C.fp.ok;
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
   const int visits = two_grid ? c->p.coarse_cycles : (c->p.cycle == MGFEM_CYCLE_W ? 2 : 1);
-  if (l + 1 == cl) coarse_wg<T>(c, false, visits);
+  if (l + 1 == cl) coarse_wg<T>(c, reverse, visits);
   else
-    for (int g = 0; g < visits; ++g) cycle_level<T>(c, l + 1, false);
-  step(true);
-  for (int s = 1; s < c->p.nu2; ++s) step(false);
+    for (int g = 0; g < visits; ++g) cycle_level<T>(c, l + 1, reverse);
+  if (reverse) {
+    fused_prolong(c, l);
+    for (int s = 0; s < post; ++s) step(false);
+  } else {
+    step(true);
+    for (int s = 1; s < post; ++s) step(false);
+  }
 }
 
 template <class T>
@@ -1644,8 +1654,8 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
     return;
   }
   if (l == nl - 1) return;  // unreachable: the coarse plan always covers the coarsest level
-  if (!reverse && c->lv[l].fp.ok) {
-    cycle_fused<T>(c, l, first_sweep_done);
+  if (c->lv[l].fp.ok) {
+    cycle_fused<T>(c, l, reverse, first_sweep_done);
     return;
   }
   const int pre = reverse ? c->p.nu2 : c->p.nu1;
@@ -1657,7 +1667,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
   else launch_resrestrict<T, 16, 8, 512>(c, l);
   c->lv[l + 1].pend = false;  // the iterate there is zero now (in memory too)
-  c->lv[l + 1].zero = !reverse && l + 1 != cl && c->lv[l + 1].fp.ok;
+  c->lv[l + 1].zero = l + 1 != cl && c->lv[l + 1].fp.ok;
   // coarse-grid visits: gamma* (section 3.2); the two-grid scheme instead
   // solves the first coarse problem with coarse_cycles V-cycles from zero
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
@@ -1665,7 +1675,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   if (l + 1 == cl) coarse_wg<T>(c, reverse, visits);  // runs its visits itself
   else
     for (int g = 0; g < visits; ++g) cycle_level<T>(c, l + 1, reverse);
-  fused_apply(c, l + 1);  // the prolongation below reads the iterate from memory
+  if (!reverse) fused_apply(c, l + 1);  // the prolongation below reads the iterate from memory
   if (reverse || post == 0) {
     prolong<T>(c, l);
     for (int s = 0; s < post; ++s) smooth<T>(c, l, reverse);

@@ -52,7 +52,7 @@ def _separate(mg, psi, N, **kw):
 def test_fused_iterates(N, coarsest, psi, kw):
     """Three cycles from zero on random data: the oracle's iterates (and the
     separate kernels') to 1e-10 of their largest entry, as for the other
-    random draws; the transposed cycle is untouched by the forward state."""
+    random draws; the transposed cycle too, and neither changes the other."""
     mg = _gpu()
     psi = psi(N)
     rng = np.random.default_rng(N)
@@ -72,6 +72,13 @@ def test_fused_iterates(N, coarsest, psi, kw):
     uw, _ = s.solve(f, g, tol=-1.0, max_cycles=1, u0=us)
     usw, _ = sep.solve(f, g, tol=-1.0, max_cycles=1, u0=us)
     assert np.abs((uw - usw).cpu().numpy()).max() <= 1e-10 * scale
+    # transposed cycles: the separate kernels' (another D, colours 3 .. 0)
+    _, _, lam, hl = s.adjoint(g, tol=-1.0, max_cycles=3)
+    _, _, lams, hls = sep.adjoint(g, tol=-1.0, max_cycles=3)
+    assert float((lam - lams).abs().max()) <= 1e-10 * float(lams.abs().max())
+    np.testing.assert_allclose(hl, hls, rtol=1e-9, atol=1e-12 * hls[0])
+    u3, h3 = s.solve(f, g, tol=-1.0, max_cycles=3)
+    assert np.array_equal(h, h3) and np.array_equal(u, u3.cpu().numpy())
     if kw.get("cycle", 1) != 3:
         d = oasm.assemble(psi, N)
         H = omg.build_hierarchy(d, coarsest_n=coarsest)
