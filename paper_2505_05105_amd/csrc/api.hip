@@ -56,10 +56,32 @@ int check_params(const mgfem_params& p, int N, std::string& why) {
 namespace mgfem {
 void set_setup_error(const std::string& msg) { g_setup_error = msg; }
 
+// A handle holds some 300 arrays, most of them small; a hipMalloc, its fill
+// and its hipFree cost about 40 us each (half of a set-up at N = 1024), so
+// arrays share chunks of 1 MB, doubling to 64 MB, cleared once; an array
+// that would waste more than a quarter of the next chunk gets its own.
 hipError_t ctx_alloc(mgfem_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
-  if (bytes == 0) bytes = 8;
-  hipError_t e = hipMalloc(p, bytes);
+  bytes = (std::max<size_t>(bytes, 8) + 255) & ~(size_t)255;
+  const size_t chunk = c->chunk_next;
+  if (bytes > c->chunk_left && bytes <= chunk / 4 * 3) {
+    void* q = nullptr;
+    const hipError_t e = hipMalloc(&q, chunk);
+    if (e != hipSuccess) return e;
+    c->allocs.push_back(q);
+    c->chunk = static_cast<char*>(q);
+    c->chunk_left = chunk;
+    c->chunk_next = std::min<size_t>(2 * chunk, (size_t)64 << 20);
+    const hipError_t z = hipMemsetAsync(q, 0, chunk, c->s);
+    if (z != hipSuccess) return z;
+  }
+  if (bytes <= c->chunk_left) {
+    *p = c->chunk;
+    c->chunk += bytes;
+    c->chunk_left -= bytes;
+    return hipSuccess;
+  }
+  const hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) return e;
   c->allocs.push_back(*p);
   return hipMemsetAsync(*p, 0, bytes, c->s);
@@ -344,13 +366,13 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
     return bail(MGFEM_ERR_INVALID_ARG);
   }
   c->coarse_n = st.coarse_n;
-  rc = build_plans(c);
+  rc = build_coarse_plan(c);
   if (rc != MGFEM_OK) return bail(rc);
   rc = build_cut_rows(c);
   if (rc != MGFEM_OK) return bail(rc);
   rc = build_coarse_map(c, member);  // batch members run forward float cycles only
   if (rc != MGFEM_OK) return bail(rc);
-  rc = build_fused(c);
+  rc = build_cycle_plans(c);
   if (rc != MGFEM_OK) return bail(rc);
   SETUP_TRY(hipStreamSynchronize(c->s));
   mgfem_info& I = c->info;
@@ -631,7 +653,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   }
   if (hist) hist[0] = r0;
   c->l2_hist.push_back(l2);
-  if (!mixed) gather_snap(c, 0, false);
+  if (!mixed && !fused_level(c, 0, false)) gather_snap(c, 0, false);
   double prev = r0;
   int grow = 0, m = 0;
   bool conv = r0 <= rel_tol * bnorm;
@@ -701,7 +723,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
     out.g = g;
     // fused: the closing sweep read the next iterate and wrote the other buffer
     out.result = mixed ? L0.X[c->u_cur] : fused ? L0.X[1 - L0.cur] : L0.X[L0.cur];
-    out.patch = fused && L0.fp.ok && L0.fp.ncut > 0;
+    out.patch = fused && fused_level(c, 0, false) && L0.fp.ncut > 0;
     return MGFEM_OK;
   };
   if (status == MGFEM_OK && !conv && m < max_cycles) {
@@ -959,6 +981,9 @@ int mgfem_adjoint(mgfem_handle c, const double* dJdu_dev, double rel_tol, int32_
                   int32_t* n_cycles) {
   if (const int e = single_problem_check(c)) return e;
   if (!dJdu_dev || max_cycles < 0) return fail(c, MGFEM_ERR_INVALID_ARG, "dJdu must be a device pointer");
+  for (int l = 0; l < cycle_levels(c); ++l)
+    if (!fused_level(c, l, false))
+      if (const int e = separate_plans(c, l)) return e;
   double* lam = lam_dev ? lam_dev : c->lam;
   // the adjoint right-hand side must vanish off the active nodes
   launch_sub_active(c, c->F, dJdu_dev, c->zero);
@@ -1005,6 +1030,7 @@ int mgfem_smooth(mgfem_handle c, int32_t level, double* x_dev, const double* b_d
   if (!c || level < 0 || level + 1 >= (int)c->lv.size() || !x_dev || !b_dev || steps < 0)
     return c ? fail(c, MGFEM_ERR_INVALID_ARG, "bad level (the coarsest has no smoother) or pointer")
              : MGFEM_ERR_INVALID_ARG;
+  if (const int e = separate_plans(c, level)) return e;
   Level& L = c->lv[level];
   double* sx = L.X[0];
   double* sb = L.b;

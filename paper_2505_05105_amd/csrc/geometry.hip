@@ -18,6 +18,7 @@
 // only; the Neumann segments give the boundary mass GN of the load
 // int_{Gamma_N} g_N v; a cell with no Dirichlet segment has lambda_K = 0.
 #include <cmath>
+#include <type_traits>
 
 #include "mgfem_internal.h"
 
@@ -490,97 +491,192 @@ __global__ void k_classify(const double* __restrict__ psi, const double* __restr
 __constant__ int kVx[4] = {0, 1, 1, 0};
 __constant__ int kVy[4] = {0, 0, 1, 1};
 
-// Gather the rows of A, M, G of every node from its (up to) four cells.
+// Rows of A, M, G of every node from its (up to) four cells, in two passes:
+// k_assemble does the interior cells' parts and the flags of every node, from
+// constants (all indices known at compile time, so the rows stay in
+// registers), and lists the nodes with a cut cell; k_assemble_cut does those
+// nodes whole.  In one pass the boundary's waves carried the cut-cell
+// integrals' 1 KB of scratch for every node of the grid (4.9 ms at N = 4096).
 // With stiffness_only (the operator of the global eigenproblem) A receives the
 // cut stiffness S alone, its stored rows with the diagonal scaled by
 // 1 + diag_shift, and Kp the boundary normal-derivative matrix K = Kn / h.
-__global__ void k_assemble(const double* __restrict__ psi, const double* __restrict__ chi, int N,
-                           mgfem_params p, double h, const uint8_t* __restrict__ ctype,
-                           const double* __restrict__ clam, double* __restrict__ A, double* __restrict__ Mm,
-                           double* __restrict__ G, double* __restrict__ GN, uint8_t* __restrict__ flags,
-                           Stats* st, int stiffness_only, double diag_shift, double* __restrict__ Kp) {
-  __shared__ unsigned int nact;
-  if (threadIdx.x == 0) nact = 0;
+struct AsmArgs {
+  const double* psi;
+  const double* chi;
+  int N;
+  double h;
+  const uint8_t* ctype;
+  const double* clam;
+  double *A, *M, *G, *GN, *Kp;
+  uint8_t* flags;
+  Stats* st;
+  int stiffness_only;
+  double diag_shift;
+  int* cut;   // nodes of k_assemble_cut
+  int* ncut;
+};
+
+// the interior cell s of a node (compile-time): the other vertices' planes
+template <int S, class F>
+__device__ inline void interior_cell(F&& add) {
+  constexpr int dx[4] = {-1, 0, 0, -1}, dy[4] = {-1, -1, 0, 0}, loc[4] = {2, 3, 0, 1};
+  constexpr int vx[4] = {0, 1, 1, 0}, vy[4] = {0, 0, 1, 1};
+#pragma unroll
+  for (int m = 0; m < 4; ++m) add((dx[S] + vx[m] + 1) + 3 * (dy[S] + vy[m] + 1), (m - loc[S]) & 3);
+}
+
+__global__ __launch_bounds__(256) void k_assemble(AsmArgs q) {
+  __shared__ int nact, ncut, base;
+  if (threadIdx.x == 0) nact = ncut = 0;
   __syncthreads();
-  const int stride = N + 1;
-  const int64_t n = (int64_t)stride * stride;
-  int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int N = q.N, stride = N + 1;
+  const int64_t n = (int64_t)stride * stride, k = blockIdx.x * 256ll + threadIdx.x;
+  int slot = -1;
   if (k < n) {
-    int i = (int)(k % stride), j = (int)(k / stride);
-    double a[9], m[9], g[9], gn[9], kn[9];
-    for (int q = 0; q < 9; ++q) a[q] = m[q] = g[q] = gn[q] = kn[q] = 0.0;
-    bool active = false, regular = true;
-    // cells around the node, with the node's local vertex number in each
-    const int cdx[4] = {-1, 0, 0, -1}, cdy[4] = {-1, -1, 0, 0}, loc[4] = {2, 3, 0, 1};
-    const double hh36 = h * h / 36.0;
+    const int i = (int)(k % stride), j = (int)(k / stride);
+    const double hh36 = q.h * q.h / 36.0;
+    int ct[4];
+    bool off = false;
+#pragma unroll
     for (int s = 0; s < 4; ++s) {
-      int ci = i + cdx[s], cj = j + cdy[s];
-      if (ci < 0 || cj < 0 || ci >= N || cj >= N) {
-        regular = false;
-        continue;
-      }
-      int64_t c = ci + (int64_t)cj * N;
-      int t = ctype[c];
-      int lv = loc[s];
-      if (t != kInternal) regular = false;
-      if (t == kExternal) continue;
-      active = true;
-      if (t == kInternal) {
-        for (int mm = 0; mm < 4; ++mm) {
-          int dxo = ci + kVx[mm] - i, dyo = cj + kVy[mm] - j;
-          int pl = (dxo + 1) + 3 * (dyo + 1);
-          int sep = (mm - lv) & 3;  // 0 same, 1/3 edge, 2 opposite
+      const int ci = i + (s == 0 || s == 3 ? -1 : 0), cj = j + (s < 2 ? -1 : 0);
+      const bool in = ci >= 0 && cj >= 0 && ci < N && cj < N;
+      ct[s] = in ? q.ctype[ci + (int64_t)cj * N] : kExternal;
+      off = off || !in;
+    }
+    bool active = false, regular = !off, cut = false;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      active = active || ct[s] != kExternal;
+      regular = regular && ct[s] == kInternal;
+      cut = cut || (ct[s] != kExternal && ct[s] != kInternal);
+    }
+    if (cut) {
+      slot = atomicAdd(&ncut, 1);
+    } else {
+      double a[9], m[9];
+#pragma unroll
+      for (int p = 0; p < 9; ++p) a[p] = m[p] = 0.0;
+      auto cell = [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if (ct[S] != kInternal) return;
+        interior_cell<S>([&](int pl, int sep) {  // sep: 0 same, 1/3 edge, 2 opposite
           a[pl] += sep == 0 ? (4.0 / 6.0) : (sep == 2 ? (-2.0 / 6.0) : (-1.0 / 6.0));
           m[pl] += hh36 * (sep == 0 ? 4.0 : (sep == 2 ? 1.0 : 2.0));
+        });
+      };
+      cell(std::integral_constant<int, 0>{});
+      cell(std::integral_constant<int, 1>{});
+      cell(std::integral_constant<int, 2>{});
+      cell(std::integral_constant<int, 3>{});
+      if (q.stiffness_only && active && !regular) a[4] *= 1.0 + q.diag_shift;
+      // the planes start cleared: rows of inactive nodes, and G, GN and K off
+      // the cut cells, stay zero
+      if (active)
+#pragma unroll
+        for (int p = 0; p < 9; ++p) {
+          q.A[p * n + k] = a[p];
+          if (q.M) q.M[p * n + k] = m[p];  // mass and boundary load: finest level only
         }
-      } else {
-        double ps[4];
-        load_cell_psi(psi, stride, ci, cj, ps);
-        CutCell cc;
-        cut_cell(ps, cc);
-        if (chi) {
-          double cs[4];
-          load_cell_psi(chi, stride, ci, cj, cs);
-          mark_neumann(cc, cs);
-        }
-        CellInt I;
-        cell_integrals(cc, I);
-        double lh = clam[c] * h;  // lambda_K h
-        for (int mm = 0; mm < 4; ++mm) {
-          int dxo = ci + kVx[mm] - i, dyo = cj + kVy[mm] - j;
-          int pl = (dxo + 1) + 3 * (dyo + 1);
-          // A_K = S - B - B^T + lambda L with the symmetric pair summed first
-          if (stiffness_only) {
-            a[pl] += I.S[lv][mm];
-            kn[pl] += I.Kn[lv][mm] / h;
-          } else {
-            double sl = I.S[lv][mm] + lh * I.L[lv][mm];
-            double nit = I.B[lv][mm] + I.B[mm][lv];
-            a[pl] += sl - nit;
-          }
-          m[pl] += (h * h) * I.Mm[lv][mm];
-          // G_ij = lambda L_ij - int (n . grad phi_i) phi_j
-          g[pl] += lh * I.L[lv][mm] - I.B[mm][lv];
-          gn[pl] += h * I.LN[lv][mm];  // int_{Gamma_N} phi_i phi_j
-        }
-      }
-    }
-    if (stiffness_only && active && !regular) a[4] *= 1.0 + diag_shift;
-    for (int q = 0; q < 9; ++q) {
-      A[q * n + k] = a[q];
-      if (Kp) Kp[q * n + k] = kn[q];
-      if (Mm) Mm[q * n + k] = m[q];  // mass and boundary load: finest level only
-      if (G) G[q * n + k] = g[q];
-      if (GN) GN[q * n + k] = gn[q];
     }
     uint8_t f = 0;
     if (active) f |= kFlagActive;
     if (active && !regular) f |= kFlagStored;
-    flags[k] = f;
-    if (active) atomicAdd(&nact, 1u);
+    q.flags[k] = f;
+    const unsigned long long b = __ballot(active);
+    if ((threadIdx.x & 63) == __ffsll((long long)__ballot(true)) - 1 && b) atomicAdd(&nact, __popcll(b));
   }
   __syncthreads();
-  if (threadIdx.x == 0 && nact) atomicAdd(&st->active, (unsigned long long)nact);
+  if (threadIdx.x == 0) {
+    if (nact) atomicAdd(&q.st->active, (unsigned long long)nact);
+    base = ncut ? atomicAdd(q.ncut, ncut) : 0;
+  }
+  __syncthreads();
+  if (slot >= 0) q.cut[base + slot] = (int)k;
+}
+
+// one thread per node with a cut cell (the list's order is free: a node's row
+// does not depend on it)
+__global__ __launch_bounds__(64) void k_assemble_cut(AsmArgs q) {
+  const int nl = *q.ncut;
+  for (int w = blockIdx.x * 64 + threadIdx.x; w < nl; w += 64 * gridDim.x) {
+    const int N = q.N, stride = N + 1;
+    const int64_t n = (int64_t)stride * stride, k = q.cut[w];
+    const int i = (int)(k % stride), j = (int)(k / stride);
+    const double h = q.h, hh36 = h * h / 36.0;
+    double a[9], m[9], g[9], gn[9], kn[9];
+    for (int p = 0; p < 9; ++p) a[p] = m[p] = g[p] = gn[p] = kn[p] = 0.0;
+    bool regular = true;
+    // cells around the node, with the node's local vertex number in each
+    const int cdx[4] = {-1, 0, 0, -1}, cdy[4] = {-1, -1, 0, 0}, loc[4] = {2, 3, 0, 1};
+    for (int s = 0; s < 4; ++s) {
+      const int ci = i + cdx[s], cj = j + cdy[s], lv = loc[s];
+      if (ci < 0 || cj < 0 || ci >= N || cj >= N) {
+        regular = false;
+        continue;
+      }
+      const int64_t c = ci + (int64_t)cj * N;
+      const int t = q.ctype[c];
+      if (t != kInternal) regular = false;
+      if (t == kExternal) continue;
+      if (t == kInternal) {
+        for (int mm = 0; mm < 4; ++mm) {
+          const int pl = (ci + kVx[mm] - i + 1) + 3 * (cj + kVy[mm] - j + 1);
+          const int sep = (mm - lv) & 3;  // 0 same, 1/3 edge, 2 opposite
+          a[pl] += sep == 0 ? (4.0 / 6.0) : (sep == 2 ? (-2.0 / 6.0) : (-1.0 / 6.0));
+          m[pl] += hh36 * (sep == 0 ? 4.0 : (sep == 2 ? 1.0 : 2.0));
+        }
+        continue;
+      }
+      double ps[4];
+      load_cell_psi(q.psi, stride, ci, cj, ps);
+      CutCell cc;
+      cut_cell(ps, cc);
+      if (q.chi) {
+        double cs[4];
+        load_cell_psi(q.chi, stride, ci, cj, cs);
+        mark_neumann(cc, cs);
+      }
+      CellInt I;
+      cell_integrals(cc, I);
+      const double lh = q.clam[c] * h;  // lambda_K h
+      for (int mm = 0; mm < 4; ++mm) {
+        const int pl = (ci + kVx[mm] - i + 1) + 3 * (cj + kVy[mm] - j + 1);
+        // A_K = S - B - B^T + lambda L with the symmetric pair summed first
+        if (q.stiffness_only) {
+          a[pl] += I.S[lv][mm];
+          kn[pl] += I.Kn[lv][mm] / h;
+        } else {
+          const double sl = I.S[lv][mm] + lh * I.L[lv][mm];
+          const double nit = I.B[lv][mm] + I.B[mm][lv];
+          a[pl] += sl - nit;
+        }
+        m[pl] += (h * h) * I.Mm[lv][mm];
+        // G_ij = lambda L_ij - int (n . grad phi_i) phi_j
+        g[pl] += lh * I.L[lv][mm] - I.B[mm][lv];
+        gn[pl] += h * I.LN[lv][mm];  // int_{Gamma_N} phi_i phi_j
+      }
+    }
+    if (q.stiffness_only && !regular) a[4] *= 1.0 + q.diag_shift;
+    for (int p = 0; p < 9; ++p) {
+      q.A[p * n + k] = a[p];
+      if (q.Kp) q.Kp[p * n + k] = kn[p];
+      if (q.M) q.M[p * n + k] = m[p];
+      if (q.G) q.G[p * n + k] = g[p];
+      if (q.GN) q.GN[p * n + k] = gn[p];
+    }
+  }
+}
+
+// both passes; the list holds at most every node of the grid, its count is
+// cleared with the handle's memory
+int assemble(mgfem_ctx* c, AsmArgs q) {
+  const int64_t n = (int64_t)(q.N + 1) * (q.N + 1);
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &q.ncut, 1));
+  hipLaunchKernelGGL(k_assemble, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->s, q);
+  hipLaunchKernelGGL(k_assemble_cut, dim3(1024), dim3(64), 0, c->s, q);
+  MGFEM_HIP_TRY(hipGetLastError());
+  return MGFEM_OK;
 }
 
 // psi of a coarse grid: the fine input at every step-th node in each direction
@@ -626,11 +722,18 @@ int assemble_level(mgfem_ctx* c, int l, const double* psi_in, const double* chi_
                      pow(h, c->p.snap_alpha), st);
   hipLaunchKernelGGL(k_classify, dim3((unsigned)((nc + tb - 1) / tb)), dim3(tb), 0, c->s, (const double*)psi,
                      (const double*)chi, N, c->p, h, ct, lam, L.cellcut, st);
-  hipLaunchKernelGGL(k_assemble, dim3((unsigned)((n + tb - 1) / tb)), dim3(tb), 0, c->s, (const double*)psi,
-                     (const double*)chi, N, c->p, h, (const uint8_t*)ct, (const double*)lam, L.A, (double*)nullptr,
-                     (double*)nullptr, (double*)nullptr, L.flags, st, 0, 0.0, (double*)nullptr);
-  MGFEM_HIP_TRY(hipGetLastError());
-  return MGFEM_OK;
+  AsmArgs q{};
+  q.psi = psi;
+  q.chi = chi;
+  q.N = N;
+  q.h = h;
+  q.ctype = ct;
+  q.clam = lam;
+  q.A = L.A;
+  q.flags = L.flags;
+  q.st = st;
+  q.cut = reinterpret_cast<int*>(raw);  // the injected level set is not needed any more
+  return assemble(c, q);
 }
 
 int setup_geometry(mgfem_ctx* c, const double* psi_in, const double* chi_in) {
@@ -660,11 +763,26 @@ int setup_geometry(mgfem_ctx* c, const double* psi_in, const double* chi_in) {
                      n, thr, c->stats);
   hipLaunchKernelGGL(k_classify, dim3((unsigned)((nc + tb - 1) / tb)), dim3(tb), 0, c->s, c->psi, chi_in, N,
                      pk, c->h, c->cell_type, c->cell_lambda, L0.cellcut, c->stats);
-  hipLaunchKernelGGL(k_assemble, dim3((unsigned)((n + tb - 1) / tb)), dim3(tb), 0, c->s, c->psi, chi_in, N,
-                     pk, c->h, c->cell_type, c->cell_lambda, L0.A, c->M, c->G, c->GN, L0.flags,
-                     c->stats, stiff ? 1 : 0, stiff ? kStiffnessShift : 0.0, c->Kp);
-  MGFEM_HIP_TRY(hipGetLastError());
-  return MGFEM_OK;
+  AsmArgs q{};
+  q.psi = c->psi;
+  q.chi = chi_in;
+  q.N = N;
+  q.h = c->h;
+  q.ctype = c->cell_type;
+  q.clam = c->cell_lambda;
+  q.A = L0.A;
+  q.M = c->M;
+  q.G = c->G;
+  q.GN = c->GN;
+  q.Kp = c->Kp;
+  q.flags = L0.flags;
+  q.st = c->stats;
+  q.stiffness_only = stiff ? 1 : 0;
+  q.diag_shift = stiff ? kStiffnessShift : 0.0;
+  q.cut = reinterpret_cast<int*>(c->F);  // the load vector's memory, cleared below
+  const int e = assemble(c, q);
+  if (e == MGFEM_OK) launch_zero(c, c->F, n);
+  return e;
 }
 
 }  // namespace mgfem

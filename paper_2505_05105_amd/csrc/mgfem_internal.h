@@ -161,6 +161,7 @@ struct Level {
   int* tc_pos = nullptr;
   int tp_max = 0, tc_max = 0;
   FusedPlan fp;
+  bool grouped = false, tiled = false;  // the separate kernels' plans exist
   int rp = 0;         // which fp.r belongs to the current iterate (host-side state, as the next two)
   bool pend = false;  // forward: the current iterate's last cut sweeps are not applied yet, x + D fp.r[rp];
                       // transposed: fp.r[rp] is its residual at the cut vertices
@@ -215,6 +216,7 @@ constexpr int kRedSlots = 8;
 // the right-hand side of the first coarse level's active nodes to the iterate
 // the coarse part leaves there, rows and columns in the order of idx.
 constexpr int kMaxMapNodes = 4096;  // larger first coarse levels keep the single-workgroup cycle
+constexpr int kMaxMapNodes64 = 2600;  // float64: the map is not extended to larger levels
 struct CoarseMap {
   int level = -1;        // the level whose coarse part the map stands for (-1: no map)
   int n = 0;             // active nodes of that level
@@ -368,7 +370,9 @@ struct mgfem_ctx {
   unsigned int* sweep_counter = nullptr;
   mgfem::Stats* stats = nullptr;  // device
   mgfem_info info{};
-  std::vector<void*> allocs;
+  std::vector<void*> allocs;        // device memory to release: chunks and large arrays
+  char* chunk = nullptr;            // the current chunk's free part
+  size_t chunk_left = 0, chunk_next = (size_t)1 << 20;
   mgfem::Profiler prof;
   // graph replay of the solve loop
   bool use_graphs = true;
@@ -460,7 +464,9 @@ void first_sweep_with_norm(mgfem_ctx* c);
 void run_cycle(mgfem_ctx* c, const CycleOpts& o);
 void smooth_level(mgfem_ctx* c, int l, bool reverse, bool fp32);
 void gather_snap(mgfem_ctx* c, int l, bool fp32);
-int build_plans(mgfem_ctx* c);  // cut groups and the coarse single-workgroup layout
+int build_coarse_plan(mgfem_ctx* c);             // the coarse single-workgroup layout
+int build_cutpos(mgfem_ctx* c, int l);           // cut-list positions by node
+int build_cut_groups(mgfem_ctx* c, int l);       // snapshots and cut groups of a level
 // the coarse part as a dense map (forward and, unless forward_only, transposed,
 // float64; float32 forward for mixed precision); skipped for large first
 // coarse levels and when MGFEM_NO_COARSE_MAP=1 at set-up
@@ -470,13 +476,23 @@ int build_coarse_map(mgfem_ctx* c, bool forward_only);
 int scratch_init(int* device);
 // mgfem_setup for one problem of a batched handle (forward coarse map only)
 int setup_member(const double* psi_dev, int32_t N, const mgfem_params* p, void* stream, mgfem_handle* out);
-int build_tile_lists(mgfem_ctx* c);
+int build_tile_list(mgfem_ctx* c, int l);
+// a level's cut groups, and with them its tile lists, built once
+int cut_plan(mgfem_ctx* c, int l);
+int separate_plans(mgfem_ctx* c, int l);
+int build_cycle_plans(mgfem_ctx* c);
+int cycle_levels(const mgfem_ctx* c);  // levels above the coarse part
 // fused smoothing steps (fused.hip): plans, one sweep (of x, or with `up` of
 // x + P x_c; norm: the residual norm of its incoming iterate), residual and
 // restriction, the pending cut sweeps applied in place (no-op when none are),
 // and the cut vertices of a level-0 array from the values the last sweep with
 // a norm started from
 int build_fused(mgfem_ctx* c);
+// level l has fused plans in this precision (a handle has them in the one its
+// solves run in; the adjoint of a mixed handle runs the separate kernels)
+inline bool fused_level(const mgfem_ctx* c, int l, bool f32) {
+  return c->lv[l].fp.ok && f32 == (c->p.precision == MGFEM_PREC_MIXED);
+}
 void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up);
 void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse, bool reverse);
 void fused_reverse_sweep(mgfem_ctx* c, int l);  // transposed step: cut sweeps, then the sweep, colours 3 .. 0

@@ -779,7 +779,7 @@ __device__ void rr_tile(const ResArgs<T>& a, const int t) {
     const T hi = r0[RW] + T(0.5) * (r0[RW - 1] + r0[RW + 1]);
     a.bc[kc] = mid + T(0.5) * (lo + hi);
     a.xc[kc] = T(0);
-    if (f & kFlagCut) a.snapc[a.cutposc[kc]] = T(0);
+    if (a.cutposc && (f & kFlagCut)) a.snapc[a.cutposc[kc]] = T(0);  // null: no cut kernel there
   }
 }
 
@@ -1317,6 +1317,54 @@ __global__ __launch_bounds__(64 * kMapWaves) void k_coarse_apply_multi(const Map
   map_rows<T>(E.B, E.ld, E.idx, E.n, E.b, E.x, w.y, reinterpret_cast<T*>(smem));
 }
 
+// the same product for kMapCols right-hand sides of one map (set-up of the
+// extended map: thousands of columns), a row of B read once for all of them;
+// every column's sum runs in the order of map_rows
+constexpr int kMapCols = 8;
+__global__ __launch_bounds__(64 * kMapWaves) void k_map_columns(const MapEntry<double>* __restrict__ tab, int J,
+                                                                int rows) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* sb = reinterpret_cast<double*>(smem);
+  const int blk = blockIdx.x % rows, j0 = (blockIdx.x / rows) * kMapCols, nc = min(kMapCols, J - j0);
+  const MapEntry<double>& E = tab[j0];
+  const int ld = E.ld, n = E.n;
+  const int* __restrict__ idx = E.idx;
+  for (int c = 0; c < nc; ++c) {
+    const double* __restrict__ b = tab[j0 + c].b;
+    for (int j = threadIdx.x; j < ld; j += 64 * kMapWaves) sb[c * ld + j] = j < n ? b[idx[j]] : 0.0;
+  }
+  __syncthreads();
+  constexpr int U = 4, G = 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blk * kMapWaves + wave;
+  const double* row = E.B + (int64_t)(r < n ? r : 0) * ld;
+  double acc[kMapCols];
+#pragma unroll
+  for (int c = 0; c < kMapCols; ++c) acc[c] = 0.0;
+  for (int base = 0; base < ld; base += U * 64 * G) {
+    double2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int col = base + (u * 64 + lane) * G;
+      v[u] = col < ld ? *reinterpret_cast<const double2*>(row + col) : double2{};
+    }
+#pragma unroll
+    for (int c = 0; c < kMapCols; ++c)
+      if (c < nc)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int col = base + (u * 64 + lane) * G;
+          if (col < ld) acc[c] += Vec16<double>::dot(v[u], sb + c * ld + col);
+        }
+  }
+#pragma unroll
+  for (int c = 0; c < kMapCols; ++c) {
+    double s = acc[c];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0 && r < n && c < nc) tab[j0 + c].x[idx[r]] = s;
+  }
+}
+
 __global__ void k_f64_to_f32(const double* __restrict__ s, float* __restrict__ d, int64_t n) {
   const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (q < n) d[q] = (float)s[q];
@@ -1628,9 +1676,10 @@ void cycle_fused(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   };
   const int pre = reverse ? c->p.nu2 : c->p.nu1, post = reverse ? c->p.nu1 : c->p.nu2;
   for (int s = first_sweep_done ? 1 : 0; s < pre; ++s) step(false);
-  fused_restrict(c, l, f32, l + 1 != cl && !C.fp.ok, reverse);
+  const bool fc = l + 1 != cl && fused_level(c, l + 1, f32);
+  fused_restrict(c, l, f32, l + 1 != cl && !fc, reverse);
   C.pend = false;
-  C.zero = l + 1 != cl && C.fp.ok;
+  C.zero = fc;
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
   const int visits = two_grid ? c->p.coarse_cycles : (c->p.cycle == MGFEM_CYCLE_W ? 2 : 1);
   if (l + 1 == cl) coarse_wg<T>(c, reverse, visits);
@@ -1654,7 +1703,8 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
     return;
   }
   if (l == nl - 1) return;  // unreachable: the coarse plan always covers the coarsest level
-  if (c->lv[l].fp.ok) {
+  constexpr bool f32 = sizeof(T) == 4;
+  if (fused_level(c, l, f32)) {
     cycle_fused<T>(c, l, reverse, first_sweep_done);
     return;
   }
@@ -1667,7 +1717,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
   else launch_resrestrict<T, 16, 8, 512>(c, l);
   c->lv[l + 1].pend = false;  // the iterate there is zero now (in memory too)
-  c->lv[l + 1].zero = l + 1 != cl && c->lv[l + 1].fp.ok;
+  c->lv[l + 1].zero = l + 1 != cl && fused_level(c, l + 1, f32);
   // coarse-grid visits: gamma* (section 3.2); the two-grid scheme instead
   // solves the first coarse problem with coarse_cycles V-cycles from zero
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
@@ -1694,7 +1744,7 @@ void run_cycle(mgfem_ctx* c, const CycleOpts& o) {
 }
 
 void first_sweep_with_norm(mgfem_ctx* c) {
-  if (!c->lv[0].fp.ok) {
+  if (!fused_level(c, 0, false)) {
     sweep<double>(c, 0, false, true);
     return;
   }
@@ -1886,100 +1936,97 @@ __global__ void k_tile_plan(const uint8_t* __restrict__ fl, const double* __rest
   }
 }
 
-int build_tile_lists(mgfem_ctx* c) {
-  const int nl = (int)c->lv.size();
-  for (int l = 0; l + 1 < nl; ++l) {  // every level with a smoother
-    Level& L = c->lv[l];
-    if (L.empty()) continue;
-    const int shape = sweep_shape(c, l);
-    const int TW = shape == kShapeSmall ? 16 : 64;
-    const int TH = shape == kShapeFinest ? 32 : 16;
-    const int ntx = (L.bbox[1] - L.bbox[0] + TW) / TW, nty = (L.bbox[3] - L.bbox[2] + TH) / TH;
-    int* act = nullptr;
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &act, ntx * nty));
-    hipLaunchKernelGGL(k_tile_active, dim3(ntx * nty), dim3(256), 0, c->s, L.flags, L.stride, L.bbox[0], L.bbox[2],
-                       L.bbox[1], L.bbox[3], TW, TH, ntx, nty, act);
-    std::vector<int> h(ntx * nty);
-    MGFEM_HIP_TRY(hipMemcpyAsync(h.data(), act, h.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
+int build_tile_list(mgfem_ctx* c, int l) {
+  Level& L = c->lv[l];
+  if (L.empty()) return MGFEM_OK;
+  const int shape = sweep_shape(c, l);
+  const int TW = shape == kShapeSmall ? 16 : 64;
+  const int TH = shape == kShapeFinest ? 32 : 16;
+  const int ntx = (L.bbox[1] - L.bbox[0] + TW) / TW, nty = (L.bbox[3] - L.bbox[2] + TH) / TH;
+  int* act = nullptr;
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &act, ntx * nty));
+  hipLaunchKernelGGL(k_tile_active, dim3(ntx * nty), dim3(256), 0, c->s, L.flags, L.stride, L.bbox[0], L.bbox[2],
+                     L.bbox[1], L.bbox[3], TW, TH, ntx, nty, act);
+  std::vector<int> h(ntx * nty);
+  MGFEM_HIP_TRY(hipMemcpyAsync(h.data(), act, h.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
+  MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
+  std::vector<int> list;
+  for (int t = 0; t < ntx * nty; ++t)
+    if (h[t]) list.push_back(t);
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tiles, std::max<size_t>(1, list.size())));
+  if (!list.empty())
+    MGFEM_HIP_TRY(hipMemcpyAsync(L.tiles, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
+  L.ntiles = (int)list.size();
+  L.tile_shape = shape;
+  // tile plans: count, offsets, fill
+  const int nt = L.ntiles;
+  int *cnt = nullptr, *ccnt = nullptr;
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &cnt, std::max(1, nt)));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &ccnt, std::max(1, nt)));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_off, nt + 1));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_off, nt + 1));
+  if (nt > 0)
+    hipLaunchKernelGGL(k_tile_plan, dim3(nt), dim3(256), 0, c->s, L.flags, L.A, L.A32, L.n, L.cutpos, L.N,
+                       L.stride, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], TW, TH, ntx, L.tiles, 0, cnt, ccnt,
+                       nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  MGFEM_HIP_TRY(hipGetLastError());
+  std::vector<int> hc(std::max(1, nt)), hcc(std::max(1, nt)), ho(nt + 1), hco(nt + 1);
+  MGFEM_HIP_TRY(hipMemcpyAsync(hc.data(), cnt, hc.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
+  MGFEM_HIP_TRY(hipMemcpyAsync(hcc.data(), ccnt, hcc.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
+  MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
+  ho[0] = hco[0] = 0;
+  L.tp_max = L.tc_max = 0;
+  for (int q = 0; q < nt; ++q) {
+    ho[q + 1] = ho[q] + hc[q];
+    hco[q + 1] = hco[q] + hcc[q];
+    L.tp_max = std::max(L.tp_max, hc[q]);
+    L.tc_max = std::max(L.tc_max, hcc[q]);
+  }
+  MGFEM_HIP_TRY(hipMemcpyAsync(L.tp_off, ho.data(), ho.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
+  MGFEM_HIP_TRY(hipMemcpyAsync(L.tc_off, hco.data(), hco.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_idx, std::max(1, ho[nt])));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_coef, 9 * (size_t)std::max(1, ho[nt])));
+  if (L.A32) MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_coef32, 9 * (size_t)std::max(1, ho[nt])));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_idx, std::max(1, hco[nt])));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_pos, std::max(1, hco[nt])));
+  if (nt > 0)
+    hipLaunchKernelGGL(k_tile_plan, dim3(nt), dim3(256), 0, c->s, L.flags, L.A, L.A32, L.n, L.cutpos, L.N,
+                       L.stride, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], TW, TH, ntx, L.tiles, 1, nullptr,
+                       nullptr, L.tp_off, L.tc_off, L.tp_idx, L.tp_coef, L.tp_coef32, L.tc_idx, L.tc_pos);
+  MGFEM_HIP_TRY(hipGetLastError());
+  std::vector<int> meta(8 * (size_t)std::max(1, nt), 0);
+  for (int q = 0; q < nt; ++q) {
+    meta[8 * q + 0] = list[q];
+    meta[8 * q + 1] = ho[q];
+    meta[8 * q + 2] = hc[q];
+    meta[8 * q + 3] = hco[q];
+    meta[8 * q + 4] = hcc[q];
+  }
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tmeta, meta.size()));
+  MGFEM_HIP_TRY(hipMemcpyAsync(L.tmeta, meta.data(), meta.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
+  // the host vectors must outlive the asynchronous copies
+  MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
+  // residual-restriction tiles: coarse tiles (the shape launch_resrestrict
+  // uses for this level) with an active coarse node
+  Level& C = c->lv[l + 1];
+  if (!C.empty()) {
+    const int CW = L.N >= 1024 ? 32 : 16, CH = L.N >= 1024 ? 16 : 8;
+    const int cnx = (C.bbox[1] - C.bbox[0] + CW) / CW, cny = (C.bbox[3] - C.bbox[2] + CH) / CH;
+    int* cact = nullptr;
+    MGFEM_HIP_TRY(ctx_alloc_t(c, &cact, cnx * cny));
+    hipLaunchKernelGGL(k_tile_active, dim3(cnx * cny), dim3(256), 0, c->s, C.flags, C.stride, C.bbox[0], C.bbox[2],
+                       C.bbox[1], C.bbox[3], CW, CH, cnx, cny, cact);
+    std::vector<int> hca(cnx * cny);
+    MGFEM_HIP_TRY(hipMemcpyAsync(hca.data(), cact, hca.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
     MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-    std::vector<int> list;
-    for (int t = 0; t < ntx * nty; ++t)
-      if (h[t]) list.push_back(t);
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tiles, std::max<size_t>(1, list.size())));
-    if (!list.empty())
-      MGFEM_HIP_TRY(hipMemcpyAsync(L.tiles, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
-    L.ntiles = (int)list.size();
-    L.tile_shape = shape;
-    // tile plans: count, offsets, fill
-    const int nt = L.ntiles;
-    int *cnt = nullptr, *ccnt = nullptr;
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &cnt, std::max(1, nt)));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &ccnt, std::max(1, nt)));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_off, nt + 1));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_off, nt + 1));
-    if (nt > 0)
-      hipLaunchKernelGGL(k_tile_plan, dim3(nt), dim3(256), 0, c->s, L.flags, L.A, L.A32, L.n, L.cutpos, L.N,
-                         L.stride, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], TW, TH, ntx, L.tiles, 0, cnt, ccnt,
-                         nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    MGFEM_HIP_TRY(hipGetLastError());
-    std::vector<int> hc(std::max(1, nt)), hcc(std::max(1, nt)), ho(nt + 1), hco(nt + 1);
-    MGFEM_HIP_TRY(hipMemcpyAsync(hc.data(), cnt, hc.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
-    MGFEM_HIP_TRY(hipMemcpyAsync(hcc.data(), ccnt, hcc.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
+    std::vector<int> rl;
+    for (int q = 0; q < cnx * cny; ++q)
+      if (hca[q]) rl.push_back(q);
+    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.rr_tiles, std::max<size_t>(1, rl.size())));
+    if (!rl.empty())
+      MGFEM_HIP_TRY(hipMemcpyAsync(L.rr_tiles, rl.data(), rl.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
     MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-    ho[0] = hco[0] = 0;
-    L.tp_max = L.tc_max = 0;
-    for (int q = 0; q < nt; ++q) {
-      ho[q + 1] = ho[q] + hc[q];
-      hco[q + 1] = hco[q] + hcc[q];
-      L.tp_max = std::max(L.tp_max, hc[q]);
-      L.tc_max = std::max(L.tc_max, hcc[q]);
-    }
-    MGFEM_HIP_TRY(hipMemcpyAsync(L.tp_off, ho.data(), ho.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
-    MGFEM_HIP_TRY(hipMemcpyAsync(L.tc_off, hco.data(), hco.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_idx, std::max(1, ho[nt])));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_coef, 9 * (size_t)std::max(1, ho[nt])));
-    if (L.A32) MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tp_coef32, 9 * (size_t)std::max(1, ho[nt])));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_idx, std::max(1, hco[nt])));
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tc_pos, std::max(1, hco[nt])));
-    if (nt > 0)
-      hipLaunchKernelGGL(k_tile_plan, dim3(nt), dim3(256), 0, c->s, L.flags, L.A, L.A32, L.n, L.cutpos, L.N,
-                         L.stride, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], TW, TH, ntx, L.tiles, 1, nullptr,
-                         nullptr, L.tp_off, L.tc_off, L.tp_idx, L.tp_coef, L.tp_coef32, L.tc_idx, L.tc_pos);
-    MGFEM_HIP_TRY(hipGetLastError());
-    std::vector<int> meta(8 * (size_t)std::max(1, nt), 0);
-    for (int q = 0; q < nt; ++q) {
-      meta[8 * q + 0] = list[q];
-      meta[8 * q + 1] = ho[q];
-      meta[8 * q + 2] = hc[q];
-      meta[8 * q + 3] = hco[q];
-      meta[8 * q + 4] = hcc[q];
-    }
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &L.tmeta, meta.size()));
-    MGFEM_HIP_TRY(hipMemcpyAsync(L.tmeta, meta.data(), meta.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
-    // the host vectors must outlive the asynchronous copies
-    MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-    // residual-restriction tiles: coarse tiles (the shape launch_resrestrict
-    // uses for this level) with an active coarse node
-    Level& C = c->lv[l + 1];
-    if (!C.empty()) {
-      const int CW = L.N >= 1024 ? 32 : 16, CH = L.N >= 1024 ? 16 : 8;
-      const int cnx = (C.bbox[1] - C.bbox[0] + CW) / CW, cny = (C.bbox[3] - C.bbox[2] + CH) / CH;
-      int* cact = nullptr;
-      MGFEM_HIP_TRY(ctx_alloc_t(c, &cact, cnx * cny));
-      hipLaunchKernelGGL(k_tile_active, dim3(cnx * cny), dim3(256), 0, c->s, C.flags, C.stride, C.bbox[0], C.bbox[2],
-                         C.bbox[1], C.bbox[3], CW, CH, cnx, cny, cact);
-      std::vector<int> hca(cnx * cny);
-      MGFEM_HIP_TRY(hipMemcpyAsync(hca.data(), cact, hca.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
-      MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-      std::vector<int> rl;
-      for (int q = 0; q < cnx * cny; ++q)
-        if (hca[q]) rl.push_back(q);
-      MGFEM_HIP_TRY(ctx_alloc_t(c, &L.rr_tiles, std::max<size_t>(1, rl.size())));
-      if (!rl.empty())
-        MGFEM_HIP_TRY(hipMemcpyAsync(L.rr_tiles, rl.data(), rl.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
-      MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-      L.rr_ntiles = (int)rl.size();
-    }
+    L.rr_ntiles = (int)rl.size();
   }
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
   return MGFEM_OK;
@@ -2067,7 +2114,7 @@ int upload_table(mgfem_ctx* c, const std::vector<E>& h, void** dev) {
 // its transpose (the transposed cycle is the cycle's adjoint).  Not for
 // W-cycles (their coarse part repeats), nor up to level 1 of the two-grid
 // scheme (its first coarse problem takes coarse_cycles cycles).
-int extend_coarse_map(mgfem_ctx* c) {
+int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
   CoarseMap& M = c->cplan.map;
   const char* env = std::getenv("MGFEM_NO_MAP_EXTENSION");
   if (env && env[0] && env[0] != '0') return MGFEM_OK;
@@ -2077,7 +2124,8 @@ int extend_coarse_map(mgfem_ctx* c) {
     if (c->p.cycle == MGFEM_CYCLE_TWO_GRID && L < 2) break;
     Level& Ll = c->lv[L];
     Level& Lc = c->lv[C];
-    if (Ll.empty() || Ll.n_active > kMaxMapNodes || sweep_shape(c, L) != kShapeSmall || Ll.N >= 1024) break;
+    if (Ll.empty() || Ll.n_active > max_nodes || sweep_shape(c, L) != kShapeSmall || Ll.N >= 1024) break;
+    if (const int e = separate_plans(c, L)) return e;
     const bool has_cut = c->p.eta > 0 && Ll.cut_off[4] > 0;
     if (has_cut && !Ll.cp.ok) break;
     // the active nodes of level L, ascending: rows and columns of the new map
@@ -2098,8 +2146,8 @@ int extend_coarse_map(mgfem_ctx* c) {
     // vectors of a batch of J columns (freed below)
     const int J = std::min(n, 512);
     const int64_t nL = Ll.n, nC = Lc.n;
-    const int64_t ncL = std::max(1, Ll.cut_off[4]), ncC = std::max(1, Lc.cut_off[4]);
-    const int64_t total = 3 * J * nL + J * ncL + 3 * J * nC + J * ncC;
+    const int64_t ncL = std::max(1, Ll.cut_off[4]);
+    const int64_t total = 3 * J * nL + J * ncL + 3 * J * nC;
     double* buf = nullptr;
     MGFEM_HIP_TRY(hipMalloc(&buf, total * sizeof(double)));
     double* XL = buf;               // buffer 0 of column j at XL + j nL, buffer 1 at XL + (J + j) nL
@@ -2107,7 +2155,6 @@ int extend_coarse_map(mgfem_ctx* c) {
     double* sL = bL + J * nL;
     double* XC = sL + J * ncL;      // level C: buffer 0 (the map's output) and buffer 1
     double* bC = XC + 2 * J * nC;
-    double* sC = bC + J * nC;
     std::vector<SweepEntry<double>> ts(J);
     std::vector<CutEntry<double>> tc(J);
     std::vector<RrEntry<double>> tr(J);
@@ -2135,7 +2182,7 @@ int extend_coarse_map(mgfem_ctx* c) {
       r.a = rr_args<double, 16, 8>(c, L);
       r.a.b = bL + j * nL;
       r.a.bc = bC + j * nC;
-      r.a.snapc = sC + j * ncC;
+      r.a.cutposc = nullptr;  // level C is the map's: no cut kernel reads its snapshot
       r.X[0] = e.X[0];
       r.X[1] = e.X[1];
       r.XC[0] = XC + j * nC;
@@ -2175,6 +2222,8 @@ int extend_coarse_map(mgfem_ctx* c) {
     const int2* wr = wc + (size_t)J * uc;
     const int2* wm = wr + (size_t)J * ur;
     const int cut_lds = Ll.cp.lds64, map_lds = M.ld * (int)sizeof(double);
+    // several columns per workgroup where their right-hand sides fit in LDS
+    const bool wide = kMapCols * map_lds <= 128 * 1024;
     for (int j0 = 0; j0 < n && !rc; j0 += J) {
       const int Jc = std::min(J, n - j0);
       hipLaunchKernelGGL(k_zero_f64, dim3(nblk(total, 256)), dim3(256), 0, c->s, buf, total);
@@ -2187,7 +2236,11 @@ int extend_coarse_map(mgfem_ctx* c) {
       };
       for (int st = 0; st < c->p.nu1; ++st) smooth_cols(false);
       col_launch(c->s, kTeamRR, dtr, wr, Jc * ur, par, 0, 0);
-      col_launch(c->s, kTeamMap, dtm, wm, Jc * um, 0, 0, map_lds);
+      if (wide)
+        hipLaunchKernelGGL(k_map_columns, dim3(um * ((Jc + kMapCols - 1) / kMapCols)), dim3(64 * kMapWaves),
+                           kMapCols * map_lds, c->s, static_cast<const MapEntry<double>*>(dtm), Jc, um);
+      else
+        col_launch(c->s, kTeamMap, dtm, wm, Jc * um, 0, 0, map_lds);
       smooth_cols(true);  // x + P x_c, then the step
       for (int st = 1; st < c->p.nu2; ++st) smooth_cols(false);
       hipLaunchKernelGGL(k_gather_cols, dim3(nblk(Jc, 256), n), dim3(256), 0, c->s,
@@ -2228,6 +2281,41 @@ int extend_coarse_map(mgfem_ctx* c) {
   return MGFEM_OK;
 }
 
+int cycle_levels(const mgfem_ctx* c) { return coarse_level(c); }
+int separate_plans(mgfem_ctx* c, int l) {
+  if (const int e = cut_plan(c, l)) return e;
+  Level& L = c->lv[l];
+  if (!L.tiled)
+    if (const int e = build_tile_list(c, l)) return e;
+  L.tiled = true;
+  return MGFEM_OK;
+}
+int cut_plan(mgfem_ctx* c, int l) {
+  Level& L = c->lv[l];
+  if (!L.grouped)
+    if (const int e = build_cut_groups(c, l)) return e;
+  L.grouped = true;
+  return MGFEM_OK;
+}
+
+// The plans of a handle's cycles: the fused levels' tiles, and the cut groups
+// and tile lists of the separate kernels where they run (the other levels;
+// in mixed precision the cut groups everywhere, and level 0's tiles for the
+// outer step).  mgfem_smooth and an unfused batch build the rest on first use.
+int build_cycle_plans(mgfem_ctx* c) {
+  const int cl = coarse_level(c);
+  const bool f32 = c->p.precision == MGFEM_PREC_MIXED;
+  if (const int e = build_cutpos(c, 0)) return e;  // the gradient's G^T too
+  if (f32)
+    for (int l = 0; l < cl; ++l)
+      if (const int e = cut_plan(c, l)) return e;
+  if (const int e = build_fused(c)) return e;
+  for (int l = 0; l < cl; ++l)
+    if (!c->lv[l].fp.ok || (f32 && l == 0))
+      if (const int e = separate_plans(c, l)) return e;
+  return MGFEM_OK;
+}
+
 int build_coarse_map(mgfem_ctx* c, bool forward_only) {
   CoarsePlan& P = c->cplan;
   CoarseMap& M = P.map;
@@ -2244,13 +2332,18 @@ int build_coarse_map(mgfem_ctx* c, bool forward_only) {
   M.level = P.lc;
   M.ld = (M.n + 15) / 16 * 16;
   const size_t cnt = (size_t)M.ld * M.n;
-  for (int rev = 0; rev < (forward_only ? 1 : 2); ++rev) {
-    MGFEM_HIP_TRY(ctx_alloc_t(c, &M.f64[rev], cnt));  // zeroed: the padding columns stay 0
-    CoarseArgs<double> a = coarse_args<double>(c, rev != 0, M.reps);
-    a.unit = 1;
-    a.map_out = M.f64[rev];
-    a.map_ld = M.ld;
-    hipLaunchKernelGGL(k_coarse<double>, dim3(M.n), dim3(kCoarseThreads), P.lds64, c->s, a);
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &M.f64[0], cnt));  // zeroed: the padding columns stay 0
+  CoarseArgs<double> a = coarse_args<double>(c, false, M.reps);
+  a.unit = 1;
+  a.map_out = M.f64[0];
+  a.map_ld = M.ld;
+  hipLaunchKernelGGL(k_coarse<double>, dim3(M.n), dim3(kCoarseThreads), P.lds64, c->s, a);
+  MGFEM_HIP_TRY(hipGetLastError());
+  if (!forward_only) {
+    // the transposed cycles' map is the transpose
+    MGFEM_HIP_TRY(ctx_alloc_t(c, &M.f64[1], cnt));
+    hipLaunchKernelGGL(k_transpose, dim3((M.n + 31) / 32, (M.n + 31) / 32), dim3(256), 0, c->s,
+                       (const double*)M.f64[0], M.f64[1], M.n, M.ld);
     MGFEM_HIP_TRY(hipGetLastError());
   }
   if (c->p.precision == MGFEM_PREC_MIXED) {
@@ -2260,8 +2353,14 @@ int build_coarse_map(mgfem_ctx* c, bool forward_only) {
     MGFEM_HIP_TRY(hipGetLastError());
   }
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
-  if (!forward_only) return extend_coarse_map(c);
-  return MGFEM_OK;
+  if (forward_only) return MGFEM_OK;
+  // In float64 a level above some 2600 unknowns costs no more with its own
+  // fused steps (N = 128 of the flower, 3600 unknowns: 17 us and the map one
+  // level lower 4 us) than its map (19 us, 104 MB), which takes 7 ms of the
+  // set-up to build; the float32 map of the mixed cycles takes 12 us
+  // against 30 us.
+  const bool f32 = c->p.precision == MGFEM_PREC_MIXED;
+  return extend_coarse_map(c, f32 ? kMaxMapNodes : kMaxMapNodes64);
 }
 
 void smooth_level(mgfem_ctx* c, int l, bool reverse, bool fp32) {
@@ -2281,6 +2380,8 @@ void set_kernel_attributes() {
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_cut_multi<float>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_cut_multi<double>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_map_columns),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_coarse<double>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -162,6 +162,14 @@ int team_build(mgfem_ctx* b) {
   T->P = P;
   T->lc.resize(P);
   bool ok = P > 0 && b->p.nu2 >= 1;
+  T->fused = true;
+  for (int p = 0; p < P; ++p)
+    for (int l = 0; l < b->members[p]->cplan.lc; ++l)
+      T->fused = T->fused && fused_units(b->members[p], l) >= 0;
+  if (!T->fused)
+    for (int p = 0; p < P; ++p)
+      for (int l = 0; l < b->members[p]->cplan.lc; ++l)
+        if (const int e = separate_plans(b->members[p], l)) return e;
   for (int p = 0; p < P && ok; ++p) {
     mgfem_ctx* m = b->members[p];
     const int lc = m->cplan.lc;
@@ -169,13 +177,10 @@ int team_build(mgfem_ctx* b) {
     ok = lc >= 1 && team_units(m, kTeamMap, 0) > 0;
     for (int l = 0; l < lc && ok; ++l)
       for (int kind : {kTeamSweep, kTeamCut, kTeamRR})
-        if (team_units(m, kind, l) < 0) ok = false;
+        if (!fused_kind(*T, kind) && team_units(m, kind, l) < 0) ok = false;
     if (ok) T->depth = std::max(T->depth, lc);
   }
   if (!ok) return MGFEM_OK;  // the persistent kernel serves this batch
-  T->fused = true;
-  for (int p = 0; p < P; ++p)
-    for (int l = 0; l < T->lc[p]; ++l) T->fused = T->fused && fused_units(b->members[p], l) >= 0;
   for (int kind = 0; kind < 4; ++kind) {
     const bool fk = fused_kind(*T, kind);
     const size_t eb = fk ? fused_entry_bytes() : team_entry_bytes(kind);

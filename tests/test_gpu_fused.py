@@ -102,6 +102,32 @@ def test_fused_float_cycles(N, coarsest):
     assert float((u - us).abs().max()) <= 1e-8 * float(us.abs().max())
 
 
+@pytest.mark.parametrize("N", [128, 512])
+def test_adjoint_and_smoothing_of_a_mixed_handle(N):
+    """A mixed handle has its fused plans in float32; its adjoint and its
+    single smoothing steps run in float64 all the same: the float64 handle's
+    results (to the bound of the random draws), before and after a solve."""
+    mg = _gpu()
+    p = W.flower_mms(N)
+    rng = np.random.default_rng(1)
+    r = rng.standard_normal((N + 1) ** 2)
+    s64, sm = mg.Solver(p.psi, N), mg.Solver(p.psi, N, precision=mg.PREC_MIXED)
+    ref = s64.adjoint(r, tol=-1.0, max_cycles=3)
+    x0 = torch.tensor(r, device="cuda:0") * (s64.export(mg._lib.EXPORT_NODE_FLAGS) > 0)
+    b = torch.tensor(rng.standard_normal((N + 1) ** 2), device="cuda:0")
+    xr = s64.smooth(0, x0.clone(), b, steps=2)
+    for _ in range(2):
+        got = sm.adjoint(r, tol=-1.0, max_cycles=3)
+        for a, c in zip(got[:3], ref[:3]):
+            assert float((a - c).abs().max()) <= 1e-10 * float(c.abs().max())
+        xm = sm.smooth(0, x0.clone(), b, steps=2)
+        assert float((xm - xr).abs().max()) <= 1e-10 * float(xr.abs().max())
+        u, h = sm.solve(p.f, p.g, tol=1e-10)
+        assert sm.last_status == 0
+    uw, _ = s64.solve(p.f, p.g, tol=1e-10)
+    assert float((u - uw).abs().max()) <= 1e-4 * float(uw.abs().max())  # both stop at the residual tolerance
+
+
 def test_crowded_tiles_keep_the_separate_kernels():
     """A level set that cuts every cell: more cut vertices in a tile than its
     record holds, so the level takes the separate kernels and still matches
