@@ -678,6 +678,12 @@ void launch_dot_reduce(mgfem_ctx* c, const double* a, const double* b) {
                      c->red_seq_dev);
 }
 
+void launch_pair_reduce(mgfem_ctx* c, int nb) {
+  c->red_seq += 1.0;
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
+                     c->red_seq_dev);
+}
+
 }  // namespace mgfem
 
 namespace mgfem {

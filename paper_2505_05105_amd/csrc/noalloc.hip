@@ -31,45 +31,52 @@ std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 bool g_scratch_tried[kMaxDevices] = {};
 
-// a block takes 256 x 4 nodes; e is staged in LDS with a halo of one (zero off
+// a block takes 256 x 8 nodes; e is staged in LDS with a halo of one (zero off
 // the grid and at inactive nodes)
-constexpr int kMX = 256, kMY = 4, kMW = kMX + 2, kMH = kMY + 2, kMN = kMW * kMH;
+constexpr int kMX = 256, kMY = 8, kMW = kMX + 2, kMH = kMY + 2, kMN = kMW * kMH;
 
 // dJ/du = M e at every node of the block (0 at inactive nodes and off the box
-// of active nodes) and the block's share of e^T M e in part[block].  Rows:
-// the gathered M row at a cut-cell vertex (cut_rows, 18 per vertex in
+// of active nodes) and the block's share of e^T M e in part[stride block]
+// (stride 2: in part[2 block + 1], with 0 beside it, for the pair reduction).
+// Rows: the gathered M row at a cut-cell vertex (cut_rows, 18 per vertex in
 // cut-list order, M first), the stored planes at any other stored row, the
-// interior Q1 mass stencil h^2/36 [1 4 1; 4 16 4; 1 4 1] elsewhere.
+// interior Q1 mass stencil h^2/36 [1 4 1; 4 16 4; 1 4 1] elsewhere.  Bound by
+// its bytes: u, u_t and a flag per node of the box, dJ/du on the whole grid;
+// every load of a block is issued before the first is used (none under a
+// branch: a node off the grid loads a clamped one and drops it).
 __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict__ u, const double* __restrict__ ut,
                                                         const uint8_t* __restrict__ fl, const int* __restrict__ cutpos,
                                                         const double* __restrict__ cut_rows,
                                                         const double* __restrict__ M, double* __restrict__ y, int N,
                                                         double hh36, int i0, int j0, int i1, int j1,
-                                                        double* __restrict__ part) {
-  __shared__ double se[kMN];
+                                                        double* __restrict__ part, int stride) {
+  constexpr int NU = (kMN + 255) / 256;
+  __shared__ double se[NU * 256];
+  __shared__ uint8_t sf[NU * 256];
   __shared__ double wsum[4];
   const int s = N + 1;
   const int64_t n = (int64_t)s * s;
   const int bi = blockIdx.x * kMX, bj = blockIdx.y * kMY;
   const bool touches = bi <= i1 && bi + kMX - 1 >= i0 && bj <= j1 && bj + kMY - 1 >= j0;  // uniform
   if (touches) {
-    constexpr int NU = (kMN + 255) / 256;
-    double r[NU];
+    double ru[NU], rt[NU];
+    uint8_t rf[NU];
 #pragma unroll
-    for (int q0 = 0; q0 < NU; ++q0) {
-      const int q = threadIdx.x + q0 * 256;
-      const int gi = bi - 1 + q % kMW, gj = bj - 1 + q / kMW;
-      double v = 0.0;
-      if (q < kMN && gi >= 0 && gj >= 0 && gi <= N && gj <= N) {
-        const int64_t k = gi + (int64_t)gj * s;
-        if (fl[k] & kFlagActive) v = u[k] - ut[k];
-      }
-      r[q0] = v;
+    for (int w = 0; w < NU; ++w) {
+      const int q = min((int)threadIdx.x + w * 256, kMN - 1);
+      const int gi = min(max(bi - 1 + q % kMW, 0), N), gj = min(max(bj - 1 + q / kMW, 0), N);
+      const int64_t k = gi + (int64_t)gj * s;
+      rf[w] = fl[k];
+      ru[w] = u[k];
+      rt[w] = ut[k];
     }
 #pragma unroll
-    for (int q0 = 0; q0 < NU; ++q0) {
-      const int q = threadIdx.x + q0 * 256;
-      if (q < kMN) se[q] = r[q0];
+    for (int w = 0; w < NU; ++w) {
+      const int q = threadIdx.x + w * 256;
+      const int gi = bi - 1 + q % kMW, gj = bj - 1 + q / kMW;
+      const bool in = q < kMN && gi >= 0 && gj >= 0 && gi <= N && gj <= N && (rf[w] & kFlagActive);
+      se[q] = in ? ru[w] - rt[w] : 0.0;
+      sf[q] = in ? rf[w] : (uint8_t)0;
     }
     __syncthreads();
   }
@@ -81,15 +88,18 @@ __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict
     if (i > N || j > N) continue;
     const int64_t k = i + (int64_t)j * s;
     double me = 0.0;
-    if (touches && i >= i0 && i <= i1 && j >= j0 && j <= j1) {
-      const uint8_t fk = fl[k];
+    if (touches) {
+      const int q = threadIdx.x + 1 + (rep + 1) * kMW;
+      const uint8_t fk = sf[q];
       if (fk & kFlagActive) {
-        const int q = threadIdx.x + 1 + (rep + 1) * kMW;
-        if (fk & kFlagCut) {
-          const double* row = cut_rows + 18 * (int64_t)cutpos[k];
-          for (int p = 0; p < 9; ++p) me += row[p] * se[q + (p % 3 - 1) + (p / 3 - 1) * kMW];
-        } else if (fk & kFlagStored) {
-          for (int p = 0; p < 9; ++p) me += M[p * n + k] * se[q + (p % 3 - 1) + (p / 3 - 1) * kMW];
+        if (fk & kFlagStored) {
+          // zero coefficients are skipped, so that a value without a share in the row has none
+          const double* row = (fk & kFlagCut) ? cut_rows + 18 * (int64_t)cutpos[k] : M + k;
+          const int64_t st = (fk & kFlagCut) ? 1 : n;
+          for (int p = 0; p < 9; ++p) {
+            const double m = row[p * st];
+            if (m != 0.0) me += m * se[q + (p % 3 - 1) + (p / 3 - 1) * kMW];
+          }
         } else {
           const double corners = (se[q - kMW - 1] + se[q - kMW + 1]) + (se[q + kMW - 1] + se[q + kMW + 1]);
           const double edges = (se[q - kMW] + se[q + kMW]) + (se[q - 1] + se[q + 1]);
@@ -103,7 +113,11 @@ __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict
   for (int o = 32; o > 0; o >>= 1) sm += __shfl_xor(sm, o);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = sm;
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x + blockIdx.y * gridDim.x] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+  if (threadIdx.x == 0) {
+    const int b = blockIdx.x + blockIdx.y * gridDim.x;
+    if (stride == 2) part[2 * b] = 0.0;
+    part[stride * b + stride - 1] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+  }
 }
 
 // sum of the block partials in a fixed order, written to pinned host memory
@@ -123,6 +137,16 @@ __global__ __launch_bounds__(1024) void k_misfit_final(const double* __restrict_
 }
 
 }  // namespace
+
+int launch_misfit(mgfem_ctx* c, const double* u, const double* ut, double* dJdu, double* part, int stride) {
+  const Level& L = c->lv[0];
+  const int N = c->N;
+  const dim3 grid((unsigned)((N + kMX) / kMX), (unsigned)((N + kMY) / kMY));  // (N+1) nodes per side
+  hipLaunchKernelGGL(k_misfit_partial, grid, dim3(256), 0, c->s, u, ut, (const uint8_t*)L.flags,
+                     (const int*)L.cutpos, (const double*)c->cut_rows, (const double*)c->M, dJdu, N,
+                     c->h * c->h / 36.0, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], part, stride);
+  return (int)(grid.x * grid.y);
+}
 
 int scratch_init(int* device) {
   int dev = 0;
@@ -169,10 +193,9 @@ int mgfem_misfit_noalloc(mgfem_handle c, const double* u_dev, const double* ut_d
     c->last_error = "the static scratch array has no device address on device " + std::to_string(c->device);
     return MGFEM_ERR_HIP;
   }
-  const Level& L = c->lv[0];
   const int N = c->N;
-  const dim3 grid((unsigned)((N + kMX) / kMX), (unsigned)((N + kMY) / kMY));  // (N+1) nodes per side
-  const int64_t nb = (int64_t)grid.x * grid.y;
+  // the documented limit: one partial sum per 256 x 4 nodes
+  const int64_t nb = (int64_t)((N + 256) / 256) * ((N + 4) / 4);
   if (nb * (int64_t)sizeof(double) > (int64_t)kScratchBytes) {
     c->last_error = "N = " + std::to_string(N) + " needs " + std::to_string(nb * sizeof(double)) +
                     " bytes of partial sums; the static scratch array holds " + std::to_string(kScratchBytes) +
@@ -182,10 +205,8 @@ int mgfem_misfit_noalloc(mgfem_handle c, const double* u_dev, const double* ut_d
   double* part = static_cast<double*>(base);
   double* rec = c->red_host + 4 * kRedSlots;  // the handle's own pinned record (allocated at set-up)
   rec[0] = 0.0;
-  hipLaunchKernelGGL(k_misfit_partial, grid, dim3(256), 0, c->s, u_dev, ut_dev, (const uint8_t*)L.flags,
-                     (const int*)L.cutpos, (const double*)c->cut_rows, (const double*)c->M, dJdu_dev, N,
-                     c->h * c->h / 36.0, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], part);
-  hipLaunchKernelGGL(k_misfit_final, dim3(1), dim3(1024), 0, c->s, (const double*)part, (int)nb, rec);
+  const int blocks = launch_misfit(c, u_dev, ut_dev, dJdu_dev, part, 1);
+  hipLaunchKernelGGL(k_misfit_final, dim3(1), dim3(1024), 0, c->s, (const double*)part, blocks, rec);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(c->s);
   if (e != hipSuccess) {
