@@ -1232,6 +1232,7 @@ int build_fused(mgfem_ctx* c) {
   const int cl = c->cplan.map.level >= 0 ? c->cplan.map.level : c->cplan.lc;
   const int eta = c->p.eta;
   const bool f32 = c->p.precision == MGFEM_PREC_MIXED;
+  const int reach = f32 ? 0 : eta;  // float32 tiles hold no D, whatever eta is
   const char* env = std::getenv("MGFEM_NO_CUT_GROUPS");
   if ((env && env[0] && env[0] != '0') || (!f32 && 4 * eta > kMaxReachX) || c->p.nu2 < 1) return MGFEM_OK;
   struct Tmp {
@@ -1337,7 +1338,7 @@ int build_fused(mgfem_ctx* c) {
     Tmp& t = tmp[l];
     const int ntile = t.nt * t.nt;
     auto count = tile_nodes(c->lv[l].N) == 32 ? k_ftile_count<32> : k_ftile_count<16>;
-    hipLaunchKernelGGL(count, dim3(ntile), dim3(256), 0, s, view(l), coarse_view(l), t.nt, eta, t.keep, t.nst, t.nseg,
+    hipLaunchKernelGGL(count, dim3(ntile), dim3(256), 0, s, view(l), coarse_view(l), t.nt, reach, t.keep, t.nst, t.nseg,
                        flags + 2 * l + 1);
     hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.keep, ntile, t.slot);
     hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.nst, ntile, t.stoff);
@@ -1350,9 +1351,10 @@ int build_fused(mgfem_ctx* c) {
   MGFEM_HIP_TRY(hipGetLastError());
   MGFEM_HIP_TRY(hipMemcpyAsync(hf.data(), flags, hf.size() * sizeof(int), hipMemcpyDeviceToHost, s));
   MGFEM_HIP_TRY(hipStreamSynchronize(s));
-  // a level whose own plan, or whose coarser level's, does not fit keeps the separate kernels
+  // a level whose own plan, or whose coarser level's, does not fit keeps the
+  // separate kernels (a stored row's record holds its position in 18 bits)
   for (int l : ls)
-    c->lv[l].fp.ok = hf[2 * l] <= kMaxBlockCols && hf[2 * l + 1] == 0 && c->lv[l].fp.ncut < (1 << 18);
+    c->lv[l].fp.ok = hf[2 * l] <= kMaxBlockCols && hf[2 * l + 1] == 0 && c->lv[l].cut_off[4] < (1 << 18);
   for (size_t q = ls.size(); q-- > 0;)
     if (in[ls[q] + 1] && !c->lv[ls[q] + 1].fp.ok && tmp[ls[q] + 1].nblk > 0) c->lv[ls[q]].fp.ok = false;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_delta_build), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1397,7 +1399,7 @@ int build_fused(mgfem_ctx* c) {
     if (!F.ok) continue;
     auto fill = [&](auto kern, auto zero) {
       using T = decltype(zero);
-      hipLaunchKernelGGL(kern, dim3(t.nt * t.nt), dim3(256), 0, s, view(l), coarse_view(l), L.A, L.n, t.nt, eta,
+      hipLaunchKernelGGL(kern, dim3(t.nt * t.nt), dim3(256), 0, s, view(l), coarse_view(l), L.A, L.n, t.nt, reach,
                          t.keep, t.slot, t.stoff, t.nst, t.segoff, F.tiles, F.st_idx, static_cast<T*>(F.st_coef),
                          (const int*)L.cutpos, reinterpret_cast<double*>(F.D), reinterpret_cast<double*>(F.DT),
                          reinterpret_cast<uint16_t*>(F.Didx));

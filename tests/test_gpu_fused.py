@@ -102,6 +102,20 @@ def test_fused_float_cycles(N, coarsest):
     assert float((u - us).abs().max()) <= 1e-8 * float(us.abs().max())
 
 
+@pytest.mark.parametrize("N,coarsest,eta", [(128, 4, 6), (640, 5, 12)])
+def test_float_cycles_with_many_cut_sweeps(N, coarsest, eta):
+    """More cut sweeps than the float64 records reach: the float32 levels hold
+    none of those, and solve as with the list smoother (its own test's bound)."""
+    mg = _gpu()
+    p = W.flower_mms(N)
+    s = mg.Solver(p.psi, N, coarsest_n=coarsest, eta=eta, precision=mg.PREC_MIXED, inner_cycles=1)
+    sep = _separate(mg, p.psi, N, coarsest_n=coarsest, eta=eta, precision=mg.PREC_MIXED, inner_cycles=1)
+    u, h = s.solve(p.f, p.g, tol=1e-10)
+    us, hs = sep.solve(p.f, p.g, tol=1e-10)
+    assert s.last_status == 0 and len(h) == len(hs)
+    assert float((u - us).abs().max()) <= 1e-8 * float(us.abs().max())
+
+
 @pytest.mark.parametrize("N", [128, 512])
 def test_adjoint_and_smoothing_of_a_mixed_handle(N):
     """A mixed handle has its fused plans in float32; its adjoint and its
