@@ -471,19 +471,26 @@ int read_norm(mgfem_ctx* c, double& mx, double& l2, double* raw_sum = nullptr, d
 // x is the caller's buffer and receives the result
 // Enqueue one iteration of the solve loop: a cycle from the current iterate
 // and the reduction that gives the residual norm of the next one.
-//  float64 forward: the rest of the cycle (its first sweep ran in the previous
-//    iteration), then the first sweep of the next cycle with the fused norm of
+//  float64 forward: the rest of the cycle (its first steps ran in the previous
+//    iteration), then the first steps of the next cycle with the norm of
 //    its incoming iterate (speculative: discarded when the loop stops);
 //  mixed: inner_cycles float cycles on the float residual of the previous
 //    step (the first from zero), then one fused pass u += e, r = F - A u
 //    (float64), its float copy, the next zero start iterate and the norm;
 //  adjoint: a transposed cycle, then the residual norm.
 struct IterKind {
-  bool mixed, reverse, first_done;
-  int inner;  // mixed: float32 cycles of this step
+  bool mixed, reverse;
+  int steps_done;  // float64 forward: level-0 steps of this cycle that the last iteration ran
+  int inner;       // mixed: float32 cycles of this step
 };
-void enqueue_iteration(mgfem_ctx* c, const IterKind& k) {
+// returns the steps of the next cycle that ran
+int enqueue_iteration(mgfem_ctx* c, const IterKind& k) {
   Level& L0 = c->lv[0];
+  L0.keep = -1;  // the last iteration's norm has been read
+  for (size_t l = 1; l < c->lv.size(); ++l) {
+    c->lv[l].cur = 0;
+    c->lv[l].pend = c->lv[l].zero = false;
+  }
   if (k.mixed) {
     // the inner right-hand side b32 and the zero start iterate X32[cur] were
     // written by the previous outer step
@@ -502,43 +509,44 @@ void enqueue_iteration(mgfem_ctx* c, const IterKind& k) {
     launch_residual_norm(c, L0.b, L0.X[L0.cur], nullptr);
   } else {
     CycleOpts o;
-    o.first_sweep_done = k.first_done;
+    o.steps_done = k.steps_done;
     run_cycle(c, o);
-    first_sweep_with_norm(c);
+    return first_steps_with_norm(c);
   }
+  return 0;
 }
 
-// host-side state that an iteration reads and advances: the ping-pong parities
-// of every level, whether its iterate has cut sweeps pending or is zero, and of the float64 level-0 iterate of the mixed solve
+// host-side state that an iteration reads and advances: level 0's buffers,
+// whether its iterate has cut sweeps pending or is zero, and the parity of the
+// float64 level-0 iterate of the mixed solve.  A cycle starts the coarser
+// levels from zero, so their state is the same at the start of every
+// iteration (fewer states, fewer captures).
 std::vector<int> loop_state(const mgfem_ctx* c) {
-  std::vector<int> st;
-  for (const Level& L : c->lv) st.push_back(L.cur | L.rp << 1 | (int)L.pend << 2 | (int)L.zero << 3);
-  st.push_back(c->u_cur);
-  return st;
+  const Level& L = c->lv[0];
+  return {L.cur, L.keep, L.pend, L.zero, c->u_cur};
 }
 void set_loop_state(mgfem_ctx* c, const std::vector<int>& st) {
-  for (size_t l = 0; l < c->lv.size(); ++l) {
-    Level& L = c->lv[l];
-    L.cur = st[l] & 1;
-    L.rp = st[l] >> 1 & 1;
-    L.pend = (st[l] >> 2 & 1) != 0;
-    L.zero = (st[l] >> 3 & 1) != 0;
-  }
-  c->u_cur = st[c->lv.size()];
+  Level& L = c->lv[0];
+  L.cur = st[0];
+  L.keep = st[1];
+  L.pend = st[2] != 0;
+  L.zero = st[3] != 0;
+  c->u_cur = st[4];
 }
 
 std::vector<int> graph_key(mgfem_ctx* c, const IterKind& k) {
-  std::vector<int> key{k.mixed, k.reverse, k.first_done, c->prof.on ? 1 : 0, k.inner};
+  std::vector<int> key{k.mixed, k.reverse, k.steps_done, c->prof.on ? 1 : 0, k.inner};
   for (int v : loop_state(c)) key.push_back(v);
   return key;
 }
 
 // Run one iteration: replay its graph (captured on first use) or launch it
-// eagerly.  Returns the graph used, or null.
-int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used) {
+// eagerly.  Returns the graph used, or null, and the steps of the next cycle
+// that ran.
+int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used, int* steps) {
   *used = nullptr;
   if (!c->use_graphs || c->graphs_failed) {
-    enqueue_iteration(c, k);
+    *steps = enqueue_iteration(c, k);
     MGFEM_HIP_TRY(hipGetLastError());
     return MGFEM_OK;
   }
@@ -564,7 +572,7 @@ int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used) {
     c->capturing = &g;
     seg_open(c);
     if (g.err == hipSuccess) {
-      enqueue_iteration(c, k);
+      g.steps = enqueue_iteration(c, k);
       seg_close(c, -1);
     }
     c->capturing = nullptr;
@@ -587,7 +595,7 @@ int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used) {
       destroy_graph(g);
       c->graphs_failed = true;
       std::fprintf(stderr, "mgfem: %s; iterations run without graphs\n", c->last_error.c_str());
-      enqueue_iteration(c, k);
+      *steps = enqueue_iteration(c, k);
       MGFEM_HIP_TRY(hipGetLastError());
       return MGFEM_OK;
     }
@@ -606,6 +614,7 @@ int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used) {
   }
   c->red_seq += g.nred;
   set_loop_state(c, g.cur_after);
+  *steps = g.steps;
   *used = &g;
   return MGFEM_OK;
 }
@@ -629,6 +638,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   L0.X[0] = c->x0;
   L0.b = const_cast<double*>(b);
   L0.cur = 0;
+  L0.keep = -1;
   c->u_cur = 0;
   for (Level& L : c->lv) L.pend = L.zero = false;
   launch_box_copy(c, c->x0, warm ? x : nullptr);
@@ -660,7 +670,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   int status = MGFEM_OK;
   if (!std::isfinite(r0)) status = MGFEM_ERR_DIVERGED;
   const bool fused = !mixed && !reverse;  // norm of u_m from the first sweep of cycle m + 1
-  bool first_done = false;
+  int steps_done = 0;
   // The mixed loop queues its next iteration before reading the norm it
   // waits for (when that iteration will most likely be needed): the outer
   // update writes the other float64 buffer, so the iterate whose norm is
@@ -715,14 +725,13 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   auto launch = [&](Pending& out) -> int {
     const GraphEntry* g = nullptr;
     const int inner = inner_for((int)step_inner.size() + 1);
-    const int e = run_iteration(c, IterKind{mixed, reverse, first_done, inner}, &g);
+    const int e = run_iteration(c, IterKind{mixed, reverse, steps_done, inner}, &g, &steps_done);
     if (e) return e;
     step_inner.push_back(inner);
-    first_done = fused;
     out.seq = c->red_seq;
     out.g = g;
-    // fused: the closing sweep read the next iterate and wrote the other buffer
-    out.result = mixed ? L0.X[c->u_cur] : fused ? L0.X[1 - L0.cur] : L0.X[L0.cur];
+    // fused: the closing steps read the next iterate and wrote the other buffers
+    out.result = L0.X[mixed ? c->u_cur : !fused ? L0.cur : L0.keep >= 0 ? L0.keep : 1 - L0.cur];
     out.patch = fused && fused_level(c, 0, false) && L0.fp.ncut > 0;
     return MGFEM_OK;
   };
@@ -781,6 +790,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   prof_collect(c);
   L0.b = nullptr;
   L0.cur = 0;
+  L0.keep = -1;
   c->u_cur = 0;
   if (ncyc) *ncyc = m;
   if (status != MGFEM_OK) {
@@ -1040,6 +1050,7 @@ int mgfem_smooth(mgfem_handle c, int32_t level, double* x_dev, const double* b_d
   L.X[0] = x_dev;
   L.b = const_cast<double*>(b_dev);
   L.cur = 0;
+  L.keep = -1;
   gather_snap(c, level, false);
   for (int s = 0; s < steps; ++s) smooth_level(c, level, reverse != 0, false);
   if (L.cur == 1) launch_copy(c, x_dev, L.X[1], L.n);

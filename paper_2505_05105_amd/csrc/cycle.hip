@@ -6,6 +6,7 @@
 #include <cmath>
 
 #include "mgfem_internal.h"
+#include "reduce.h"
 
 namespace mgfem {
 namespace {
@@ -169,57 +170,9 @@ __global__ void k_dot_partial(const double* __restrict__ a, const double* __rest
   block_pair(0.0, sm, part);
 }
 
-__global__ __launch_bounds__(1024) void k_reduce_final(const double* __restrict__ part, int nb,
-                                                      double* __restrict__ out, double* host_out, double* seq) {
-  __shared__ double smax[16], ssum[16];
-  // pairs in chunks of 8 per thread, the loads of a chunk issued together (a
-  // lane beyond nb reads pair 0 and drops it: loads under a branch would
-  // wait for one another)
-  constexpr int U = 8;
-  double mx = 0.0, sm = 0.0;
-  for (int base = 0; base < nb; base += U * 1024) {
-    double lm[U], ls[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = base + threadIdx.x + u * 1024;
-      const int tt = t < nb ? t : 0;
-      lm[u] = part[2 * tt];
-      ls[u] = part[2 * tt + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in = base + (int)threadIdx.x + u * 1024 < nb;
-      mx = nanmax(mx, in ? lm[u] : 0.0);
-      sm += in ? ls[u] : 0.0;
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    mx = nanmax(mx, __shfl_xor(mx, o));
-    sm += __shfl_xor(sm, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    smax[threadIdx.x >> 6] = mx;
-    ssum[threadIdx.x >> 6] = sm;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-      mx = nanmax(mx, smax[w]);
-      sm += ssum[w];
-    }
-    out[0] = mx;
-    out[1] = sm;
-    // straight to pinned host memory; the sequence number (counted on the
-    // device, so a replayed graph still numbers its reductions) goes last
-    const double q = seq[0] + 1.0;
-    seq[0] = q;
-    double* rec = host_out + 4 * (int)((long long)q % kRedSlots);
-    rec[0] = mx;
-    rec[1] = sm;
-    __threadfence_system();
-    rec[2] = q;
-    __threadfence_system();
-  }
+__global__ __launch_bounds__(1024) void k_reduce_final(Reduce r) {
+  __shared__ double sh[32];
+  reduce_block<1024, 8>(r, sh);
 }
 
 // F = M f + G g (+ GN g_N on mixed boundaries; section 2, the discrete load)
@@ -536,9 +489,7 @@ void launch_rhs(mgfem_ctx* c, const double* f, const double* g, const double* gN
   const int nb = (int)(grid.x * grid.y);
   hipLaunchKernelGGL(k_rhs, grid, dim3(256), 0, c->s, c->M, c->G, (const double*)c->GN, L.flags, f, g, gN, F, c->N,
                      c->h * c->h / 36.0, L.bbox[0], L.bbox[2], ni, nj, c->red_partial);
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
-                     c->red_seq_dev);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->red_partial, nb));
 }
 
 void launch_outer(mgfem_ctx* c, const double* u, const float* e, double* u_out, float* r32, float* z32) {
@@ -556,9 +507,7 @@ void launch_outer(mgfem_ctx* c, const double* u, const float* e, double* u_out, 
     if (shape == kShapeFinest) e ? go(k_outer_tiles<64, 32, true>) : go(k_outer_tiles<64, 32, false>);
     else if (shape == kShapeLarge) e ? go(k_outer_tiles<64, 16, true>) : go(k_outer_tiles<64, 16, false>);
     else e ? go(k_outer_tiles<16, 16, true>) : go(k_outer_tiles<16, 16, false>);
-    c->red_seq += 1.0;
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, (const double*)c->sweep_part, L.ntiles,
-                       c->red_out, c->red_host, c->red_seq_dev);
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->sweep_part, L.ntiles));
     return;
   }
   const int ni = L.bbox[1] - L.bbox[0] + 1, nj = L.bbox[3] - L.bbox[2] + 1;
@@ -566,9 +515,7 @@ void launch_outer(mgfem_ctx* c, const double* u, const float* e, double* u_out, 
   const int nb = (int)(grid.x * grid.y);
   hipLaunchKernelGGL(k_outer, grid, dim3(256), 0, c->s, v, (const double*)L.b, u, e, u_out, r32, z32,
                      L.bbox[0], L.bbox[2], ni, nj, c->red_partial);
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
-                     c->red_seq_dev);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->red_partial, nb));
 }
 
 namespace {
@@ -664,24 +611,18 @@ void launch_residual_norm(mgfem_ctx* c, const double* F, const double* u, double
   const int nb = (int)(grid.x * grid.y);
   hipLaunchKernelGGL(k_resnorm_partial, grid, dim3(256), 0, c->s, v, F, r_out, L.bbox[0],
                      L.bbox[2], ni, nj, c->red_partial);
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
-                     c->red_seq_dev);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->red_partial, nb));
 }
 
 void launch_dot_reduce(mgfem_ctx* c, const double* a, const double* b) {
   const int64_t n = c->lv[0].n;
   const int nb = (int)std::min<int64_t>(kDotBlocks, (n + 255) / 256);  // grid-stride beyond
   hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(256), 0, c->s, a, b, n, c->red_partial);
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
-                     c->red_seq_dev);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->red_partial, nb));
 }
 
 void launch_pair_reduce(mgfem_ctx* c, int nb) {
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, c->red_partial, nb, c->red_out, c->red_host,
-                     c->red_seq_dev);
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(1024), 0, c->s, next_reduce(c, c->red_partial, nb));
 }
 
 }  // namespace mgfem

@@ -32,6 +32,7 @@
 #include <cstring>
 
 #include "mgfem_internal.h"
+#include "reduce.h"
 
 namespace mgfem {
 namespace {
@@ -87,11 +88,11 @@ struct FArgs {
   const int* cutposc;
   T* snapc;
   double* part;        // per-tile (max |r|, sum r^2) of the incoming iterate, or null
+  Reduce red;          // sweeps: pairs of an earlier launch that one more workgroup reduces
 };
 
 __device__ inline double fma_t(double a, double b, double c) { return fma(a, b, c); }
 __device__ inline float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline double nanmax3(double a, double b) { return (b > a || b != b) ? b : a; }
 
 // lanes of one wave see each other's LDS stores
 __device__ inline void wave_sync() {
@@ -395,7 +396,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
         __shared__ double smx[NW], ssm[NW];
         double mx = 0.0, sm = 0.0;
         auto add = [&](double r) {
-          mx = nanmax3(mx, fabs(r));
+          mx = nanmax2(mx, fabs(r));
           sm += r * r;
         };
         // the regular rows of the core are the phases' nodes: every core node is one of them
@@ -412,7 +413,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
           if (in_core(q2)) add((double)(b2 - (c2[4] * su[q2] + row_off<T, kRW>(c2, su, q2))));
         });
         for (int o = 32; o > 0; o >>= 1) {
-          mx = nanmax3(mx, __shfl_xor(mx, o));
+          mx = nanmax2(mx, __shfl_xor(mx, o));
           sm += __shfl_xor(sm, o);
         }
         if (lane == 0) {
@@ -422,7 +423,7 @@ __device__ void fused_tile(const FArgs<T>& a, const int t) {
         __syncthreads();
         if (tid == 0) {
           for (int w = 1; w < NW; ++w) {
-            mx = nanmax3(mx, smx[w]);
+            mx = nanmax2(mx, smx[w]);
             sm += ssm[w];
           }
           a.part[2 * t] = mx;
@@ -474,6 +475,13 @@ __device__ inline int xcd_slot(int per) { return (blockIdx.x & 7) * per + (block
 
 template <class T, int KIND, int FT, int BS>
 __global__ __launch_bounds__(BS) void k_fused(FArgs<T> a) {
+  if constexpr (KIND == kSweepK && sizeof(T) == 8) {
+    if (a.red.part && blockIdx.x == gridDim.x - 1) {
+      __shared__ double sh[2 * BS / 64];
+      reduce_block<BS, 4>(a.red, sh);
+      return;
+    }
+  }
   const int t = xcd_slot((a.ntiles + 7) >> 3);
   if (t >= a.ntiles) return;  // uniform, before any barrier
   fused_tile<T, KIND, FT, BS>(a, t);
@@ -1054,34 +1062,35 @@ FArgs<T> fargs(mgfem_ctx* c, int l) {
 
 template <class T, int KIND>
 void launch_tiles(const FArgs<T>& a, hipStream_t st) {
-  const dim3 grid(8u * (unsigned)((a.ntiles + 7) / 8));
+  const dim3 grid(8u * (unsigned)((a.ntiles + 7) / 8) + (a.red.part ? 1 : 0));
   if (tile_nodes(a.N) == 32) hipLaunchKernelGGL((k_fused<T, KIND, 32, 512>), grid, dim3(512), 0, st, a);
   else if (a.ntiles > kWideTiles) hipLaunchKernelGGL((k_fused<T, KIND, 16, 256>), grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL((k_fused<T, KIND, 16, 512>), grid, dim3(512), 0, st, a);
 }
 
 template <class T>
-void launch_sweep(mgfem_ctx* c, int l, bool norm, bool up) {
+void launch_sweep(mgfem_ctx* c, int l, bool norm, bool up, const Reduce* red) {
   Level& L = c->lv[l];
   FusedPlan& F = L.fp;
   FArgs<T> a = fargs<T>(c, l);
   a.xin = L.zero ? nullptr : Of<T>::X(L, L.cur);
-  a.xout = Of<T>::X(L, 1 - L.cur);
+  const int to = L.next();
+  a.xout = Of<T>::X(L, to);
+  if (red) a.red = *red;
   if (up) a.xc = Of<T>::X(c->lv[l + 1], c->lv[l + 1].cur);
   if constexpr (sizeof(T) == 4) {
     a.cut_out = L.snap32;
   } else {
-    if (F.ncut > 0) a.cut_out = F.r[1 - L.rp];
+    if (F.ncut > 0) a.cut_out = F.r[to];
     if (up) {
       const Level& C = c->lv[l + 1];
       if (L.pend) a.xs_in = F.xs;
-      if (C.pend) a.rc = C.fp.r[C.rp];
+      if (C.pend) a.rc = C.fp.r[C.cur];
     } else if (L.pend) {
-      a.r = F.r[L.rp];
+      a.r = F.r[L.cur];
       if (norm) a.xs_out = F.xs;
     }
     if (norm) a.part = c->sweep_part;
-    L.rp = 1 - L.rp;
     L.pend = F.ncut > 0;
   }
   auto go = [a, up](hipStream_t st) {
@@ -1096,7 +1105,7 @@ void launch_sweep(mgfem_ctx* c, int l, bool norm, bool up) {
   } else {
     go(c->s);
   }
-  L.cur = 1 - L.cur;
+  L.cur = to;
   L.zero = false;
 }
 
@@ -1113,13 +1122,12 @@ void launch_reverse_sweep(mgfem_ctx* c, int l) {
   a.reverse = 1;
   if (F.ncut > 0) {
     a.D = F.DT;
-    a.r = F.r[L.rp];
+    a.r = F.r[L.cur];
     a.rows = L.pend ? nullptr : F.rows;
-    a.cut_out = F.r[1 - L.rp];
+    a.cut_out = F.r[1 - L.cur];
   }
   launch_tiles<double, kSweepK>(a, c->s);
   L.cur = 1 - L.cur;
-  L.rp = 1 - L.rp;
   L.pend = F.ncut > 0;
   L.zero = false;
 }
@@ -1130,10 +1138,9 @@ void launch_prolong(mgfem_ctx* c, int l) {
   a.xin = L.X[L.cur];
   a.xout = L.X[1 - L.cur];
   a.xc = c->lv[l + 1].X[c->lv[l + 1].cur];
-  if (F.ncut > 0) a.cut_out = F.r[1 - L.rp];
+  if (F.ncut > 0) a.cut_out = F.r[1 - L.cur];
   launch_tiles<double, kProlongK>(a, c->s);
   L.cur = 1 - L.cur;
-  L.rp = 1 - L.rp;
   L.pend = F.ncut > 0;
 }
 
@@ -1144,7 +1151,7 @@ void launch_rr(mgfem_ctx* c, int l, bool clear_coarse, bool reverse) {
   FArgs<T> a = fargs<T>(c, l);
   a.xin = L.zero ? nullptr : Of<T>::X(L, L.cur);
   if (L.pend && !reverse) {
-    a.r = L.fp.r[L.rp];
+    a.r = L.fp.r[L.cur];
     a.xs_out = L.fp.xs;
   }
   if (clear_coarse) {
@@ -1157,9 +1164,9 @@ void launch_rr(mgfem_ctx* c, int l, bool clear_coarse, bool reverse) {
 
 }  // namespace
 
-void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up) {
-  if (fp32) launch_sweep<float>(c, l, norm, up);
-  else launch_sweep<double>(c, l, norm, up);
+void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up, const Reduce* red) {
+  if (fp32) launch_sweep<float>(c, l, norm, up, nullptr);
+  else launch_sweep<double>(c, l, norm, up, red);
 }
 void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse, bool reverse) {
   if (fp32) launch_rr<float>(c, l, clear_coarse, false);
@@ -1173,7 +1180,7 @@ void fused_apply(mgfem_ctx* c, int l) {
   if (!L.pend) return;
   FArgs<double> a = fargs<double>(c, l);
   a.xout = L.X[L.cur];
-  a.r = F.r[L.rp];
+  a.r = F.r[L.cur];
   const dim3 grid(8u * (unsigned)((F.ntiles + 7) / 8));
   if (tile_nodes(L.N) == 32) hipLaunchKernelGGL((k_fused_apply<32, 512>), grid, dim3(512), 0, c->s, a);
   else hipLaunchKernelGGL((k_fused_apply<16, 256>), grid, dim3(256), 0, c->s, a);
@@ -1365,16 +1372,18 @@ int build_fused(mgfem_ctx* c) {
     FusedPlan& F = L.fp;
     if (!F.ok) continue;
     F.ntiles = tot[8 * l + 4];
+    // the second step carries the reduction of the first one's norm
+    if (l == 0 && !f32 && c->p.nu1 >= 2 && !L.X[2]) MGFEM_HIP_TRY(ctx_alloc_t(c, &L.X[2], L.n));
     const size_t nst = (size_t)tot[8 * l + 5], nseg = (size_t)tot[8 * l + 6], v = f32 ? 4 : 8;
     char* buf = nullptr;
     MGFEM_HIP_TRY(ctx_alloc(c, reinterpret_cast<void**>(&buf),
-                            (size_t)F.ncut * (sizeof(int) + 3 * v) + (size_t)F.ntiles * sizeof(FTile) +
+                            (size_t)F.ncut * (sizeof(int) + 4 * v) + (size_t)F.ntiles * sizeof(FTile) +
                                 nst * (sizeof(int) + 10 * v) + nseg * 288 + 4096));
     F.tiles = reinterpret_cast<FTile*>(carve(buf, (size_t)F.ntiles * sizeof(FTile)));
     F.st_coef = carve(buf, nst * 10 * v);
     F.st_idx = reinterpret_cast<int*>(carve(buf, nst * sizeof(int)));
     F.rows = reinterpret_cast<int*>(carve(buf, (size_t)F.ncut * sizeof(int)));
-    for (double** q : {&F.r[0], &F.r[1], &F.xs}) *q = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
+    for (double** q : {&F.r[0], &F.r[1], &F.r[2], &F.xs}) *q = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
     if (!f32) {
       F.D = reinterpret_cast<double2*>(carve(buf, nseg * 128));
       F.DT = reinterpret_cast<double2*>(carve(buf, nseg * 128));

@@ -113,7 +113,7 @@ struct FusedPlan {
   double2* DT = nullptr;     // the transposed steps' values (fine rows only)
   uint4* Didx = nullptr;     // their local columns
   int* rows = nullptr;       // per position: i | j << 16
-  double* r[2] = {nullptr, nullptr};  // ping-pong residual at the cut vertices, by position
+  double* r[3] = {nullptr, nullptr, nullptr};  // residual at the cut vertices, by position, per iterate buffer
   double* xs = nullptr;               // their values after the pending sweeps
 };
 
@@ -125,11 +125,12 @@ struct Level {
   float* A32 = nullptr;
   uint8_t* flags = nullptr;
   uint8_t* cellcut = nullptr;  // N*N, 1 on cut cells of this level
-  double* X[2] = {nullptr, nullptr};  // ping-pong iterates (level 0: X[0] is the caller's)
+  double* X[3] = {nullptr, nullptr, nullptr};  // iterates, in turn (the third on a fused level 0, see keep)
   float* X32[2] = {nullptr, nullptr};
   double* b = nullptr;
   float* b32 = nullptr;
   int cur = 0;                // which X holds the current iterate (host-side state)
+  int keep = -1;              // level 0 with three buffers: the iterate whose norm is being reduced
   int* cut_list = nullptr;    // concatenated colour lists of the cut vertices
   int cut_off[5] = {0, 0, 0, 0, 0};
   int* cutpos = nullptr;      // per node: position in cut_list, or -1
@@ -162,11 +163,11 @@ struct Level {
   int tp_max = 0, tc_max = 0;
   FusedPlan fp;
   bool grouped = false, tiled = false;  // the separate kernels' plans exist
-  int rp = 0;         // which fp.r belongs to the current iterate (host-side state, as the next two)
-  bool pend = false;  // forward: the current iterate's last cut sweeps are not applied yet, x + D fp.r[rp];
-                      // transposed: fp.r[rp] is its residual at the cut vertices
+  bool pend = false;  // forward: the current iterate's last cut sweeps are not applied yet, x + D fp.r[cur];
+                      // transposed: fp.r[cur] is its residual at the cut vertices (host-side state)
   bool zero = false;  // the current iterate is zero and its buffer is not cleared
   bool empty() const { return bbox[0] > bbox[1]; }
+  int next() const { return keep >= 0 ? 3 - cur - keep : cur == 0 ? 1 : 0; }  // the buffer a sweep writes
 };
 
 // HIP-event timing of one kernel class inside a solve (see mgfem_profile)
@@ -203,6 +204,7 @@ struct GraphEntry {
   std::vector<GraphSeg> segs;
   std::vector<int> cur_after;  // loop state (ping-pong parities) after one replay
   int nred = 0;                // reductions per replay
+  int steps = 0;               // level-0 steps of the next cycle it ran
   std::vector<ProfSlot> slots; // timed launches
   hipError_t err = hipSuccess; // first capture error
 };
@@ -460,11 +462,13 @@ void launch_export(mgfem_ctx* c, double* dst, const double* src);
 struct CycleOpts {
   bool reverse = false;           // transposed cycle (adjoint)
   bool fp32 = false;              // float inner cycle
-  bool first_sweep_done = false;  // the first level-0 sweep already ran (first_sweep_with_norm)
+  int steps_done = 0;       // level-0 pre-smoothing steps that ran already (first_steps_with_norm)
 };
-// first pre-smoothing sweep of level 0 (float64, forward) that also reduces the
-// residual norm of its incoming iterate into red_out
-void first_sweep_with_norm(mgfem_ctx* c);
+// the first pre-smoothing steps of level 0 (float64, forward), whose first sweep
+// also takes the residual norm of its incoming iterate; returns their number
+int first_steps_with_norm(mgfem_ctx* c);
+struct Reduce;
+Reduce next_reduce(mgfem_ctx* c, const double* part, int nb);  // the next reduction in sequence (reduce.h)
 // one cycle on level 0 from its current iterate X[cur] and right-hand side b
 void run_cycle(mgfem_ctx* c, const CycleOpts& o);
 void smooth_level(mgfem_ctx* c, int l, bool reverse, bool fp32);
@@ -498,7 +502,8 @@ int build_fused(mgfem_ctx* c);
 inline bool fused_level(const mgfem_ctx* c, int l, bool f32) {
   return c->lv[l].fp.ok && f32 == (c->p.precision == MGFEM_PREC_MIXED);
 }
-void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up);
+// (red: the reduction that one more workgroup of the launch carries)
+void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up, const Reduce* red = nullptr);
 void fused_restrict(mgfem_ctx* c, int l, bool fp32, bool clear_coarse, bool reverse);
 void fused_reverse_sweep(mgfem_ctx* c, int l);  // transposed step: cut sweeps, then the sweep, colours 3 .. 0
 void fused_prolong(mgfem_ctx* c, int l);        // x + P x_c and the residual the next transposed step starts from

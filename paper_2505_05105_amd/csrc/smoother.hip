@@ -40,6 +40,7 @@
 #include <cstring>
 
 #include "mgfem_internal.h"
+#include "reduce.h"
 
 namespace mgfem {
 namespace {
@@ -84,8 +85,6 @@ struct SweepArgs {
   const int* tc_pos;
   const T* zero;  // at least 16 zero bytes: the source of staged groups off the grid
 };
-
-__device__ inline double nanmax2(double a, double b) { return (b > a || b != b) ? b : a; }
 
 // product of the stored stencil row at node k with LDS values around q
 template <class T, int RW>
@@ -140,57 +139,9 @@ __device__ inline T gs_value(const T* __restrict__ A, int64_t n, int64_t k, bool
 //           separate prolongation pass).
 //  norm:    before the first phase, the residual of the incoming iterate on
 //           the core is reduced into per-tile partials (max |r|, sum r^2).
-// final reduction of (max, sum) pairs in a fixed order: each of the 1024
-// threads takes the pairs in chunks of four, the loads of a chunk issued
-// together (a lane beyond nb reads pair 0 and drops it: loads under a branch
-// would wait for one another), then a wave reduction and the 16 waves in
-// order
-__global__ __launch_bounds__(1024) void k_reduce_pairs(const double* __restrict__ part, int nb, double* __restrict__ out, double* host_out,
-                               double* seq) {
-  __shared__ double smx[16], ssm[16];
-  constexpr int U = 4;
-  double mx = 0.0, sm = 0.0;
-  for (int base = 0; base < nb; base += U * 1024) {
-    double lm[U], ls[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = base + threadIdx.x + u * 1024;
-      const int qq = q < nb ? q : 0;
-      lm[u] = part[2 * qq];
-      ls[u] = part[2 * qq + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in = base + (int)threadIdx.x + u * 1024 < nb;
-      mx = nanmax2(mx, in ? lm[u] : 0.0);
-      sm += in ? ls[u] : 0.0;
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    mx = nanmax2(mx, __shfl_xor(mx, o));
-    sm += __shfl_xor(sm, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    smx[threadIdx.x >> 6] = mx;
-    ssm[threadIdx.x >> 6] = sm;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) {
-      mx = nanmax2(mx, smx[w]);
-      sm += ssm[w];
-    }
-    out[0] = mx;
-    out[1] = sm;
-    const double q = seq[0] + 1.0;  // counted on the device (graph replays)
-    seq[0] = q;
-    double* rec = host_out + 4 * (int)((long long)q % kRedSlots);
-    rec[0] = mx;  // straight to pinned host memory; the sequence number goes last
-    rec[1] = sm;
-    __threadfence_system();
-    rec[2] = q;
-    __threadfence_system();
-  }
+__global__ __launch_bounds__(1024) void k_reduce_pairs(Reduce r) {
+  __shared__ double sh[32];
+  reduce_block<1024, 4>(r, sh);
 }
 
 // 16 bytes per lane from global memory straight into LDS at dst + 16 * lane
@@ -475,6 +426,7 @@ struct CutArgs {
   const T* b;
   const T* snap;
   int eta, reverse;
+  Reduce red;  // pairs of an earlier launch that one more workgroup reduces
 };
 
 
@@ -644,6 +596,10 @@ __device__ void cut_group(const CutArgs<T>& a, const int g, unsigned char* smem)
 template <class T>
 __global__ __launch_bounds__(kCutThreads) void k_cut(CutArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
+  if (a.red.part && blockIdx.x == gridDim.x - 1) {
+    reduce_block<kCutThreads, 16>(a.red, reinterpret_cast<double*>(smem));
+    return;
+  }
   cut_group<T>(a, blockIdx.x, smem);
 }
 
@@ -1413,7 +1369,7 @@ SweepArgs<T> sweep_args(mgfem_ctx* c, int l, bool reverse, bool norm, bool prolo
     a.sc = C.stride;
   }
   a.xin = Xp<T>(L, L.cur);
-  a.xout = Xp<T>(L, 1 - L.cur);
+  a.xout = Xp<T>(L, L.next());
   a.b = Bp<T>(L);
   a.A = Ap<T>(L);
   a.fl = L.flags;
@@ -1467,12 +1423,7 @@ void launch_sweep(mgfem_ctx* c, int l, bool reverse, bool norm, bool prolong_fro
   } else {
     hipLaunchKernelGGL((k_sweep<T, TW, TH, BS>), dim3(8 * a.per), dim3(BS), 0, c->s, a);
   }
-  if (norm) {
-    c->red_seq += 1.0;
-    hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, (const double*)c->sweep_part, a.ntiles,
-                       c->red_out, c->red_host, c->red_seq_dev);
-  }
-  L.cur = 1 - L.cur;
+  L.cur = L.next();
 }
 
 template <class T>
@@ -1503,18 +1454,22 @@ CutArgs<T> cut_args(mgfem_ctx* c, int l, bool reverse) {
   a.snap = Sp<T>(L);
   a.eta = c->p.eta;
   a.reverse = reverse ? 1 : 0;
+  a.red = Reduce{};
   return a;
 }
 
 template <class T>
-void cut_sweeps(mgfem_ctx* c, int l, bool reverse) {
+void cut_sweeps(mgfem_ctx* c, int l, bool reverse, const Reduce* red = nullptr) {
   Level& L = c->lv[l];
   const int eta = c->p.eta;
+  const bool groups = eta > 0 && L.cut_off[4] > 0 && L.cp.ok;
+  if (red && !groups) hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, *red);
   if (eta == 0 || L.cut_off[4] == 0) return;
-  if (L.cp.ok) {
-    const CutArgs<T> a = cut_args<T>(c, l, reverse);
+  if (groups) {
+    CutArgs<T> a = cut_args<T>(c, l, reverse);
+    if (red) a.red = *red;
     const size_t lds = std::is_same<T, double>::value ? L.cp.lds64 : L.cp.lds32;
-    hipLaunchKernelGGL(k_cut<T>, dim3(L.cp.ngroups), dim3(kCutThreads), lds, c->s, a);
+    hipLaunchKernelGGL(k_cut<T>, dim3(L.cp.ngroups + (red ? 1 : 0)), dim3(kCutThreads), lds, c->s, a);
     return;
   }
   for (int e = 0; e < eta; ++e)
@@ -1660,9 +1615,9 @@ void coarse_wg(mgfem_ctx* c, bool reverse, int reps) {
 // one cycle of a level with the fused kernels (fused.hip): in float64 the cut
 // sweeps of each step are applied by whatever reads its result
 template <class T>
-void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done = false);
+void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done = 0);
 template <class T>
-void cycle_fused(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
+void cycle_fused(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   constexpr bool f32 = sizeof(T) == 4;
   const int cl = coarse_level(c);
   Level& C = c->lv[l + 1];
@@ -1675,7 +1630,7 @@ void cycle_fused(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
     if (f32) cut_sweeps<T>(c, l, false);
   };
   const int pre = reverse ? c->p.nu2 : c->p.nu1, post = reverse ? c->p.nu1 : c->p.nu2;
-  for (int s = first_sweep_done ? 1 : 0; s < pre; ++s) step(false);
+  for (int s = steps_done; s < pre; ++s) step(false);
   const bool fc = l + 1 != cl && fused_level(c, l + 1, f32);
   fused_restrict(c, l, f32, l + 1 != cl && !fc, reverse);
   C.pend = false;
@@ -1695,7 +1650,7 @@ void cycle_fused(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
 }
 
 template <class T>
-void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
+void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   const int nl = (int)c->lv.size();
   const int cl = coarse_level(c);
   if (cl >= 0 && l == cl) {
@@ -1705,15 +1660,12 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
   if (l == nl - 1) return;  // unreachable: the coarse plan always covers the coarsest level
   constexpr bool f32 = sizeof(T) == 4;
   if (fused_level(c, l, f32)) {
-    cycle_fused<T>(c, l, reverse, first_sweep_done);
+    cycle_fused<T>(c, l, reverse, steps_done);
     return;
   }
   const int pre = reverse ? c->p.nu2 : c->p.nu1;
   const int post = reverse ? c->p.nu1 : c->p.nu2;
-  for (int s = 0; s < pre; ++s) {
-    if (s == 0 && first_sweep_done) cut_sweeps<T>(c, l, reverse);
-    else smooth<T>(c, l, reverse);
-  }
+  for (int s = steps_done; s < pre; ++s) smooth<T>(c, l, reverse);
   if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
   else launch_resrestrict<T, 16, 8, 512>(c, l);
   c->lv[l + 1].pend = false;  // the iterate there is zero now (in memory too)
@@ -1739,19 +1691,44 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, bool first_sweep_done) {
 }  // namespace
 
 void run_cycle(mgfem_ctx* c, const CycleOpts& o) {
-  if (o.fp32) cycle_level<float>(c, 0, o.reverse, o.first_sweep_done);
-  else cycle_level<double>(c, 0, o.reverse, o.first_sweep_done);
+  if (o.fp32) cycle_level<float>(c, 0, o.reverse, o.steps_done);
+  else cycle_level<double>(c, 0, o.reverse, o.steps_done);
 }
 
-void first_sweep_with_norm(mgfem_ctx* c) {
+Reduce next_reduce(mgfem_ctx* c, const double* part, int nb) {
+  c->red_seq += 1.0;
+  return Reduce{part, nb, c->red_out, c->red_host, c->red_seq_dev};
+}
+
+// The launch behind the sweep with the norm carries the norm's reduction in
+// one more workgroup: the cut sweeps, or on a fused level the second step,
+// which writes a third buffer so that the iterate of the norm stays whole
+// (profiled solves time that step, and repeat it, alone).  A launch of its own
+// took 4.5-5.7 us of each cycle: solves of the circle with N = 64 took 268 us,
+// 239 without it, of the flower with N = 1024 1198 and 1171.
+int first_steps_with_norm(mgfem_ctx* c) {
+  Level& L0 = c->lv[0];
+  auto alone = [&](const Reduce& r) { hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, r); };
+  if (L0.empty()) return 1;
   if (!fused_level(c, 0, false)) {
     sweep<double>(c, 0, false, true);
-    return;
+    const Reduce red = next_reduce(c, c->sweep_part, L0.ntiles);
+    if (c->p.nu1 > 0) cut_sweeps<double>(c, 0, false, &red);
+    else alone(red);
+    return 1;
   }
+  const int in = L0.cur;
   fused_sweep(c, 0, false, true, false);
-  c->red_seq += 1.0;
-  hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, (const double*)c->sweep_part, c->lv[0].fp.ntiles,
-                     c->red_out, c->red_host, c->red_seq_dev);
+  const Reduce red = next_reduce(c, c->sweep_part, L0.fp.ntiles);
+  if (L0.X[2]) {
+    L0.keep = in;
+    if (c->prof.on) alone(red);
+    fused_sweep(c, 0, false, false, false, c->prof.on ? nullptr : &red);
+    return 2;
+  }
+  if (c->p.nu1 == 0) L0.pend = false;
+  alone(red);
+  return 1;
 }
 
 // ---- batched solves on the tiled kernels: float-cycle entries and launches.
