@@ -1373,7 +1373,7 @@ int build_fused(mgfem_ctx* c) {
     if (!F.ok) continue;
     F.ntiles = tot[8 * l + 4];
     // the second step carries the reduction of the first one's norm
-    if (l == 0 && !f32 && c->p.nu1 >= 2 && !L.X[2]) MGFEM_HIP_TRY(ctx_alloc_t(c, &L.X[2], L.n));
+    if (l == 0 && !f32 && c->p.nu1 >= 2) L.X[2] = c->lam;
     const size_t nst = (size_t)tot[8 * l + 5], nseg = (size_t)tot[8 * l + 6], v = f32 ? 4 : 8;
     char* buf = nullptr;
     MGFEM_HIP_TRY(ctx_alloc(c, reinterpret_cast<void**>(&buf),

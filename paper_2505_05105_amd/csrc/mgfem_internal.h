@@ -117,6 +117,16 @@ struct FusedPlan {
   double* xs = nullptr;               // their values after the pending sweeps
 };
 
+// The one-pass downward half of the largest levels (stream.hip): the windows,
+// and the tiles and residual tiles of the rest.
+struct StreamPlan {
+  bool ok = false;
+  int nwin = 0, nband = 0, nrr = 0;
+  int4* win = nullptr;
+  int* band = nullptr;     // their tmeta entries
+  int* rr_band = nullptr;  // their entries of the residual tile list
+};
+
 struct Level {
   int N = 0;
   int stride = 0;  // N + 1
@@ -162,6 +172,7 @@ struct Level {
   int* tc_pos = nullptr;
   int tp_max = 0, tc_max = 0;
   FusedPlan fp;
+  StreamPlan sp;
   bool grouped = false, tiled = false;  // the separate kernels' plans exist
   bool pend = false;  // forward: the current iterate's last cut sweeps are not applied yet, x + D fp.r[cur];
                       // transposed: fp.r[cur] is its residual at the cut vertices (host-side state)
@@ -355,7 +366,8 @@ struct mgfem_ctx {
   double* F = nullptr;
   double* F64tmp = nullptr;  // outer residual / scratch on level 0
   double* zero = nullptr;    // all-zero vector of level 0
-  double* lam = nullptr;     // adjoint state when the caller passes none
+  double* lam = nullptr;     // adjoint state when the caller passes none; in forward solves level 0's third
+                             // iterate buffer (zero at the inactive nodes, as every iterate)
   // coarsest exact solve
   double* coarse_L = nullptr;  // cn x cn lower Cholesky factor, then its inverse
   int* coarse_idx = nullptr;   // cn node indices
@@ -515,6 +527,12 @@ void fused_entry(mgfem_ctx* m, int l, void* out);
 int fused_units(mgfem_ctx* m, int l);
 void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, int nwork, int par, int parc, bool zero,
                   bool up);
+// one-pass downward half (stream.hip): whether a level may take it, its plan,
+// and the pass over the windows (iterate buffers in, after the first sweep and
+// after the second; part: the norm's partials of the start iterate, or null)
+bool stream_candidate(const mgfem_ctx* c, int l);
+int build_stream(mgfem_ctx* c, int l);
+void stream_pass(mgfem_ctx* c, int l, int in, int mid, int out, double* part);
 // sweep tile shapes, all with 512 threads (a workgroup's load phase is bound
 // by the memory instructions each wave issues, so more waves per tile start
 // the phases sooner): 64 x 32 on a finest level with N >= 2048, 64 x 16 on

@@ -129,16 +129,6 @@ __device__ inline T gs_value(const T* __restrict__ A, int64_t n, int64_t k, bool
   return (T(3) * bv + q1_neighbours<T, RW>(su, q)) * T(0.125);
 }
 
-// One full four-colour sweep of a TW x TH tile.  The iterate is staged in
-// LDS (tile plus a halo of 4) together with the tile plan's stored rows; each
-// thread prefetches the flags and right-hand sides of the nodes it updates in
-// the four phases into registers.  A node's value is final after the phase of
-// its colour, so core nodes are written out right there.
-//  prolong: the staged iterate is x + P x_c (the coarse-grid correction is
-//           applied on the fly, so the first post-smoothing sweep needs no
-//           separate prolongation pass).
-//  norm:    before the first phase, the residual of the incoming iterate on
-//           the core is reduced into per-tile partials (max |r|, sum r^2).
 __global__ __launch_bounds__(1024) void k_reduce_pairs(Reduce r) {
   __shared__ double sh[32];
   reduce_block<1024, 4>(r, sh);
@@ -150,7 +140,17 @@ __device__ inline void lds_load16(const void* src, void* dst) {
   __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 
-// the sweep of tile t of the level's tile list (one workgroup)
+// One full four-colour sweep of a TW x TH tile.  The iterate is staged in
+// LDS (tile plus a halo of 4) together with the tile plan's stored rows; each
+// thread prefetches the flags and right-hand sides of the nodes it updates in
+// the four phases into registers.  A node's value is final after the phase of
+// its colour, so core nodes are written out right there.
+//  prolong: the staged iterate is x + P x_c (the coarse-grid correction is
+//           applied on the fly, so the first post-smoothing sweep needs no
+//           separate prolongation pass).
+//  norm:    before the first phase, the residual of the incoming iterate on
+//           the core is reduced into per-tile partials (max |r|, sum r^2).
+// The sweep of tile t of the level's tile list (one workgroup).
 template <class T, int TW, int TH, int BS>
 __device__ void sweep_tile(const SweepArgs<T>& a, const int t) {
   constexpr int RW = TW + 2 * kHalo, RH = TH + 2 * kHalo;
@@ -1368,7 +1368,8 @@ SweepArgs<T> sweep_args(mgfem_ctx* c, int l, bool reverse, bool norm, bool prolo
     a.xc = Xp<T>(C, C.cur);
     a.sc = C.stride;
   }
-  a.xin = Xp<T>(L, L.cur);
+  // a zero iterate that was not cleared reads as the (larger) all-zero vector
+  a.xin = std::is_same<T, double>::value && L.zero ? reinterpret_cast<const T*>(c->zero) : Xp<T>(L, L.cur);
   a.xout = Xp<T>(L, L.next());
   a.b = Bp<T>(L);
   a.A = Ap<T>(L);
@@ -1424,6 +1425,7 @@ void launch_sweep(mgfem_ctx* c, int l, bool reverse, bool norm, bool prolong_fro
     hipLaunchKernelGGL((k_sweep<T, TW, TH, BS>), dim3(8 * a.per), dim3(BS), 0, c->s, a);
   }
   L.cur = L.next();
+  L.zero = false;
 }
 
 template <class T>
@@ -1532,6 +1534,48 @@ void launch_resrestrict(mgfem_ctx* c, int l) {
   const ResArgs<T> a = rr_args<T, CW, CH>(c, l);
   hipLaunchKernelGGL((k_resrestrict<T, CW, CH, BS>), dim3(8 * a.per), dim3(BS), 0, c->s, a);
 }
+
+// the downward half of a cycle of a streaming level; the residual norm of the
+// start iterate on request, its reduction behind the first sweep
+template <int TH>
+void stream_down(mgfem_ctx* c, int l, bool norm) {
+  Level& L = c->lv[l];
+  const StreamPlan& S = L.sp;
+  const int in = L.cur, mid = in == 0 ? 1 : 0, out = 3 - in - mid;
+  stream_pass(c, l, in, mid, out, norm ? c->sweep_part : nullptr);
+  auto band = [&](int from, int to, bool nrm) {
+    L.cur = from;
+    SweepArgs<double> a = sweep_args<double, 64, TH>(c, l, false, nrm, false);
+    a.xout = L.X[to];
+    a.tmeta = S.band;
+    a.ntiles = S.nband;
+    a.per = (S.nband + 7) / 8;
+    a.part = c->sweep_part + 2 * S.nwin;
+    if (S.nband > 0) hipLaunchKernelGGL((k_sweep<double, 64, TH, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
+    L.cur = to;
+    L.zero = false;
+  };
+  band(in, mid, norm);
+  if (norm) {
+    const Reduce red = next_reduce(c, c->sweep_part, S.nwin + S.nband);
+    cut_sweeps<double>(c, l, false, &red);
+  } else {
+    cut_sweeps<double>(c, l, false);
+  }
+  band(mid, out, false);
+  cut_sweeps<double>(c, l, false);
+  ResArgs<double> a = rr_args<double, 32, 16>(c, l);
+  a.tiles = S.rr_band;
+  a.ntiles = S.nrr;
+  a.per = (S.nrr + 7) / 8;
+  if (S.nrr > 0) hipLaunchKernelGGL((k_resrestrict<double, 32, 16, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
+}
+void stream_down(mgfem_ctx* c, int l, bool norm) {
+  if (sweep_shape(c, l) == kShapeFinest) stream_down<32>(c, l, norm);
+  else stream_down<16>(c, l, norm);
+}
+// a profiled solve times the sweeps, so it runs them
+inline bool streams(const mgfem_ctx* c, int l) { return c->lv[l].sp.ok && !c->prof.on; }
 
 template <class T>
 void prolong(mgfem_ctx* c, int l) {
@@ -1665,11 +1709,17 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   }
   const int pre = reverse ? c->p.nu2 : c->p.nu1;
   const int post = reverse ? c->p.nu1 : c->p.nu2;
-  for (int s = steps_done; s < pre; ++s) smooth<T>(c, l, reverse);
-  if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
-  else launch_resrestrict<T, 16, 8, 512>(c, l);
-  c->lv[l + 1].pend = false;  // the iterate there is zero now (in memory too)
-  c->lv[l + 1].zero = l + 1 != cl && fused_level(c, l + 1, f32);
+  const bool stream = !f32 && !reverse && streams(c, l);
+  if (stream) {
+    if (steps_done == 0) stream_down(c, l, false);
+  } else {
+    for (int s = steps_done; s < pre; ++s) smooth<T>(c, l, reverse);
+    if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
+    else launch_resrestrict<T, 16, 8, 512>(c, l);
+  }
+  // the iterate there is zero now (in memory too, unless this level streamed)
+  c->lv[l + 1].pend = false;
+  c->lv[l + 1].zero = l + 1 != cl && (stream || fused_level(c, l + 1, f32));
   // coarse-grid visits: gamma* (section 3.2); the two-grid scheme instead
   // solves the first coarse problem with coarse_cycles V-cycles from zero
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
@@ -1710,6 +1760,12 @@ int first_steps_with_norm(mgfem_ctx* c) {
   Level& L0 = c->lv[0];
   auto alone = [&](const Reduce& r) { hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, r); };
   if (L0.empty()) return 1;
+  if (streams(c, 0)) {  // all of the downward half
+    const int in = L0.cur;
+    stream_down(c, 0, true);
+    L0.keep = in;
+    return 2;
+  }
   if (!fused_level(c, 0, false)) {
     sweep<double>(c, 0, false, true);
     const Reduce red = next_reduce(c, c->sweep_part, L0.ntiles);
@@ -2282,6 +2338,12 @@ int cut_plan(mgfem_ctx* c, int l) {
 int build_cycle_plans(mgfem_ctx* c) {
   const int cl = coarse_level(c);
   const bool f32 = c->p.precision == MGFEM_PREC_MIXED;
+  // (a window's columns and rows come in pairs from an even one)
+  for (int l = 0; l < cl; ++l)
+    if (stream_candidate(c, l)) {
+      c->lv[l].bbox[0] &= ~1;
+      c->lv[l].bbox[2] &= ~1;
+    }
   if (const int e = build_cutpos(c, 0)) return e;  // the gradient's G^T too
   if (f32)
     for (int l = 0; l < cl; ++l)
@@ -2290,6 +2352,9 @@ int build_cycle_plans(mgfem_ctx* c) {
   for (int l = 0; l < cl; ++l)
     if (!c->lv[l].fp.ok || (f32 && l == 0))
       if (const int e = separate_plans(c, l)) return e;
+  for (int l = 0; l < cl; ++l)
+    if (!c->lv[l].fp.ok)
+      if (const int e = build_stream(c, l)) return e;
   return MGFEM_OK;
 }
 
