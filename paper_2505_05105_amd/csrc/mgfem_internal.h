@@ -117,12 +117,13 @@ struct FusedPlan {
   double* xs = nullptr;               // their values after the pending sweeps
 };
 
-// The one-pass downward half of the largest levels (stream.hip): the windows,
-// and the tiles and residual tiles of the rest.
+// The streaming passes of the largest levels (stream.hip): the windows of the
+// downward and of the upward one, and the tiles and residual tiles of the rest.
 struct StreamPlan {
   bool ok = false;
-  int nwin = 0, nband = 0, nrr = 0;
+  int nwin = 0, nup = 0, nband = 0, nrr = 0;
   int4* win = nullptr;
+  int4* up = nullptr;
   int* band = nullptr;     // their tmeta entries
   int* rr_band = nullptr;  // their entries of the residual tile list
 };
@@ -136,7 +137,7 @@ struct Level {
   uint8_t* flags = nullptr;
   uint8_t* cellcut = nullptr;  // N*N, 1 on cut cells of this level
   double* X[3] = {nullptr, nullptr, nullptr};  // iterates, in turn (the third on a fused level 0, see keep)
-  float* X32[2] = {nullptr, nullptr};
+  float* X32[3] = {nullptr, nullptr, nullptr};
   double* b = nullptr;
   float* b32 = nullptr;
   int cur = 0;                // which X holds the current iterate (host-side state)
@@ -527,12 +528,14 @@ void fused_entry(mgfem_ctx* m, int l, void* out);
 int fused_units(mgfem_ctx* m, int l);
 void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, int nwork, int par, int parc, bool zero,
                   bool up);
-// one-pass downward half (stream.hip): whether a level may take it, its plan,
-// and the pass over the windows (iterate buffers in, after the first sweep and
-// after the second; part: the norm's partials of the start iterate, or null)
+// streaming passes (stream.hip): whether a level may take them, the plan, and
+// the passes over the windows: down (iterate buffers in, after the first sweep
+// and after the second; part: the norm's partials of the start iterate, or
+// null) and up (x + P x_c and a sweep)
 bool stream_candidate(const mgfem_ctx* c, int l);
 int build_stream(mgfem_ctx* c, int l);
-void stream_pass(mgfem_ctx* c, int l, int in, int mid, int out, double* part);
+void stream_down_windows(mgfem_ctx* c, int l, bool fp32, int in, int mid, int out, double* part);
+void stream_up_windows(mgfem_ctx* c, int l, bool fp32, int in, int out);
 // sweep tile shapes, all with 512 threads (a workgroup's load phase is bound
 // by the memory instructions each wave issues, so more waves per tile start
 // the phases sooner): 64 x 32 on a finest level with N >= 2048, 64 x 16 on

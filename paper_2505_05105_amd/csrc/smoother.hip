@@ -1369,7 +1369,7 @@ SweepArgs<T> sweep_args(mgfem_ctx* c, int l, bool reverse, bool norm, bool prolo
     a.sc = C.stride;
   }
   // a zero iterate that was not cleared reads as the (larger) all-zero vector
-  a.xin = std::is_same<T, double>::value && L.zero ? reinterpret_cast<const T*>(c->zero) : Xp<T>(L, L.cur);
+  a.xin = L.zero ? reinterpret_cast<const T*>(c->zero) : Xp<T>(L, L.cur);
   a.xout = Xp<T>(L, L.next());
   a.b = Bp<T>(L);
   a.A = Ap<T>(L);
@@ -1535,44 +1535,58 @@ void launch_resrestrict(mgfem_ctx* c, int l) {
   hipLaunchKernelGGL((k_resrestrict<T, CW, CH, BS>), dim3(8 * a.per), dim3(BS), 0, c->s, a);
 }
 
+// sweep of the band of a streaming level (with `up` of x + P x_c), from one
+// iterate buffer to another, which becomes the current one
+template <class T, int TH>
+void band_sweep(mgfem_ctx* c, int l, int from, int to, double* part, bool up) {
+  Level& L = c->lv[l];
+  const StreamPlan& S = L.sp;
+  L.cur = from;
+  SweepArgs<T> a = sweep_args<T, 64, TH>(c, l, false, part != nullptr, up);
+  a.xout = Xp<T>(L, to);
+  a.tmeta = S.band;
+  a.ntiles = S.nband;
+  a.per = (S.nband + 7) / 8;
+  a.part = part;
+  if (S.nband > 0) hipLaunchKernelGGL((k_sweep<T, 64, TH, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
+  L.cur = to;
+  L.zero = false;
+}
+template <class T>
+void band_sweep(mgfem_ctx* c, int l, int from, int to, double* part, bool up) {
+  if (sweep_shape(c, l) == kShapeFinest) band_sweep<T, 32>(c, l, from, to, part, up);
+  else band_sweep<T, 16>(c, l, from, to, part, up);
+}
 // the downward half of a cycle of a streaming level; the residual norm of the
 // start iterate on request, its reduction behind the first sweep
-template <int TH>
+template <class T>
 void stream_down(mgfem_ctx* c, int l, bool norm) {
   Level& L = c->lv[l];
   const StreamPlan& S = L.sp;
   const int in = L.cur, mid = in == 0 ? 1 : 0, out = 3 - in - mid;
-  stream_pass(c, l, in, mid, out, norm ? c->sweep_part : nullptr);
-  auto band = [&](int from, int to, bool nrm) {
-    L.cur = from;
-    SweepArgs<double> a = sweep_args<double, 64, TH>(c, l, false, nrm, false);
-    a.xout = L.X[to];
-    a.tmeta = S.band;
-    a.ntiles = S.nband;
-    a.per = (S.nband + 7) / 8;
-    a.part = c->sweep_part + 2 * S.nwin;
-    if (S.nband > 0) hipLaunchKernelGGL((k_sweep<double, 64, TH, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
-    L.cur = to;
-    L.zero = false;
-  };
-  band(in, mid, norm);
+  stream_down_windows(c, l, sizeof(T) == 4, in, mid, out, norm ? c->sweep_part : nullptr);
+  band_sweep<T>(c, l, in, mid, norm ? c->sweep_part + 2 * S.nwin : nullptr, false);
   if (norm) {
     const Reduce red = next_reduce(c, c->sweep_part, S.nwin + S.nband);
-    cut_sweeps<double>(c, l, false, &red);
+    cut_sweeps<T>(c, l, false, &red);
   } else {
-    cut_sweeps<double>(c, l, false);
+    cut_sweeps<T>(c, l, false);
   }
-  band(mid, out, false);
-  cut_sweeps<double>(c, l, false);
-  ResArgs<double> a = rr_args<double, 32, 16>(c, l);
+  band_sweep<T>(c, l, mid, out, nullptr, false);
+  cut_sweeps<T>(c, l, false);
+  ResArgs<T> a = rr_args<T, 32, 16>(c, l);
   a.tiles = S.rr_band;
   a.ntiles = S.nrr;
   a.per = (S.nrr + 7) / 8;
-  if (S.nrr > 0) hipLaunchKernelGGL((k_resrestrict<double, 32, 16, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
+  if (S.nrr > 0) hipLaunchKernelGGL((k_resrestrict<T, 32, 16, 512>), dim3(8 * a.per), dim3(512), 0, c->s, a);
 }
-void stream_down(mgfem_ctx* c, int l, bool norm) {
-  if (sweep_shape(c, l) == kShapeFinest) stream_down<32>(c, l, norm);
-  else stream_down<16>(c, l, norm);
+template <class T>
+void stream_up(mgfem_ctx* c, int l) {
+  Level& L = c->lv[l];
+  const int in = L.cur, to = L.next();
+  stream_up_windows(c, l, sizeof(T) == 4, in, to);
+  band_sweep<T>(c, l, in, to, nullptr, true);
+  cut_sweeps<T>(c, l, false);
 }
 // a profiled solve times the sweeps, so it runs them
 inline bool streams(const mgfem_ctx* c, int l) { return c->lv[l].sp.ok && !c->prof.on; }
@@ -1709,9 +1723,9 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   }
   const int pre = reverse ? c->p.nu2 : c->p.nu1;
   const int post = reverse ? c->p.nu1 : c->p.nu2;
-  const bool stream = !f32 && !reverse && streams(c, l);
+  const bool stream = !reverse && streams(c, l);
   if (stream) {
-    if (steps_done == 0) stream_down(c, l, false);
+    if (steps_done == 0) stream_down<T>(c, l, false);
   } else {
     for (int s = steps_done; s < pre; ++s) smooth<T>(c, l, reverse);
     if (c->lv[l].N >= 1024) launch_resrestrict<T, 32, 16, 512>(c, l);
@@ -1732,8 +1746,12 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
     prolong<T>(c, l);
     for (int s = 0; s < post; ++s) smooth<T>(c, l, reverse);
   } else {
-    sweep<T>(c, l, false, false, true);  // x + P x_c, then the sweep
-    cut_sweeps<T>(c, l, false);
+    if (stream && c->lv[l].sp.nup > 0) {
+      stream_up<T>(c, l);
+    } else {
+      sweep<T>(c, l, false, false, true);  // x + P x_c, then the sweep
+      cut_sweeps<T>(c, l, false);
+    }
     for (int s = 1; s < post; ++s) smooth<T>(c, l, reverse);
   }
 }
@@ -1762,7 +1780,7 @@ int first_steps_with_norm(mgfem_ctx* c) {
   if (L0.empty()) return 1;
   if (streams(c, 0)) {  // all of the downward half
     const int in = L0.cur;
-    stream_down(c, 0, true);
+    stream_down<double>(c, 0, true);
     L0.keep = in;
     return 2;
   }

@@ -1,28 +1,29 @@
-// The downward half of a cycle on the largest levels: two smoothing sweeps,
-// the residual and its restriction in one pass over memory.
+// Streaming passes of the largest levels: downwards two smoothing sweeps, the
+// residual and its restriction in one pass over memory, upwards the
+// prolongation and a sweep.
 //
-// These levels are bound by their bytes (at N = 16384 a sweep moves its 24
-// bytes per unknown at 8 TB/s), and the separate kernels read the iterate and
-// the right-hand side three times on the way down.  Where every row in reach is
-// the interior Q1 row a wave can do all of it as it streams down the grid: 64
-// lanes of two columns each, rows in registers, the neighbouring columns by
-// lane shifts, no LDS and no barrier.  Colours 0 and 1 are the even grid rows
-// and 2 and 3 the odd ones, so a sweep takes one pass: even row 2m needs the old
-// odd rows beside it, odd row 2m - 1 the new even ones.  The second sweep
-// follows a row pair behind, the residual and its restriction another one.
-// A window's values are exact on its core; the 10 columns and 6 rows around it
-// are computed again by the windows beside it (a third more arithmetic than
-// nodes, of which there is plenty).
+// These levels are bound by their bytes, and the separate kernels read the
+// iterate and the right-hand side three times on the way down.  Where every row
+// in reach is the interior Q1 row a wave can do all of it as it streams down
+// the grid: 64 lanes of two columns each, rows in registers, the neighbouring
+// columns by lane shifts, no LDS and no barrier.  Colours 0 and 1 are the even
+// grid rows and 2 and 3 the odd ones, so a sweep takes one pass: even row 2m
+// needs the old odd rows beside it, odd row 2m - 1 the new even ones.  The
+// second sweep follows a row pair behind, the residual and its restriction
+// another one.  A window's values are exact on its core; the columns and rows
+// around it are computed again by the windows beside it.
 //
 // The windows are runs of sweep tiles away from the boundary.  The other tiles,
 // the band, run the separate kernels, cut sweeps included.  The iterate goes
 // through three buffers: the band's first sweep, and the windows that touch the
 // band, write the second one, the second sweep the third.
 //
-// Measured (flower, float64, MI355X): at N = 4096 the two sweeps and the
-// residual took 22 + 22 + 19 us in three launches; the windows take 21.5, the
-// band 10 + 11 + 10.  At N = 16384 the windows take 320 us, the band 22 + 22 +
-// 13, a sweep of the whole level alone 400; a solve went from 31.3 to 20.4 ms.
+// Measured (flower, float64, MI355X).  N = 16384 (54 million unknowns, 1.4 GB
+// per pass): down 320 us (4.4 TB/s; a large copy reaches 5.2) where two sweeps
+// and the residual took 400 + 400 + 300, up 308 (before 386); the band's
+// launches 13 to 40.  A solve went from 31.3 to 20 ms.  N = 4096 (90 MB per
+// pass, in the last-level cache): down 20-21 us and the band 10 + 11 + 10 where
+// the three launches took 22 + 22 + 19, up 20 and 17 (before 32).
 #include <algorithm>
 
 #include "mgfem_internal.h"
@@ -31,55 +32,139 @@
 namespace mgfem {
 namespace {
 
-constexpr int kHX = 10, kHY = 6;  // columns on either side of a window's core, rows above and below
-constexpr int kCore = 128 - 2 * kHX;
+constexpr int kHX = 10, kHY = 6;     // columns on either side of a window's core, rows above and below
+constexpr int kUpX = 6, kUpY = 2;    // of the upward pass (4 columns of the sweep, one of the prolongation)
+constexpr int kCore = 128 - 2 * kHX, kUpCore = 128 - 2 * kUpX;
 
+template <class T>
 struct Row {  // a lane's two columns: even, odd
-  double e, o;
+  T e, o;
 };
+template <class T>
 struct Pair {  // an even and the next odd row: iterate, right-hand side
-  Row xe, xo, be, bo;
+  Row<T> xe, xo, be, bo;
 };
 typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
 
-__device__ inline Row load_row(const double* p) {
+__device__ inline Row<double> load_row(const double* p) {
   const double2u v = *reinterpret_cast<const double2u*>(p);
-  return Row{v.x, v.y};
+  return Row<double>{v.x, v.y};
 }
-__device__ inline void store_row(double* p, const Row& v) {
-  double2u w;
-  w.x = v.e;
-  w.y = v.o;
-  *reinterpret_cast<double2u*>(p) = w;
+__device__ inline Row<float> load_row(const float* p) {
+  const float2u v = *reinterpret_cast<const float2u*>(p);
+  return Row<float>{v.x, v.y};
 }
+// Stores that no branch guards: a lane or row outside a window's core stores
+// beyond the buffer's end, where the hardware drops it.  (Loads and stores
+// complete in order behind one counter, so a store that may or may not have
+// been issued makes the compiler wait for rows it only wants three pairs
+// later.  With the copies below, N = 2048 18.4 us before, 14.6 after.)
+struct Out {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ Out(void* base, unsigned bytes) : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000)) {}
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  __device__ void put(unsigned at, const Row<double>& v) const {
+    u4 w;
+    w.x = __double2loint(v.e);
+    w.y = __double2hiint(v.e);
+    w.z = __double2loint(v.o);
+    w.w = __double2hiint(v.o);
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, at, 0, 0);
+  }
+  __device__ void put(unsigned at, double v) const {
+    u2 w;
+    w.x = __double2loint(v);
+    w.y = __double2hiint(v);
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, at, 0, 0);
+  }
+  __device__ void put(unsigned at, const Row<float>& v) const {
+    u2 w;
+    w.x = __float_as_uint(v.e);
+    w.y = __float_as_uint(v.o);
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, at, 0, 0);
+  }
+  __device__ void put(unsigned at, float v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, at, 0, 0);
+  }
+};
 
 // the value of the lane to the left, to the right (wave shifts; a wave's end
 // lanes get 0, which only halo columns see)
-__device__ inline double lane_left(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
+template <int CTRL>
+__device__ inline float lane_shift(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ inline double lane_shift(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
-__device__ inline double lane_right(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
+template <class T>
+__device__ inline T lane_left(T v) {
+  return lane_shift<0x138>(v);
+}
+template <class T>
+__device__ inline T lane_right(T v) {
+  return lane_shift<0x130>(v);
+}
+
+// A copy in registers of its own.  What a step keeps of a loaded row for the
+// next steps goes through it, so that the row's registers are free when the row
+// three pairs on is loaded into them: left to itself the compiler rotates the
+// prefetched rows through copies at the end of its unrolled loop, each of which
+// waits for a load just issued.
+__device__ inline float own(float v) {
+  float w;
+  asm("v_mov_b32 %0, %1" : "=v"(w) : "v"(v));
+  return w;
+}
+__device__ inline double own(double v) {
+  int lo, hi;
+  asm("v_mov_b32 %0, %1" : "=v"(lo) : "v"(__double2loint(v)));
+  asm("v_mov_b32 %0, %1" : "=v"(hi) : "v"(__double2hiint(v)));
   return __hiloint2double(hi, lo);
 }
+template <class T>
+__device__ inline Row<T> own(const Row<T>& r) {
+  return Row<T>{own(r.e), own(r.o)};
+}
+
+// A sweep does not use the old values of its first colour: their half of a
+// row load is used here, so that nothing else takes those registers while the
+// load is in flight (and waits for it).
+template <class T>
+__device__ inline void use(T v) {
+  asm volatile("" : : "v"(v));
+}
+
+__device__ inline double fma_t(double a, double b, double c) { return fma(a, b, c); }
+__device__ inline float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 
 // sums of three nodes of a row around each column, l and r the values of the
 // neighbouring lanes' odd and even columns
-__device__ inline Row sum3(const Row& x, double l, double r) { return Row{(l + x.e) + x.o, (x.e + x.o) + r}; }
-__device__ inline double gs(double b, double below, double pair, double above) {
-  return fma(3.0, b, (below + pair) + above) * 0.125;
+template <class T>
+__device__ inline Row<T> sum3(const Row<T>& x, T l, T r) {
+  return Row<T>{(l + x.e) + x.o, (x.e + x.o) + r};
 }
-__device__ inline double resid(double b, double x, double below, double pair, double above) {
-  return b - fma(8.0 / 3.0, x, -(((below + pair) + above) * (1.0 / 3.0)));
+// the tile kernels' expressions, operation for operation (float32 results do
+// not depend on which of the two computed a node)
+template <class T>
+__device__ inline T gs(T b, T below, T pair, T above) {
+  return fma_t(T(3), b, (below + pair) + above) * T(0.125);
+}
+template <class T>
+__device__ inline T resid(T b, T x, T below, T pair, T above) {
+  return b - fma_t(T(8) / T(3), x, -(((below + pair) + above) * T(1.0 / 3.0)));
 }
 
 // Gauss-Seidel on both columns of a row between rows with the sums `below` and
 // `above`; l: the left lane's odd value before the update.  Returns the row's
 // new sums; l and r become the neighbours' new values.
-__device__ inline Row sweep_row(Row& x, const Row& b, const Row& below, const Row& above, double& l, double& r) {
+template <class T>
+__device__ inline Row<T> sweep_row(Row<T>& x, const Row<T>& b, const Row<T>& below, const Row<T>& above, T& l, T& r) {
   x.e = gs(b.e, below.e, l + x.o, above.e);
   r = lane_right(x.e);
   x.o = gs(b.o, below.o, x.e + r, above.o);
@@ -87,16 +172,18 @@ __device__ inline Row sweep_row(Row& x, const Row& b, const Row& below, const Ro
   return sum3(x, l, r);
 }
 
+template <class T>
 struct StreamArgs {
-  const double* x;  // start iterate (null: zero)
-  const double* b;
-  double* out1;     // after the first sweep (windows that touch the band)
-  double* out;      // after the second
-  double* bc;       // restricted residual
+  const T* x;   // start iterate (null: zero)
+  const T* b;
+  T* out1;      // down: after the first sweep (windows that touch the band)
+  T* out;       // after the last
+  T* bc;        // down: restricted residual
+  const T* xc;  // up: coarse iterate
   int N, s, sc;
   const int4* win;  // x, y, width | rows << 16, touches the band
   int nwin;
-  double* part;     // per window (max |r|, sum r^2) of the start iterate
+  double* part;  // down: per window (max |r|, sum r^2) of the start iterate
 };
 
 constexpr int kDepth = 3;  // row pairs in flight
@@ -109,121 +196,127 @@ __device__ inline int window_of_wave(int nwin) {
 }
 
 // two sweeps, residual, restriction
-template <bool ZERO, bool NORM>
-__global__ __launch_bounds__(256) void k_stream(StreamArgs a) {
-  const int wi = __builtin_amdgcn_readfirstlane(window_of_wave(a.nwin));
-  if (wi >= a.nwin) return;  // whole waves; no barriers below
-  const int4 W = a.win[wi];
+template <class T, bool ZERO, bool NORM, bool BORDER>
+__device__ inline void stream_window(const StreamArgs<T>& a, const int wi, const int4 W) {
   const int X = W.x, Y = W.y, width = W.z & 0xffff, H = W.z >> 16, lane = threadIdx.x & 63;
-  const bool border = W.w != 0;
   const int col = X - kHX + 2 * lane;
   const bool core = lane >= kHX / 2 && lane < (kHX + width) / 2;
   const int lc = min(col, a.N - 1);  // lanes beyond the window's halo read inside the grid
   const int m0 = Y / 2 - kHY / 2, steps = H / 2 + kHY - 1, last = Y + H + kHY - 3;
+  // byte offsets from the core's first row (a row before or behind the core
+  // is beyond the end, as is a lane beside it)
+  const unsigned rb = (unsigned)(a.s * sizeof(T)), rc = (unsigned)(a.sc * sizeof(T));
+  const unsigned at = core ? (unsigned)(col * (int)sizeof(T)) : 0x80000000u, atc = core ? (unsigned)((col >> 1) * (int)sizeof(T)) : 0x80000000u;
+  const Out out(a.out + (int64_t)Y * a.s, (unsigned)H * rb);
+  const Out out1(a.out1 + (int64_t)Y * a.s, (unsigned)H * rb);
+  const Out bc(a.bc + (int64_t)(Y / 2) * a.sc, (unsigned)(H / 2) * rc);
   auto load = [&](int m) {
-    Pair p;
+    Pair<T> p;
     const int64_t r0 = (int64_t)min(2 * m, last) * a.s + lc, r1 = (int64_t)min(2 * m + 1, last) * a.s + lc;
     if constexpr (!ZERO) {
       p.xe = load_row(a.x + r0);
       p.xo = load_row(a.x + r1);
     } else {
-      p.xe = p.xo = Row{0.0, 0.0};
+      p.xe = p.xo = Row<T>{T(0), T(0)};
     }
     p.be = load_row(a.b + r0);
     p.bo = load_row(a.b + r1);
     return p;
   };
-  Pair q[kDepth];
+  Pair<T> q[kDepth];
 #pragma unroll
-  for (int k = 0; k < kDepth; ++k) q[k] = load(m0 + k);
-  const Row z{0.0, 0.0};
+  for (int k = 0; k < kDepth; ++k) {
+    q[k] = load(m0 + k);
+    __builtin_amdgcn_sched_barrier(0);  // oldest first
+  }
+  const Row<T> z{0.0, 0.0};
   // first sweep: odd row 2m - 1 (values, old sums, right-hand side, left
   // neighbour), new sums of even row 2m - 2; its old sums for the norm
-  Row O = z, Ot = z, Ob = z, Et = z, Eold = z;
-  double Ol = 0.0, Onr = 0.0;
+  Row<T> O = z, Ot = z, Ob = z, Et = z, Eold = z;
+  T Ol = T(0), Onr = T(0);
   // second sweep: even row 2m - 2, odd row 2m - 3 after the first sweep
-  Row F = z, Fb = z, P = z, Pb = z, Pt = z;
-  double Fl = 0.0, Pl = 0.0;
+  Row<T> F = z, Fb = z, P = z, Pb = z, Pt = z;
+  T Fl = T(0), Pl = T(0);
   // residual: even row 2m - 4 after both sweeps, its pair sums and sums, sums
   // of row 2m - 5, restricted part of row 2m - 5
-  Row G = z, Gb = z, Gp = z, Gt = z, Ht = z;
-  double lo = 0.0;
+  Row<T> G = z, Gb = z, Gp = z, Gt = z, Ht = z;
+  T lo = T(0);
   double mx = 0.0, sm = 0.0;
-  auto step = [&](const Pair& p, int m) {
+  auto step = [&](const Pair<T>& p, int m) {
     // --- first sweep: row 2m, then row 2m - 1
-    Row E = p.xe;
-    const Row Nx = p.xo;
-    const double Nl = lane_left(Nx.o), Nr = lane_right(Nx.e);
-    const Row Nt = sum3(Nx, Nl, Nr);
-    double El = lane_left(E.o), Er;
+    if constexpr (!ZERO) use(p.xe.e);
+    Row<T> E = p.xe;
+    const Row<T> Nx = own(p.xo);
+    const T Nl = lane_left(Nx.o), Nr = lane_right(Nx.e);
+    const Row<T> Nt = sum3(Nx, Nl, Nr);
+    T El = lane_left(E.o), Er;
     if constexpr (NORM) {
       // residuals of the start iterate: row 2m, and row 2m - 1 (its
       // neighbours' sums are all old here)
-      const double er = lane_right(E.e);
-      const Row old = sum3(E, El, er);
-      if (core && 2 * m >= Y && 2 * m < Y + H) {
-        const double r0 = resid(p.be.e, E.e, Ot.e, El + E.o, Nt.e);
-        const double r1 = resid(p.be.o, E.o, Ot.o, E.e + er, Nt.o);
-        mx = nanmax2(nanmax2(mx, fabs(r0)), fabs(r1));
-        sm += r0 * r0 + r1 * r1;
-      }
-      if (core && 2 * m - 1 >= Y && 2 * m - 1 < Y + H) {
-        const double r0 = resid(Ob.e, O.e, Eold.e, Ol + O.o, old.e);
-        const double r1 = resid(Ob.o, O.o, Eold.o, O.e + Onr, old.o);
-        mx = nanmax2(nanmax2(mx, fabs(r0)), fabs(r1));
-        sm += r0 * r0 + r1 * r1;
-      }
+      const T er = lane_right(E.e);
+      const Row<T> old = sum3(E, El, er);
+      const bool in0 = core && 2 * m >= Y && 2 * m < Y + H, in1 = core && 2 * m - 1 >= Y && 2 * m - 1 < Y + H;
+      const double r0 = in0 ? (double)resid(p.be.e, E.e, Ot.e, El + E.o, Nt.e) : 0.0;
+      const double r1 = in0 ? (double)resid(p.be.o, E.o, Ot.o, E.e + er, Nt.o) : 0.0;
+      const double r2 = in1 ? (double)resid(Ob.e, O.e, Eold.e, Ol + O.o, old.e) : 0.0;
+      const double r3 = in1 ? (double)resid(Ob.o, O.o, Eold.o, O.e + Onr, old.o) : 0.0;
+      mx = nanmax2(nanmax2(nanmax2(nanmax2(mx, fabs(r0)), fabs(r1)), fabs(r2)), fabs(r3));
+      sm += (r0 * r0 + r1 * r1) + (r2 * r2 + r3 * r3);
       Eold = old;
     }
-    const Row Enew = sweep_row(E, p.be, Ot, Nt, El, Er);
-    double Or;
-    const Row Onew = sweep_row(O, Ob, Et, Enew, Ol, Or);
-    if (border && core) {
-      if (2 * m >= Y && 2 * m < Y + H) store_row(a.out1 + (int64_t)(2 * m) * a.s + col, E);
-      if (2 * m - 1 >= Y && 2 * m - 1 < Y + H) store_row(a.out1 + (int64_t)(2 * m - 1) * a.s + col, O);
+    const Row<T> Enew = sweep_row(E, p.be, Ot, Nt, El, Er);
+    T Or;
+    const Row<T> Onew = sweep_row(O, Ob, Et, Enew, Ol, Or);
+    const unsigned rel = (unsigned)(2 * m - Y);
+    if constexpr (BORDER) {
+      out1.put(at + rel * rb, E);
+      out1.put(at + (rel - 1) * rb, O);
     }
     // --- second sweep: row 2m - 2, then row 2m - 3
-    double Fr, Pr;
-    const Row Ft = sweep_row(F, Fb, Pt, Onew, Fl, Fr);
-    const Row Pt2 = sweep_row(P, Pb, Gt, Ft, Pl, Pr);
-    if (core) {
-      if (2 * m - 2 >= Y && 2 * m - 2 < Y + H) store_row(a.out + (int64_t)(2 * m - 2) * a.s + col, F);
-      if (2 * m - 3 >= Y && 2 * m - 3 < Y + H) store_row(a.out + (int64_t)(2 * m - 3) * a.s + col, P);
-    }
+    T Fr, Pr;
+    const Row<T> Ft = sweep_row(F, Fb, Pt, Onew, Fl, Fr);
+    const Row<T> Pt2 = sweep_row(P, Pb, Gt, Ft, Pl, Pr);
+    out.put(at + (rel - 2) * rb, F);
+    out.put(at + (rel - 3) * rb, P);
     // --- residual: rows 2m - 4 and 2m - 3, restriction to coarse row m - 2
-    const double g0 = resid(Gb.e, G.e, Ht.e, Gp.e, Pt2.e), g1 = resid(Gb.o, G.o, Ht.o, Gp.o, Pt2.o);
-    const double p0 = resid(Pb.e, P.e, Gt.e, Pl + P.o, Ft.e), p1 = resid(Pb.o, P.o, Gt.o, P.e + Pr, Ft.o);
-    const double mid = g0 + 0.5 * (lane_left(g1) + g1);
-    const double hi = p0 + 0.5 * (lane_left(p1) + p1);
-    if (core && 2 * m - 4 >= Y && 2 * m - 4 < Y + H) a.bc[(col >> 1) + (int64_t)(m - 2) * a.sc] = mid + 0.5 * (lo + hi);
+    const T g0 = resid(Gb.e, G.e, Ht.e, Gp.e, Pt2.e), g1 = resid(Gb.o, G.o, Ht.o, Gp.o, Pt2.o);
+    const T p0 = resid(Pb.e, P.e, Gt.e, Pl + P.o, Ft.e), p1 = resid(Pb.o, P.o, Gt.o, P.e + Pr, Ft.o);
+    const T mid = g0 + T(0.5) * (lane_left(g1) + g1);
+    const T hi = p0 + T(0.5) * (lane_left(p1) + p1);
+    bc.put(atc + (unsigned)(m - 2 - Y / 2) * rc, mid + T(0.5) * (lo + hi));
     lo = hi;
     // --- shift
     Ht = Pt2;
     G = F;
     Gb = Fb;
-    Gp = Row{Fl + F.o, F.e + Fr};
+    Gp = Row<T>{Fl + F.o, F.e + Fr};
     Gt = Ft;
     P = O;
     Pb = Ob;
     Pt = Onew;
     Pl = Ol;
     F = E;
-    Fb = p.be;
+    Fb = own(p.be);
     Fl = El;
     Et = Enew;
     O = Nx;
     Ot = Nt;
-    Ob = p.bo;
+    Ob = own(p.bo);
     Ol = Nl;
     Onr = Nr;
   };
-  for (int k0 = 0; k0 < steps; k0 += kDepth)
+  auto round = [&](int k0) {
 #pragma unroll
     for (int k = 0; k < kDepth; ++k) {
-      const Pair p = q[k];
+      step(q[k], m0 + k0 + k);
       q[k] = load(m0 + k0 + k + kDepth);
-      step(p, m0 + k0 + k);
+      __builtin_amdgcn_sched_barrier(0);  // no step starts before its turn (it would wait for its rows)
     }
+  };
+  // the first round apart: what the loop finds in flight is then the same on
+  // every way in, and it waits for no more than its own rows
+  round(0);
+  for (int k0 = kDepth; k0 < steps; k0 += kDepth) round(k0);
   if constexpr (NORM) {
     for (int o = 32; o > 0; o >>= 1) {
       mx = nanmax2(mx, __shfl_xor(mx, o));
@@ -234,6 +327,90 @@ __global__ __launch_bounds__(256) void k_stream(StreamArgs a) {
       a.part[2 * wi + 1] = sm;
     }
   }
+}
+
+template <class T, bool ZERO, bool NORM>
+__global__ __launch_bounds__(256) void k_stream(StreamArgs<T> a) {
+  const int wi = __builtin_amdgcn_readfirstlane(window_of_wave(a.nwin));
+  if (wi >= a.nwin) return;  // whole waves; no barriers below
+  const int4 W = a.win[wi];
+  if (W.w) stream_window<T, ZERO, NORM, true>(a, wi, W);
+  else stream_window<T, ZERO, NORM, false>(a, wi, W);
+}
+
+// x + P x_c, then one sweep (odd row 2m - 1 once the even row 2m is new)
+template <class T>
+__global__ __launch_bounds__(256) void k_stream_up(StreamArgs<T> a) {
+  const int wi = __builtin_amdgcn_readfirstlane(window_of_wave(a.nwin));
+  if (wi >= a.nwin) return;
+  const int4 W = a.win[wi];
+  const int X = W.x, Y = W.y, width = W.z & 0xffff, H = W.z >> 16, lane = threadIdx.x & 63;
+  const int col = X - kUpX + 2 * lane;
+  const bool core = lane >= kUpX / 2 && lane < (kUpX + width) / 2;
+  const int lc = min(col, a.N - 1), lcc = min(col, a.N) >> 1, Nc = a.N >> 1;
+  const int m0 = Y / 2 - kUpY / 2, steps = H / 2 + kUpY, last = Y + H + kUpY - 1;
+  const unsigned rb = (unsigned)(a.s * sizeof(T));
+  const unsigned at = core ? (unsigned)(col * (int)sizeof(T)) : 0x80000000u;
+  const Out out(a.out + (int64_t)Y * a.s, (unsigned)H * rb);
+  struct Rows {
+    Pair<T> p;
+    T c;  // coarse row m + 1
+  };
+  auto load = [&](int m) {
+    Rows u;
+    const int64_t r0 = (int64_t)min(2 * m, last) * a.s + lc, r1 = (int64_t)min(2 * m + 1, last) * a.s + lc;
+    u.p.xe = load_row(a.x + r0);
+    u.p.xo = load_row(a.x + r1);
+    u.c = a.xc[lcc + (int64_t)min(m + 1, Nc) * a.sc];
+    u.p.be = load_row(a.b + r0);
+    u.p.bo = load_row(a.b + r1);
+    return u;
+  };
+  T C = a.xc[lcc + (int64_t)m0 * a.sc];
+  Rows q[kDepth];
+#pragma unroll
+  for (int k = 0; k < kDepth; ++k) {
+    q[k] = load(m0 + k);
+    __builtin_amdgcn_sched_barrier(0);  // oldest first
+  }
+  const Row<T> z{T(0), T(0)};
+  T Cr = lane_right(C), Ol = T(0);
+  Row<T> O = z, Ot = z, Ob = z, Et = z;
+  auto step = [&](const Rows& u, int m) {
+    use(u.p.xe.e);
+    // even columns have one coarse parent in x, odd ones two; rows in y likewise
+    const T D = own(u.c), Dr = lane_right(D);
+    Row<T> E, Nx;
+    E.e = fma_t(T(0.25), (C + C) + (C + C), u.p.xe.e);
+    E.o = fma_t(T(0.25), (C + Cr) + (C + Cr), u.p.xe.o);
+    Nx.e = fma_t(T(0.25), (C + C) + (D + D), u.p.xo.e);
+    Nx.o = fma_t(T(0.25), (C + Cr) + (D + Dr), u.p.xo.o);
+    C = D;
+    Cr = Dr;
+    const T Nl = lane_left(Nx.o), Nr = lane_right(Nx.e);
+    const Row<T> Nt = sum3(Nx, Nl, Nr);
+    T El = lane_left(E.o), Er, Or;
+    const Row<T> Enew = sweep_row(E, u.p.be, Ot, Nt, El, Er);
+    sweep_row(O, Ob, Et, Enew, Ol, Or);
+    const unsigned rel = (unsigned)(2 * m - Y);
+    out.put(at + rel * rb, E);
+    out.put(at + (rel - 1) * rb, O);
+    Et = Enew;
+    O = Nx;
+    Ot = Nt;
+    Ob = own(u.p.bo);
+    Ol = Nl;
+  };
+  auto round = [&](int k0) {
+#pragma unroll
+    for (int k = 0; k < kDepth; ++k) {
+      step(q[k], m0 + k0 + k);
+      q[k] = load(m0 + k0 + k + kDepth);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  round(0);  // apart, as in the downward pass
+  for (int k0 = kDepth; k0 < steps; k0 += kDepth) round(k0);
 }
 
 // tiles of a list whose core and halo hold only active nodes with the interior
@@ -272,35 +449,133 @@ __global__ __launch_bounds__(256) void k_coarse_band(const int* __restrict__ til
 
 }  // namespace
 
-void stream_pass(mgfem_ctx* c, int l, int in, int mid, int out, double* part) {
-  Level& L = c->lv[l];
-  StreamArgs a{};
-  a.x = L.zero ? nullptr : L.X[in];
-  a.b = L.b;
-  a.out1 = L.X[mid];
-  a.out = L.X[out];
-  a.bc = c->lv[l + 1].b;
+namespace {
+template <class T>
+struct Of;
+template <>
+struct Of<double> {
+  static double* X(const Level& L, int w) { return L.X[w]; }
+  static double* B(const Level& L) { return L.b; }
+};
+template <>
+struct Of<float> {
+  static float* X(const Level& L, int w) { return L.X32[w]; }
+  static float* B(const Level& L) { return L.b32; }
+};
+template <class T>
+StreamArgs<T> stream_args(mgfem_ctx* c, int l, int in, int out, const int4* win, int nwin) {
+  const Level& L = c->lv[l];
+  StreamArgs<T> a{};
+  a.x = Of<T>::X(L, in);
+  a.b = Of<T>::B(L);
+  a.out = Of<T>::X(L, out);
   a.N = L.N;
   a.s = L.stride;
   a.sc = c->lv[l + 1].stride;
-  a.win = L.sp.win;
-  a.nwin = L.sp.nwin;
+  a.win = win;
+  a.nwin = nwin;
+  return a;
+}
+inline dim3 stream_grid(int nwin) { return dim3(8u * (unsigned)((((nwin + 3) / 4) + 7) / 8)); }
+template <class T>
+void launch_down(mgfem_ctx* c, int l, int in, int mid, int out, double* part) {
+  const Level& L = c->lv[l];
+  StreamArgs<T> a = stream_args<T>(c, l, in, out, L.sp.win, L.sp.nwin);
+  a.out1 = Of<T>::X(L, mid);
+  a.bc = Of<T>::B(c->lv[l + 1]);
   a.part = part;
-  const dim3 g(8u * (unsigned)((((a.nwin + 3) / 4) + 7) / 8)), bs(256);
-  if (L.zero && part) hipLaunchKernelGGL((k_stream<true, true>), g, bs, 0, c->s, a);
-  else if (L.zero) hipLaunchKernelGGL((k_stream<true, false>), g, bs, 0, c->s, a);
-  else if (part) hipLaunchKernelGGL((k_stream<false, true>), g, bs, 0, c->s, a);
-  else hipLaunchKernelGGL((k_stream<false, false>), g, bs, 0, c->s, a);
+  const dim3 g = stream_grid(a.nwin), bs(256);
+  if (L.zero && part) hipLaunchKernelGGL((k_stream<T, true, true>), g, bs, 0, c->s, a);
+  else if (L.zero) hipLaunchKernelGGL((k_stream<T, true, false>), g, bs, 0, c->s, a);
+  else if (part) hipLaunchKernelGGL((k_stream<T, false, true>), g, bs, 0, c->s, a);
+  else hipLaunchKernelGGL((k_stream<T, false, false>), g, bs, 0, c->s, a);
+}
+template <class T>
+void launch_up(mgfem_ctx* c, int l, int in, int out) {
+  const Level& L = c->lv[l];
+  const Level& C = c->lv[l + 1];
+  StreamArgs<T> a = stream_args<T>(c, l, in, out, L.sp.up, L.sp.nup);
+  a.xc = Of<T>::X(C, C.cur);
+  hipLaunchKernelGGL(k_stream_up<T>, stream_grid(a.nwin), dim3(256), 0, c->s, a);
+}
+}  // namespace
+
+void stream_down_windows(mgfem_ctx* c, int l, bool fp32, int in, int mid, int out, double* part) {
+  if (fp32) launch_down<float>(c, l, in, mid, out, part);
+  else launch_down<double>(c, l, in, mid, out, part);
+}
+void stream_up_windows(mgfem_ctx* c, int l, bool fp32, int in, int out) {
+  if (fp32) launch_up<float>(c, l, in, out);
+  else launch_up<double>(c, l, in, out);
 }
 
-// Levels that stream: float64 forward cycles with two sweeps down, N >= 4096
-// (the same three launches of a smaller level take 34 us at N = 2048).
-constexpr int kStreamN = 4096;
+// Levels that stream: forward cycles with two sweeps down, N >= 4096, and in
+// float64 the coarser levels with N >= 2048, whose start iterate is zero and
+// is not read.  The upward pass from N >= 4096.  Speed of solves against one
+// fixed earlier program, with separate kernels | downward pass | both:
+//   flower, float64, N = 4096     1.12 | 1.19 | 1.19, with the 2048 level 1.22
+//   ellipse, mixed, N = 4096      1.06 | 1.08 | 1.09, with the 2048 level 1.07
+//   gradient, float64, N = 2048   1.18 to 1.20, if level 0 streams 1.15 to 1.17
+//   annulus, float64, N = 1536    1.20, if level 0 streams 1.20
+constexpr int kStreamN = 4096, kStreamCoarseN = 2048, kUpN = 4096;
 bool stream_candidate(const mgfem_ctx* c, int l) {
   const Level& L = c->lv[l];
-  return c->p.precision != MGFEM_PREC_MIXED && c->p.nu1 == 2 && L.N >= kStreamN && !L.empty() &&
-         l + 1 < (int)c->lv.size() && !c->lv[l + 1].empty();
+  const int n = l > 0 && c->p.precision != MGFEM_PREC_MIXED ? kStreamCoarseN : kStreamN;
+  return c->p.nu1 == 2 && c->p.nu2 >= 1 && L.N >= n && !L.empty() && l + 1 < (int)c->lv.size() &&
+         !c->lv[l + 1].empty();
 }
+
+namespace {
+// Windows of at most `core` columns over the inner tiles of a tile grid: runs
+// of them, several tile rows high where they all are (fewer rows computed
+// twice) as long as that gives every SIMD a few waves, half a tile row high
+// where even one gives too few (a wave's row pairs are one serial chain).
+std::vector<int4> build_windows(const std::vector<uint8_t>& map, const std::vector<uint8_t>& list, int ntx, int nty,
+                                int x0, int y0, int TW, int TH, int core) {
+  std::vector<int4> win;
+  for (int rows = 128 / TH; rows >= 1; rows /= 2) {
+    std::vector<uint8_t> left = map;
+    win.clear();
+    for (int g = rows; g >= 1; g /= 2)
+      for (int y = 0; y + g <= nty; y += g)
+        for (int x = 0; x < ntx;) {
+          auto good = [&](int tx) {
+            bool on = tx < ntx;
+            for (int v = 0; on && v < g; ++v) on = left[tx + (size_t)(y + v) * ntx] != 0;
+            return on;
+          };
+          int e = x;
+          for (; good(e); ++e)
+            for (int v = 0; v < g; ++v) left[e + (size_t)(y + v) * ntx] = 0;
+          if (e == x) {
+            ++x;
+            continue;
+          }
+          const int cols = (e - x) * TW, n = (cols + core - 1) / core, w = (cols / 2 + n - 1) / n * 2;
+          for (int at = 0; at < cols; at += w) {
+            const int width = std::min(w, cols - at);
+            bool touch = false;  // a listed tile around the window is not inner
+            for (int ty = std::max(0, y - 1); ty <= std::min(nty - 1, y + g); ++ty)
+              for (int tx = std::max(0, x + at / TW - 1); tx <= std::min(ntx - 1, x + (at + width - 1) / TW + 1); ++tx)
+                touch = touch || (list[tx + (size_t)ty * ntx] && !map[tx + (size_t)ty * ntx]);
+            win.push_back(make_int4(x0 + x * TW + at, y0 + y * TH, width | g * TH << 16, touch));
+          }
+          x = e;
+        }
+    if (win.size() >= 3072) return win;
+  }
+  if (win.size() < 1536)
+    for (size_t q = 0, n = win.size(); q < n; ++q) {
+      int4 w = win[q];
+      const int h = w.z >> 17;
+      win[q].z = (w.z & 0xffff) | h << 16;
+      w.y += h;
+      w.z = win[q].z;
+      win.push_back(w);
+    }
+  return win;
+}
+}  // namespace
 
 // Windows and band of a level whose tile lists exist.  No window, or no memory
 // for the third buffer: the level keeps the separate kernels.
@@ -334,40 +609,8 @@ int build_stream(mgfem_ctx* c, int l) {
     map[tiles[q]] = inner[q] != 0;
     list[tiles[q]] = 1;
   }
-  // windows: runs of inner tiles, several tile rows high where they all are
-  // (fewer rows computed twice), as long as they give every SIMD a few waves
-  std::vector<int4> win;
-  for (int rows = 128 / TH; rows >= 1; rows /= 2) {
-    std::vector<uint8_t> left = map;
-    win.clear();
-    for (int g = rows; g >= 1; g /= 2)
-      for (int y = 0; y + g <= nty; y += g)
-        for (int x = 0; x < ntx;) {
-          auto good = [&](int tx) {
-            bool on = tx < ntx;
-            for (int v = 0; on && v < g; ++v) on = left[tx + (size_t)(y + v) * ntx] != 0;
-            return on;
-          };
-          int e = x;
-          for (; good(e); ++e)
-            for (int v = 0; v < g; ++v) left[e + (size_t)(y + v) * ntx] = 0;
-          if (e == x) {
-            ++x;
-            continue;
-          }
-          const int cols = (e - x) * TW, n = (cols + kCore - 1) / kCore, w = (cols / 2 + n - 1) / n * 2;
-          for (int at = 0; at < cols; at += w) {
-            const int width = std::min(w, cols - at);
-            bool touch = false;  // a listed tile around the window is not inner
-            for (int ty = std::max(0, y - 1); ty <= std::min(nty - 1, y + g); ++ty)
-              for (int tx = std::max(0, x + at / TW - 1); tx <= std::min(ntx - 1, x + (at + width - 1) / TW + 1); ++tx)
-                touch = touch || (list[tx + (size_t)ty * ntx] && !map[tx + (size_t)ty * ntx]);
-            win.push_back(make_int4(L.bbox[0] + x * TW + at, L.bbox[2] + y * TH, width | g * TH << 16, touch));
-          }
-          x = e;
-        }
-    if (win.size() >= 3072) break;
-  }
+  const std::vector<int4> win = build_windows(map, list, ntx, nty, L.bbox[0], L.bbox[2], TW, TH, kCore);
+  const std::vector<int4> up = build_windows(map, list, ntx, nty, L.bbox[0], L.bbox[2], TW, TH, kUpCore);
   if (win.empty()) return MGFEM_OK;
   std::vector<int> meta(8 * (size_t)L.ntiles), band;
   MGFEM_HIP_TRY(hipMemcpyAsync(meta.data(), L.tmeta, meta.size() * sizeof(int), hipMemcpyDeviceToHost, c->s));
@@ -386,14 +629,17 @@ int build_stream(mgfem_ctx* c, int l) {
     if (!inner[q]) band.insert(band.end(), meta.begin() + 8 * (size_t)q, meta.begin() + 8 * (size_t)(q + 1));
   for (int q = 0; q < L.rr_ntiles; ++q)
     if (rr_keep[q]) rr_band.push_back(rr[q]);
-  if (l == 0) {
-    L.X[2] = c->lam;
-  } else if (ctx_alloc_t(c, &L.X[2], L.n) != hipSuccess) {
+  hipError_t e = hipSuccess;
+  if (c->p.precision == MGFEM_PREC_MIXED) e = ctx_alloc_t(c, &L.X32[2], L.n);
+  else if (l == 0) L.X[2] = c->lam;
+  else e = ctx_alloc_t(c, &L.X[2], L.n);
+  if (e != hipSuccess) {
     (void)hipGetLastError();
-    L.X[2] = nullptr;
     return MGFEM_OK;
   }
   MGFEM_HIP_TRY(ctx_alloc_t(c, &S.win, win.size()));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &S.up, up.size()));
+  MGFEM_HIP_TRY(hipMemcpyAsync(S.up, up.data(), up.size() * sizeof(int4), hipMemcpyHostToDevice, c->s));
   MGFEM_HIP_TRY(ctx_alloc_t(c, &S.band, std::max<size_t>(8, band.size())));
   MGFEM_HIP_TRY(ctx_alloc_t(c, &S.rr_band, std::max<size_t>(1, rr_band.size())));
   MGFEM_HIP_TRY(hipMemcpyAsync(S.win, win.data(), win.size() * sizeof(int4), hipMemcpyHostToDevice, c->s));
@@ -401,6 +647,7 @@ int build_stream(mgfem_ctx* c, int l) {
   MGFEM_HIP_TRY(hipMemcpyAsync(S.rr_band, rr_band.data(), rr_band.size() * sizeof(int), hipMemcpyHostToDevice, c->s));
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
   S.nwin = (int)win.size();
+  S.nup = L.N >= kUpN ? (int)up.size() : 0;
   S.nband = (int)band.size() / 8;
   S.nrr = (int)rr_band.size();
   S.ok = true;

@@ -1,7 +1,7 @@
-"""The one-pass downward half of the largest float64 levels (two sweeps,
-residual and restriction over windows away from the boundary, the separate
-kernels on the band along it) against the separate kernels everywhere, which a
-profiled solve runs."""
+"""The streaming passes of the largest levels (downwards two sweeps, residual and
+restriction, upwards prolongation and a sweep, over windows away from the
+boundary; the separate kernels on the band along it) against the separate
+kernels everywhere, which a profiled solve runs."""
 import numpy as np
 import pytest
 
@@ -12,23 +12,34 @@ torch = pytest.importorskip("torch")
 
 
 # one and two levels that stream (32- and 16-row tiles), a bounding box from an
-# odd column, domains that reach the sides of the grid, no cut sweeps, a warm
-# start, a small domain (few windows)
-@pytest.mark.parametrize("N,coarsest,psi,kw", [
+# odd column, domains that reach the sides of the grid, no cut sweeps, more
+# sweeps up, a small domain (few windows)
+CASES = [
     (4096, 4, lambda N: W.flower(N), {}),
     (4096, 4, lambda N: W.ellipse(N, center=(0.0517, -0.0321)), {"cycle": 2}),
     (4608, 9, lambda N: W.circle(N, radius=1.1, center=(0.1, 0.0)), {"nu2": 2, "eta": 0}),
     (4096, 8, lambda N: W.circle(N, radius=0.12, center=(0.2, 0.1)), {}),
+    (1536, 3, lambda N: W.circle(N, radius=0.9), {}),
+    (2048, 4, lambda N: W.flower(N), {"cycle": 3, "coarse_cycles": 2}),
     (8192, 4, lambda N: W.flower(N), {"eta": 1}),
-])
-def test_streamed_iterates(N, coarsest, psi, kw):
-    """Iterates to 1e-10 of their largest entry on random data."""
+]
+
+
+def _setup(N, coarsest, psi, **kw):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2505_05105_amd as mg
     gen = torch.Generator(device="cuda:0").manual_seed(N)
-    f, g, u0 = (2 * torch.rand((N + 1) ** 2, generator=gen, device="cuda:0", dtype=torch.float64) - 1 for _ in range(3))
-    s = mg.Solver(psi(N), N, coarsest_n=coarsest, **kw)
+    data = [2 * torch.rand((N + 1) ** 2, generator=gen, device="cuda:0", dtype=torch.float64) - 1 for _ in range(3)]
+    if kw.pop("mixed", False):
+        kw["precision"] = mg.PREC_MIXED
+    return mg.Solver(psi(N), N, coarsest_n=coarsest, **kw), data
+
+
+@pytest.mark.parametrize("N,coarsest,psi,kw", CASES)
+def test_streamed_iterates(N, coarsest, psi, kw):
+    """float64 iterates to 1e-10 of their largest entry on random data."""
+    s, (f, g, u0) = _setup(N, coarsest, psi, **kw)
 
     def close(a, b, ha, hb):
         assert float((a - b).abs().max()) <= 1e-10 * float(b.abs().max())
@@ -45,3 +56,14 @@ def test_streamed_iterates(N, coarsest, psi, kw):
     # the same bits again, and stopped by the tolerance instead
     u2, h2 = s.solve(f, g, tol=h[3] / h[0] * (1 + 1e-9), max_cycles=50)
     assert np.array_equal(h, h2) and torch.equal(u, u2)
+
+
+@pytest.mark.parametrize("N,coarsest,psi,kw", CASES)
+def test_streamed_float_cycles_keep_their_bits(N, coarsest, psi, kw):
+    """float32 cycles do not depend on which kernel computed a node."""
+    s, (f, g, _) = _setup(N, coarsest, psi, mixed=True, **kw)
+    u, h = s.solve(f, g, tol=-1.0, max_cycles=3)
+    s.profile(True)
+    us, hs = s.solve(f, g, tol=-1.0, max_cycles=3)
+    s.profile(False)
+    assert np.array_equal(h, hs) and torch.equal(u, us)
