@@ -43,7 +43,10 @@ constexpr int kMX = 256, kMY = 8, kMW = kMX + 2, kMH = kMY + 2, kMN = kMW * kMH;
 // interior Q1 mass stencil h^2/36 [1 4 1; 4 16 4; 1 4 1] elsewhere.  Bound by
 // its bytes: u, u_t and a flag per node of the box, dJ/du on the whole grid;
 // every load of a block is issued before the first is used (none under a
-// branch: a node off the grid loads a clamped one and drops it).
+// branch: a node off the grid loads a clamped one and drops it).  The stored
+// rows of a wave's nodes are listed first and then taken one per lane, with
+// all nine coefficients in flight: row by row, each node with its nine loads
+// behind branches, N = 2048 took 30 us, like this 17.
 __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict__ u, const double* __restrict__ ut,
                                                         const uint8_t* __restrict__ fl, const int* __restrict__ cutpos,
                                                         const double* __restrict__ cut_rows,
@@ -54,7 +57,8 @@ __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict
   __shared__ double se[NU * 256];
   __shared__ uint8_t sf[NU * 256];
   __shared__ double wsum[4];
-  const int s = N + 1;
+  __shared__ uint16_t list[4][64 * kMY];  // a wave's stored nodes, by row, as indices of se
+  const int s = N + 1, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t n = (int64_t)s * s;
   const int bi = blockIdx.x * kMX, bj = blockIdx.y * kMY;
   const bool touches = bi <= i1 && bi + kMX - 1 >= i0 && bj <= j1 && bj + kMY - 1 >= j0;  // uniform
@@ -82,36 +86,52 @@ __global__ __launch_bounds__(256) void k_misfit_partial(const double* __restrict
   }
   double sm = 0.0;
   const int i = bi + threadIdx.x;
+  int nst = 0;
 #pragma unroll
   for (int rep = 0; rep < kMY; ++rep) {
     const int j = bj + rep;
-    if (i > N || j > N) continue;
-    const int64_t k = i + (int64_t)j * s;
+    const bool in = i <= N && j <= N;
     double me = 0.0;
+    bool stored = false;
     if (touches) {
       const int q = threadIdx.x + 1 + (rep + 1) * kMW;
-      const uint8_t fk = sf[q];
-      if (fk & kFlagActive) {
-        if (fk & kFlagStored) {
-          // zero coefficients are skipped, so that a value without a share in the row has none
-          const double* row = (fk & kFlagCut) ? cut_rows + 18 * (int64_t)cutpos[k] : M + k;
-          const int64_t st = (fk & kFlagCut) ? 1 : n;
-          for (int p = 0; p < 9; ++p) {
-            const double m = row[p * st];
-            if (m != 0.0) me += m * se[q + (p % 3 - 1) + (p / 3 - 1) * kMW];
-          }
-        } else {
-          const double corners = (se[q - kMW - 1] + se[q - kMW + 1]) + (se[q + kMW - 1] + se[q + kMW + 1]);
-          const double edges = (se[q - kMW] + se[q + kMW]) + (se[q - 1] + se[q + 1]);
-          me = hh36 * (16.0 * se[q] + 4.0 * edges + corners);
-        }
+      const uint8_t fk = sf[q];  // 0 off the grid
+      stored = (fk & kFlagActive) && (fk & kFlagStored);
+      const unsigned long long m = __ballot(stored);
+      if (stored) list[wave][nst + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)q;
+      nst += __popcll(m);
+      if ((fk & kFlagActive) && !stored) {
+        const double corners = (se[q - kMW - 1] + se[q - kMW + 1]) + (se[q + kMW - 1] + se[q + kMW + 1]);
+        const double edges = (se[q - kMW] + se[q + kMW]) + (se[q - 1] + se[q + 1]);
+        me = hh36 * (16.0 * se[q] + 4.0 * edges + corners);
         sm += se[q] * me;
       }
     }
+    if (y && in && !stored) y[i + (int64_t)j * s] = me;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's own list
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int e = lane; e < nst; e += 64) {
+    const int q = list[wave][e];
+    const int64_t k = bi - 1 + q % kMW + (int64_t)(bj - 1 + q / kMW) * s;
+    const bool cut = (sf[q] & kFlagCut) != 0;
+    const double* row = cut ? cut_rows + 18 * (int64_t)cutpos[k] : M + k;
+    const int64_t st = cut ? 1 : n;
+    double m[9], me = 0.0;
+#pragma unroll
+    for (int p = 0; p < 9; ++p) m[p] = row[p * st];
+    // zero coefficients are skipped, so that a value without a share in the row has none
+#pragma unroll
+    for (int p = 0; p < 9; ++p) {
+      const double v = se[q + (p % 3 - 1) + (p / 3 - 1) * kMW];
+      me += m[p] != 0.0 ? m[p] * v : 0.0;
+    }
+    sm += se[q] * me;
     if (y) y[k] = me;
   }
   for (int o = 32; o > 0; o >>= 1) sm += __shfl_xor(sm, o);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = sm;
+  if (lane == 0) wsum[wave] = sm;
   __syncthreads();
   if (threadIdx.x == 0) {
     const int b = blockIdx.x + blockIdx.y * gridDim.x;
