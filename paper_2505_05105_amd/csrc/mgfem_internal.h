@@ -57,7 +57,21 @@ struct CutPlan {
   double* cl_coef = nullptr;  // 9 per closure node: 8 off-diagonals, 1/diagonal
   float* cl_coef32 = nullptr;
   int max_cl = 0, max_ext = 0;
-  int lds64 = 0, lds32 = 0;   // dynamic LDS of the largest group
+  int lds64 = 0, lds32 = 0;   // dynamic LDS of a workgroup
+  int units = 0;              // workgroups
+  // The same with one wave per group, four groups per workgroup, where no group
+  // has more than kLanes closure nodes of one colour: kSlots slots per group,
+  // kLanes of each colour, one per lane; unused ones hold node -1.  The other
+  // arrays above are null then.
+  static constexpr int kLanes = 64, kSlots = 4 * kLanes, kExt = 256, kWaves = 4;
+  static constexpr int kVals = kSlots + kExt + 8;  // values of a group in LDS: slots, external ones, a zero
+  bool wave = false;
+  int* w_node = nullptr;
+  int* w_q = nullptr;        // position in the level's cut list | not owned << 31
+  uint4* w_nbr = nullptr;    // eight 16-bit indices into the group's values
+  int* w_ext = nullptr;      // kExt per group, as ext_src (unused: any valid source)
+  double* w_coef = nullptr;  // 9 planes per group, as cl_coef
+  float* w_coef32 = nullptr;
 };
 
 // LDS layout of one cut group: values (closure, external, one zero slot),

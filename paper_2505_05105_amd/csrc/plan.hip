@@ -5,8 +5,10 @@
 //    applies 4 eta colour phases to the cut vertices; a value after them
 //    depends on values at most 4 eta nodes away, so a group owning the cut
 //    vertices of one tile and holding every cut vertex within 4 eta of that
-//    tile (its closure) computes its own vertices exactly, alone.  Tiles
-//    whose closure does not fit in LDS are split in four.
+//    tile (its closure) computes its own vertices exactly, alone.  A group is
+//    one wave with a node of each colour per lane; a tile whose closure has more
+//    is split in four.  Levels where that does not help (and eta > 4) take
+//    groups of four waves, split until their closure fits in LDS.
 //  * The single-workgroup part: the coarsest levels whose arrays (iterate,
 //    right-hand side, residual on the bounding box grown by one ring, the
 //    stored stencil rows and the cut lists) fit in one workgroup's LDS.
@@ -48,7 +50,25 @@ __global__ void k_fill_i(int* __restrict__ p, int64_t n, int v) {
   if (k < n) p[k] = v;
 }
 
+// the same in planes over the slots of each group of one wave
+__global__ void k_gather_slots(const double* __restrict__ A, int64_t n, const int* __restrict__ node, int cnt,
+                               double* __restrict__ out, float* __restrict__ out32) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= cnt || node[t] < 0) return;
+  const int64_t k = node[t];
+  const int pl[9] = {0, 1, 2, 3, 5, 6, 7, 8, 4};
+  for (int e = 0; e < 9; ++e) {
+    const int64_t w = ((int64_t)(t / CutPlan::kSlots) * 9 + e) * CutPlan::kSlots + t % CutPlan::kSlots;
+    const double v = A[pl[e] * n + k];
+    out[w] = e < 8 ? v : 1.0 / v;
+    if (out32) out32[w] = e < 8 ? (float)v : 1.0f / (float)v;
+  }
+}
+
 struct GroupBuild {
+  // groups of one wave: slots, the eight neighbours of each, external sources
+  std::vector<int> w_node, w_q, w_ext;
+  std::vector<uint16_t> w_nbr;
   std::vector<int> info, node, q, ext;
   std::vector<uint8_t> own;
   std::vector<int16_t> nbr;
@@ -60,8 +80,9 @@ struct GroupBuild {
 // in the closure, index of the external value.
 struct GroupLevel {
   const std::vector<int>& nodes;
-  int N, D;
+  int N, DX, DY;  // the closure's reach in columns and rows
   size_t lds_cap;
+  bool wave;      // one wave per group
   static constexpr int BT = 16;
   int nbx;
   std::vector<std::vector<int>> buckets;
@@ -72,10 +93,10 @@ struct GroupLevel {
 bool build_groups(GroupLevel& G, int x0, int x1, int y0, int y1, const std::vector<int>& owned_q, GroupBuild& gb) {
   if (owned_q.empty()) return true;
   const std::vector<int>& nodes = G.nodes;
-  const int N = G.N, D = G.D, s = N + 1, BT = GroupLevel::BT;
-  // closure: cut vertices in the rectangle grown by D; the ring around it
+  const int N = G.N, DX = G.DX, DY = G.DY, s = N + 1, BT = GroupLevel::BT;
+  // closure: cut vertices in the rectangle grown by its reach; the ring around it
   // holds cut vertices whose values are read from the snapshot
-  const int bx = x0 - D - 1, by = y0 - D - 1, W = x1 - x0 + 2 * D + 2, H = y1 - y0 + 2 * D + 2;
+  const int bx = x0 - DX - 1, by = y0 - DY - 1, W = x1 - x0 + 2 * DX + 2, H = y1 - y0 + 2 * DY + 2;
   G.gq.assign((size_t)W * H, -1);
   G.gslot.assign((size_t)W * H, -1);
   G.gext.assign((size_t)W * H, -1);
@@ -117,7 +138,19 @@ bool build_groups(GroupLevel& G, int x0, int x1, int y0, int y1, const std::vect
     }
   }
   const size_t bytes = (size_t)cut_lds_layout((int)cl.size(), (int)ext.size(), (int)sizeof(double)).total;
-  if (bytes > G.lds_cap || cl.size() + ext.size() > 32000) {
+  // colour offsets
+  int col_off[5] = {0, 0, 0, 0, 0}, col_max = 0;
+  for (size_t t = 0; t < cl.size(); ++t) {
+    const int k = nodes[cl[t]];
+    ++col_off[1 + (k % s & 1) + 2 * (k / s & 1)];
+  }
+  for (int cc = 1; cc < 5; ++cc) {
+    col_max = std::max(col_max, col_off[cc]);
+    col_off[cc] += col_off[cc - 1];
+  }
+  const bool fits = G.wave ? col_max <= CutPlan::kLanes && ext.size() <= (size_t)CutPlan::kExt
+                           : bytes <= G.lds_cap && cl.size() + ext.size() <= 32000;
+  if (!fits) {
     if (x1 - x0 <= 4 && y1 - y0 <= 4) return false;
     const int xm = (x0 + x1) / 2, ym = (y0 + y1) / 2;
     const int rx[4][2] = {{x0, xm}, {xm, x1}, {x0, xm}, {xm, x1}};
@@ -132,13 +165,30 @@ bool build_groups(GroupLevel& G, int x0, int x1, int y0, int y1, const std::vect
     }
     return true;
   }
-  // colour offsets and ownership
-  int col_off[5] = {0, 0, 0, 0, 0};
-  for (size_t t = 0; t < cl.size(); ++t) {
-    const int k = nodes[cl[t]];
-    ++col_off[1 + (k % s & 1) + 2 * (k / s & 1)];
+  if (G.wave) {
+    constexpr int NS = CutPlan::kSlots, NL = CutPlan::kLanes, NE = CutPlan::kExt;
+    const size_t base = gb.w_node.size(), eb = gb.w_ext.size();
+    gb.w_node.resize(base + NS, -1);
+    gb.w_q.resize(base + NS, 0);
+    gb.w_nbr.resize(8 * (base + NS), 0);
+    gb.w_ext.resize(eb + NE, nodes[cl[0]]);
+    std::vector<uint16_t> slot(cl.size());
+    for (int cc = 0; cc < 4; ++cc)
+      for (int t = col_off[cc]; t < col_off[cc + 1]; ++t) slot[t] = (uint16_t)(cc * NL + t - col_off[cc]);
+    for (size_t t = 0; t < cl.size(); ++t) {
+      const int k = nodes[cl[t]], i = k % s, j = k / s;
+      const bool own = i >= x0 && i < x1 && j >= y0 && j < y1;
+      gb.w_node[base + slot[t]] = k;
+      gb.w_q[base + slot[t]] = own ? cl[t] : (int)((unsigned)cl[t] | 0x80000000u);
+      for (int e = 0; e < 8; ++e) {
+        const int r = nbr[8 * t + e];  // neighbours outside the grid read the zero behind the external values
+        gb.w_nbr[8 * (base + slot[t]) + e] =
+            r < 0 ? (uint16_t)(NS + NE) : r < (int)cl.size() ? slot[r] : (uint16_t)(NS + r - (int)cl.size());
+      }
+    }
+    for (size_t e = 0; e < ext.size(); ++e) gb.w_ext[eb + e] = ext[e];
+    return true;
   }
-  for (int cc = 1; cc < 5; ++cc) col_off[cc] += col_off[cc - 1];
   const int base = (int)gb.node.size(), ebase = (int)gb.ext.size();
   gb.info.push_back(base);
   gb.info.push_back((int)cl.size());
@@ -218,7 +268,7 @@ int build_cut_groups(mgfem_ctx* c, int l) {
   MGFEM_HIP_TRY(hipMemcpyAsync(nodes.data(), L.cut_list, cnt * sizeof(int), hipMemcpyDeviceToHost, c->s));
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
   const int s = L.stride;
-  GroupLevel G{nodes, L.N, D, cap, (L.N + GroupLevel::BT) / GroupLevel::BT, {}, {}, {}, {}};
+  GroupLevel G{nodes, L.N, D, D, cap, false, (L.N + GroupLevel::BT) / GroupLevel::BT, {}, {}, {}, {}};
   G.buckets.resize((size_t)G.nbx * G.nbx);
   const int GT = 32;  // owned tile of one group
   const int ngx = (L.N + GT) / GT;
@@ -229,15 +279,47 @@ int build_cut_groups(mgfem_ctx* c, int l) {
     owned[i / GT + (size_t)(j / GT) * ngx].push_back(q);
   }
   GroupBuild gb;
-  bool ok = true;
-  for (int g = 0; g < ngx * ngx && ok; ++g) {
-    if (owned[g].empty()) continue;
-    const int x0 = (g % ngx) * GT, y0 = (g / ngx) * GT;
-    ok = build_groups(G, x0, x0 + GT, y0, y0 + GT, owned[g], gb);
+  auto build = [&] {
+    bool ok = true;
+    gb = GroupBuild();
+    for (int g = 0; g < ngx * ngx && ok; ++g) {
+      if (owned[g].empty()) continue;
+      const int x0 = (g % ngx) * GT, y0 = (g / ngx) * GT;
+      ok = build_groups(G, x0, x0 + GT, y0, y0 + GT, owned[g], gb);
+    }
+    return ok;
+  };
+  // groups of one wave where every one fits (a sweep's four phases reach four
+  // columns, but two rows: rows alternate between the even and the odd colours)
+  G.wave = true;
+  G.DY = D / 2;
+  if (c->p.eta <= 4 && build()) {
+    CutPlan& P = L.cp;
+    const int nslot = (int)gb.w_node.size();
+    P.ok = P.wave = true;
+    P.ngroups = nslot / CutPlan::kSlots;
+    P.units = (P.ngroups + CutPlan::kWaves - 1) / CutPlan::kWaves;
+    P.lds64 = CutPlan::kWaves * CutPlan::kVals * (int)sizeof(double);
+    P.lds32 = P.lds64 / 2;
+    int rc;
+    if ((rc = upload(c, &P.w_node, gb.w_node))) return rc;
+    if ((rc = upload(c, &P.w_q, gb.w_q))) return rc;
+    if ((rc = upload(c, &P.w_ext, gb.w_ext))) return rc;
+    MGFEM_HIP_TRY(ctx_alloc_t(c, &P.w_nbr, nslot));
+    MGFEM_HIP_TRY(hipMemcpyAsync(P.w_nbr, gb.w_nbr.data(), gb.w_nbr.size() * 2, hipMemcpyHostToDevice, c->s));
+    MGFEM_HIP_TRY(ctx_alloc_t(c, &P.w_coef, 9 * (size_t)nslot));
+    if (mixed) MGFEM_HIP_TRY(ctx_alloc_t(c, &P.w_coef32, 9 * (size_t)nslot));
+    hipLaunchKernelGGL(k_gather_slots, dim3((unsigned)((nslot + 255) / 256)), dim3(256), 0, c->s, L.A, L.n,
+                       (const int*)P.w_node, nslot, P.w_coef, P.w_coef32);
+    MGFEM_HIP_TRY(hipGetLastError());
+    MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
+    return MGFEM_OK;
   }
-  L.cp.ok = ok;
-  if (!ok) return MGFEM_OK;
-  L.cp.ngroups = (int)gb.info.size() / 9;
+  G.wave = false;
+  G.DY = D;
+  L.cp.ok = build();
+  if (!L.cp.ok) return MGFEM_OK;
+  L.cp.ngroups = L.cp.units = (int)gb.info.size() / 9;
   L.cp.max_cl = gb.max_cl;
   L.cp.max_ext = gb.max_ext;
   L.cp.lds64 = gb.lds64;
