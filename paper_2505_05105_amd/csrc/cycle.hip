@@ -793,9 +793,12 @@ __global__ __launch_bounds__(256) void k_team_export(const TeamL0* __restrict__ 
   e.u_out[k] = in ? e.U[e.ucur][k] : 0.0;
 }
 
-// one workgroup per listed problem: its box partials in block order
+// one workgroup per listed problem: its box partials in block order, into the
+// problem's record of pinned host memory (max, sum of squares, number of the
+// reduction, which goes last)
 __global__ __launch_bounds__(256) void k_team_reduce(const TeamL0* __restrict__ tab, const int* __restrict__ probs,
-                                                     double* __restrict__ out) {
+                                                     double* rec, double seq) {
+  __shared__ double out[2];
   const int p = probs[blockIdx.x];
   const TeamL0& e = tab[p];
   double mx = 0.0, sm = 0.0;
@@ -803,7 +806,14 @@ __global__ __launch_bounds__(256) void k_team_reduce(const TeamL0* __restrict__ 
     mx = nanmax(mx, e.part[2 * q]);
     sm += e.part[2 * q + 1];
   }
-  block_pair_to(mx, sm, out + 2 * p);
+  block_pair_to(mx, sm, out);
+  if (threadIdx.x == 0) {
+    rec[4 * p] = out[0];
+    rec[4 * p + 1] = out[1];
+    __threadfence_system();
+    rec[4 * p + 2] = seq;
+    __threadfence_system();
+  }
 }
 
 }  // namespace
@@ -864,8 +874,8 @@ void team_l0_launch(hipStream_t s, int kind, const TeamL0* tab, const int2* work
   }
 }
 
-void team_reduce(hipStream_t s, const TeamL0* tab, const int* probs, int nprobs, double* out) {
-  if (nprobs > 0) hipLaunchKernelGGL(k_team_reduce, dim3(nprobs), dim3(256), 0, s, tab, probs, out);
+void team_reduce(hipStream_t s, const TeamL0* tab, const int* probs, int nprobs, double* rec, double seq) {
+  if (nprobs > 0) hipLaunchKernelGGL(k_team_reduce, dim3(nprobs), dim3(256), 0, s, tab, probs, rec, seq);
 }
 
 void launch_box_copy(mgfem_ctx* c, double* dst, const double* src) {

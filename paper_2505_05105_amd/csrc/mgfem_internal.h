@@ -326,11 +326,11 @@ void team_launch(hipStream_t s, int kind, const void* tab, const int2* work, int
                  int prolong, int lds);
 // level 0 (cycle.hip): a member's entry (data pointers left null), the units
 // of a level-0 launch kind, one launch, and the per-problem reduction of the
-// box partials into out[2 p], out[2 p + 1] (max, sum of squares)
+// box partials into rec[4 p ... 4 p + 2] (max, sum of squares, seq) of pinned host memory
 void team_l0_entry(mgfem_ctx* m, TeamL0* out);
 int team_l0_units(const TeamL0& e, int kind);
 void team_l0_launch(hipStream_t s, int kind, const TeamL0* tab, const int2* work, int nwork, int upar, int epar);
-void team_reduce(hipStream_t s, const TeamL0* tab, const int* probs, int nprobs, double* out);
+void team_reduce(hipStream_t s, const TeamL0* tab, const int* probs, int nprobs, double* rec, double seq);
 // the tiled path of a batched handle (team.hip): tables after the members'
 // set-up, one solve (history count x (max_cycles + 1), cycles per problem,
 // device time of the solve), release

@@ -17,6 +17,7 @@
 // all; a problem whose coarse part starts at level d + 1 reads that level's
 // iterate from buffer 0, where its coarse map writes it.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -36,10 +37,13 @@ struct TeamPlan {
   std::vector<TeamL0> l0h;           // level-0 entries (host copy)
   TeamL0* l0 = nullptr;              // device copy
   int2* work = nullptr;              // device work lists of the current active set
-  size_t work_cap = 0;
-  int* probs = nullptr;              // device: the active problems (reductions)
-  double* red = nullptr;             // device: (max, sum of squares) per problem
-  double* red_host = nullptr;        // pinned copy
+  std::vector<int> units;            // items per segment and problem (float-cycle kinds by level, level-0 kinds)
+  int* units_dev = nullptr;
+  int* first = nullptr;              // device: list positions per segment and problem, then the active problems
+  int* stage = nullptr;              // pinned: the same, and below
+  TeamL0* l0_stage = nullptr;
+  double* rec = nullptr;             // pinned: two records of 4 doubles per problem (max, sum of squares, number)
+  double seq = 0.0;                  // the last reduction's number
   // segments of the work buffer: float-cycle kinds [kind][level], level-0 kinds
   std::vector<int> seg_off, seg_cnt;
   int l0_off[5] = {0, 0, 0, 0, 0}, l0_cnt[5] = {0, 0, 0, 0, 0};
@@ -51,47 +55,45 @@ namespace {
 int seg(const TeamPlan& T, int kind, int d) { return kind * T.depth + d; }
 bool fused_kind(const TeamPlan& T, int kind) { return T.fused && (kind == kTeamSweep || kind == kTeamRR); }
 
-// work lists of the active problems (all float-cycle and level-0 kinds)
+// One workgroup per (segment, problem): the problem's items of that work list.
+// first: per segment and problem the list position of its first item, or -1
+__global__ __launch_bounds__(256) void k_team_lists(const int* __restrict__ first, const int* __restrict__ units, int P,
+                                                    int2* __restrict__ work) {
+  const int k = blockIdx.y * P + blockIdx.x, at = first[k], n = at < 0 ? 0 : units[k];
+  for (int q = threadIdx.x; q < n; q += 256) work[at + q] = make_int2(blockIdx.x, q);
+}
+
+// Work lists of the active problems (all float-cycle and level-0 kinds).  The
+// host only counts; the lists are written where they are read, in stream
+// order.  (Written on the host and copied, with a wait for the copy, they kept
+// the chip idle for some 40 us each time a problem finished.)
 int team_lists(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, bool with_export) {
   mgfem_ctx* c = b;
-  std::vector<int2> w;
   T.seg_off.assign(4 * T.depth, 0);
   T.seg_cnt.assign(4 * T.depth, 0);
-  for (int kind = 0; kind < 4; ++kind)
-    for (int d = 0; d < T.depth; ++d) {
-      T.seg_off[seg(T, kind, d)] = (int)w.size();
+  const int S = 4 * T.depth + 5, P = T.P;
+  // the copy below has been read by the time the host knows a norm behind it
+  int* first = T.stage;
+  std::fill(first, first + (size_t)S * P, -1);
+  int w = 0;
+  for (int k = 0; k < S; ++k) {
+    int* off = k < 4 * T.depth ? &T.seg_off[k] : &T.l0_off[k - 4 * T.depth];
+    int* cnt = k < 4 * T.depth ? &T.seg_cnt[k] : &T.l0_cnt[k - 4 * T.depth];
+    *off = w;
+    if (k != 4 * T.depth + kTeamExport || with_export)
       for (int p : active) {
-        mgfem_ctx* m = b->members[p];
-        const bool smooths = d < T.lc[p];
-        const bool maps = T.lc[p] == d + 1;
-        if ((kind == kTeamMap && !maps) || (kind != kTeamMap && !smooths)) continue;
-        const int u = fused_kind(T, kind) ? fused_units(m, d) : team_units(m, kind, d);
-        for (int q = 0; q < u; ++q) w.push_back(make_int2(p, q));
+        first[(size_t)k * P + p] = w;
+        w += T.units[(size_t)k * P + p];
       }
-      T.seg_cnt[seg(T, kind, d)] = (int)w.size() - T.seg_off[seg(T, kind, d)];
-    }
-  for (int kind = 0; kind < 5; ++kind) {
-    T.l0_off[kind] = (int)w.size();
-    if (kind != kTeamExport || with_export) {
-      const std::vector<int>& who = active;
-      for (int p : who) {
-        const int u = team_l0_units(T.l0h[p], kind);
-        for (int q = 0; q < u; ++q) w.push_back(make_int2(p, q));
-      }
-    }
-    T.l0_cnt[kind] = (int)w.size() - T.l0_off[kind];
+    *cnt = w - *off;
   }
-  if (w.size() > T.work_cap) {
-    T.work_cap = std::max(w.size(), 2 * T.work_cap);
-    MGFEM_HIP_TRY(ctx_alloc_t(b, &T.work, T.work_cap));
-  }
-  if (!w.empty())
-    MGFEM_HIP_TRY(hipMemcpyAsync(T.work, w.data(), w.size() * sizeof(int2), hipMemcpyHostToDevice, b->s));
+  for (size_t q = 0; q < active.size(); ++q) first[(size_t)S * P + q] = active[q];
   T.nprobs = (int)active.size();
-  if (!active.empty())
-    MGFEM_HIP_TRY(hipMemcpyAsync(T.probs, active.data(), active.size() * sizeof(int), hipMemcpyHostToDevice, b->s));
-  // the host vectors must outlive the copies
-  MGFEM_HIP_TRY(hipStreamSynchronize(b->s));
+  MGFEM_HIP_TRY(hipMemcpyAsync(T.first, first, ((size_t)S * P + active.size()) * sizeof(int), hipMemcpyHostToDevice,
+                               b->s));
+  hipLaunchKernelGGL(k_team_lists, dim3(P, S), dim3(256), 0, b->s, (const int*)T.first, (const int*)T.units_dev, P,
+                     T.work);
+  MGFEM_HIP_TRY(hipGetLastError());
   return MGFEM_OK;
 }
 
@@ -132,11 +134,26 @@ void team_level(mgfem_ctx* b, TeamPlan& T, int d, std::vector<int>& par) {
   }
 }
 
-int read_red(mgfem_ctx* b, TeamPlan& T) {
+// the active problems' norms as reduction number T.seq (records `slot`), and
+// the wait for them
+void reduce(mgfem_ctx* b, TeamPlan& T, int slot) {
+  T.seq += 1.0;
+  team_reduce(b->s, T.l0, T.first + (size_t)(4 * T.depth + 5) * T.P, T.nprobs, T.rec + 4 * (size_t)slot * T.P, T.seq);
+}
+int read_red(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, int slot, double seq) {
   mgfem_ctx* c = b;
-  team_reduce(b->s, T.l0, T.probs, T.nprobs, T.red);
-  MGFEM_HIP_TRY(hipMemcpyAsync(T.red_host, T.red, 2 * T.P * sizeof(double), hipMemcpyDeviceToHost, b->s));
-  MGFEM_HIP_TRY(hipStreamSynchronize(b->s));
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int p : active) {
+    volatile const double* r = T.rec + 4 * ((size_t)slot * T.P + p);
+    while (r[2] != seq)
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200)) {
+        MGFEM_HIP_TRY(hipStreamSynchronize(b->s));
+        if (r[2] != seq) {
+          c->last_error = "residual norms of the batch did not arrive";
+          return MGFEM_ERR_HIP;
+        }
+      }
+  }
   return MGFEM_OK;
 }
 
@@ -146,7 +163,7 @@ bool team_ok(const mgfem_ctx* b) { return b->team && b->team->ok; }
 
 void team_free(mgfem_ctx* b) {
   if (!b->team) return;
-  if (b->team->red_host) (void)hipHostFree(b->team->red_host);
+  if (b->team->rec) (void)hipHostFree(b->team->rec);
   delete b->team;  // device buffers are the handle's allocations
   b->team = nullptr;
 }
@@ -205,9 +222,34 @@ int team_build(mgfem_ctx* b) {
   T->l0h.resize(P);
   for (int p = 0; p < P; ++p) team_l0_entry(b->members[p], &T->l0h[p]);
   MGFEM_HIP_TRY(ctx_alloc_t(b, &T->l0, P));
-  MGFEM_HIP_TRY(ctx_alloc_t(b, &T->probs, P));
-  MGFEM_HIP_TRY(ctx_alloc_t(b, &T->red, 2 * P));
-  MGFEM_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&T->red_host), 2 * P * sizeof(double)));
+  const int S = 4 * T->depth + 5;
+  T->units.assign((size_t)S * P, 0);
+  size_t items = 0;
+  for (int k = 0; k < S; ++k)
+    for (int p = 0; p < P; ++p) {
+      mgfem_ctx* m = b->members[p];
+      const int kind = k / T->depth, d = k % T->depth;
+      int n = 0;
+      if (k >= 4 * T->depth) n = team_l0_units(T->l0h[p], k - 4 * T->depth);
+      else if (kind == kTeamMap ? T->lc[p] == d + 1 : d < T->lc[p])
+        n = fused_kind(*T, kind) ? fused_units(m, d) : team_units(m, kind, d);
+      T->units[(size_t)k * P + p] = n;
+      items += (size_t)n;
+    }
+  MGFEM_HIP_TRY(ctx_alloc_t(b, &T->work, items + 1));
+  MGFEM_HIP_TRY(ctx_alloc_t(b, &T->units_dev, T->units.size()));
+  MGFEM_HIP_TRY(ctx_alloc_t(b, &T->first, T->units.size() + P));
+  MGFEM_HIP_TRY(hipMemcpyAsync(T->units_dev, T->units.data(), T->units.size() * sizeof(int), hipMemcpyHostToDevice,
+                               b->s));
+  const size_t rec_bytes = 8 * (size_t)P * sizeof(double), l0_bytes = P * sizeof(TeamL0);
+  char* pin = nullptr;
+  MGFEM_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&pin),
+                              rec_bytes + l0_bytes + (T->units.size() + P) * sizeof(int)));
+  std::memset(pin, 0, rec_bytes);
+  T->rec = reinterpret_cast<double*>(pin);
+  T->l0_stage = reinterpret_cast<TeamL0*>(pin + rec_bytes);
+  T->stage = reinterpret_cast<int*>(pin + rec_bytes + l0_bytes);
+  MGFEM_HIP_TRY(hipStreamSynchronize(b->s));
   T->ok = true;
   return MGFEM_OK;
 }
@@ -230,7 +272,8 @@ int team_solve(mgfem_ctx* b, const double* const* f, const double* const* g, dou
     T.l0h[p].u_out = u[p];
     T.l0h[p].ucur = 0;
   }
-  MGFEM_HIP_TRY(hipMemcpyAsync(T.l0, T.l0h.data(), P * sizeof(TeamL0), hipMemcpyHostToDevice, b->s));
+  std::memcpy(T.l0_stage, T.l0h.data(), P * sizeof(TeamL0));
+  MGFEM_HIP_TRY(hipMemcpyAsync(T.l0, T.l0_stage, P * sizeof(TeamL0), hipMemcpyHostToDevice, b->s));
   std::vector<int> active(P);
   for (int p = 0; p < P; ++p) active[p] = p;
   int rc = team_lists(b, T, active, false);
@@ -238,13 +281,15 @@ int team_solve(mgfem_ctx* b, const double* const* f, const double* const* g, dou
   // F = M f + G g and its norm
   launch_l0(b, T, kTeamCutRows, 0, 0);
   launch_l0(b, T, kTeamRhs, 0, 0);
-  if ((rc = read_red(b, T))) return rc;
-  std::vector<double> bnorm(P), prev(P);
-  std::vector<int> grow(P, 0);
-  for (int p = 0; p < P; ++p) bnorm[p] = T.red_host[2 * p];
+  reduce(b, T, 1);
   // u = 0: r = F
   launch_l0(b, T, kTeamOuterFirst, 0, 0);
-  if ((rc = read_red(b, T))) return rc;
+  reduce(b, T, 0);
+  if ((rc = read_red(b, T, active, 1, T.seq - 1.0))) return rc;
+  std::vector<double> bnorm(P), prev(P);
+  std::vector<int> grow(P, 0);
+  for (int p = 0; p < P; ++p) bnorm[p] = T.rec[4 * (P + p)];
+  if ((rc = read_red(b, T, active, 0, T.seq))) return rc;
   std::vector<int> ucur(P, 0);
   auto done = [&](int p, double r) {
     if (!std::isfinite(r)) return true;
@@ -252,7 +297,7 @@ int team_solve(mgfem_ctx* b, const double* const* f, const double* const* g, dou
   };
   std::vector<int> next;
   for (int p : active) {
-    const double r = T.red_host[2 * p];
+    const double r = T.rec[4 * p];
     hist[(size_t)p * H] = r;
     prev[p] = r;
     if (!done(p, r) && max_cycles > 0) next.push_back(p);
@@ -298,10 +343,11 @@ int team_solve(mgfem_ctx* b, const double* const* f, const double* const* g, dou
     upar ^= 1;
     par[0] = 1 - ce;
     ++m;
-    if ((rc = read_red(b, T))) return rc;
+    reduce(b, T, 0);
+    if ((rc = read_red(b, T, active, 0, T.seq))) return rc;
     next.clear();
     for (int p : active) {
-      const double r = T.red_host[2 * p];
+      const double r = T.rec[4 * p];
       hist[(size_t)p * H + m] = r;
       ncyc[p] = m;
       ucur[p] = upar;
@@ -314,7 +360,8 @@ int team_solve(mgfem_ctx* b, const double* const* f, const double* const* g, dou
   }
   // every problem's result into the caller's arrays
   for (int p = 0; p < P; ++p) T.l0h[p].ucur = ucur[p];
-  MGFEM_HIP_TRY(hipMemcpyAsync(T.l0, T.l0h.data(), P * sizeof(TeamL0), hipMemcpyHostToDevice, b->s));
+  std::memcpy(T.l0_stage, T.l0h.data(), P * sizeof(TeamL0));
+  MGFEM_HIP_TRY(hipMemcpyAsync(T.l0, T.l0_stage, P * sizeof(TeamL0), hipMemcpyHostToDevice, b->s));
   std::vector<int> all(P);
   for (int p = 0; p < P; ++p) all[p] = p;
   if ((rc = team_lists(b, T, all, true))) return rc;
