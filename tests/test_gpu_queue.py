@@ -36,3 +36,27 @@ def test_steps_behind_the_norm_leave_its_iterate(N, coarsest, kw):
         up, hp = s.solve(p.f, p.g, tol=-1.0, max_cycles=m)
         s.profile(False)
         assert np.array_equal(hp, h) and torch.equal(u, up)
+
+
+@pytest.mark.parametrize("N,coarsest,kw", [(64, 4, {}), (1536, 3, {}), (128, 4, {"mixed": True})])
+def test_iteration_queued_before_the_first_norm(N, coarsest, kw):
+    """Data whose residual is zero or not finite from the start: the zero
+    vector comes back, and the next solve and adjoint are not touched."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_05105_amd as mg
+    p = W.flower_mms(N)
+    s = mg.Solver(p.psi, N, coarsest_n=coarsest, precision=mg.PREC_MIXED if kw.get("mixed") else mg.PREC_FP64)
+    u, h = s.solve(p.f, p.g, tol=1e-9)
+    lam = s.adjoint(u, tol=1e-9)[2]
+    zero = torch.zeros_like(u)
+    uz, hz = s.solve(zero, zero, tol=1e-9)
+    assert len(hz) == 1 and hz[0] == 0.0 and not uz.any()
+    un, hn = s.solve(zero + float("nan"), p.g, tol=1e-9, raise_on_fail=False)
+    assert len(hn) == 1 and not np.isfinite(hn[0]) and not un.any()
+    assert s.last_status == mg._lib.ERR_DIVERGED
+    lz = s.adjoint(zero, tol=1e-9)
+    assert not lz[2].any()
+    u2, h2 = s.solve(p.f, p.g, tol=1e-9)
+    assert np.array_equal(h, h2) and torch.equal(u, u2)
+    assert torch.equal(lam, s.adjoint(u, tol=1e-9)[2])
