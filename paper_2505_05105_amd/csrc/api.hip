@@ -57,23 +57,32 @@ namespace mgfem {
 void set_setup_error(const std::string& msg) { g_setup_error = msg; }
 
 // A handle holds some 300 arrays, most of them small; a hipMalloc, its fill
-// and its hipFree cost about 40 us each (half of a set-up at N = 1024), so
-// arrays share chunks of 1 MB, doubling to 64 MB, cleared once; an array
-// that would waste more than a quarter of the next chunk gets its own.
+// and its hipFree cost about 40 us each, and a hipFree of anything from 48 MB
+// 250 us whatever its size (a hipMalloc 140 to 300 us up to 48 MB, 35 us from
+// 150 MB), so arrays share chunks, cleared once: the first of the size that a
+// handle is expected to need (set-up), the next ones an eighth of that,
+// doubling, within 2 and 64 MB.
+// An array that would waste more than a quarter of the next chunk gets its own.
+// Set-up and release of the flower with N = 1024: 10 ms with chunks doubling
+// from 1 MB, 5 ms like this.
 hipError_t ctx_alloc(mgfem_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   bytes = (std::max<size_t>(bytes, 8) + 255) & ~(size_t)255;
-  const size_t chunk = c->chunk_next;
+  const size_t chunk = (c->chunk_next + 255) & ~(size_t)255;  // (scratch from its end is as aligned as the arrays)
   if (bytes > c->chunk_left && bytes <= chunk / 4 * 3) {
     void* q = nullptr;
     const hipError_t e = hipMalloc(&q, chunk);
-    if (e != hipSuccess) return e;
-    c->allocs.push_back(q);
-    c->chunk = static_cast<char*>(q);
-    c->chunk_left = chunk;
-    c->chunk_next = std::min<size_t>(2 * chunk, (size_t)64 << 20);
-    const hipError_t z = hipMemsetAsync(q, 0, chunk, c->s);
-    if (z != hipSuccess) return z;
+    const size_t next = c->allocs.empty() ? chunk / 8 : 2 * chunk;
+    c->chunk_next = std::min<size_t>(std::max<size_t>(next, (size_t)2 << 20), (size_t)64 << 20);
+    if (e == hipSuccess) {
+      c->allocs.push_back(q);
+      c->chunk = static_cast<char*>(q);
+      c->chunk_left = chunk;
+      const hipError_t z = hipMemsetAsync(q, 0, chunk, c->s);
+      if (z != hipSuccess) return z;
+    } else {
+      (void)hipGetLastError();  // the array alone may fit
+    }
   }
   if (bytes <= c->chunk_left) {
     *p = c->chunk;
@@ -85,6 +94,27 @@ hipError_t ctx_alloc(mgfem_ctx* c, void** p, size_t bytes) {
   if (e != hipSuccess) return e;
   c->allocs.push_back(*p);
   return hipMemsetAsync(*p, 0, bytes, c->s);
+}
+
+// scratch from the end of the current chunk where it fits, given back (and
+// cleared) in stream order; else an allocation of its own
+hipError_t TempMem::alloc(size_t bytes) {
+  size_ = (bytes + 255) & ~(size_t)255;
+  if (size_ <= c_->chunk_left) {
+    c_->chunk_left -= size_;
+    p_ = c_->chunk + c_->chunk_left;
+    tail_ = true;
+    return hipSuccess;
+  }
+  return hipMalloc(&p_, size_);
+}
+TempMem::~TempMem() {
+  if (!p_) return;
+  if (!tail_) {
+    (void)hipFree(p_);
+  } else if (p_ == c_->chunk + c_->chunk_left && hipMemsetAsync(p_, 0, size_, c_->s) == hipSuccess) {
+    c_->chunk_left += size_;
+  }  // (a new chunk has been started since: the piece goes with its chunk)
 }
 }  // namespace mgfem
 
@@ -287,6 +317,12 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
     L.n = (int64_t)(n + 1) * (n + 1);
     c->lv.push_back(L);
   }
+  // the first chunk: planes and vectors of level 0, a third of them again for
+  // the coarser levels, and the plans and the coarse map
+  const size_t plane = (size_t)c->lv[0].n * sizeof(double);
+  const size_t planes = (p.precision == MGFEM_PREC_MIXED ? 52 : 42) + (chi_dev ? 10 : 0);
+  c->chunk_next = std::min<size_t>(std::max<size_t>(plane * planes + (N >= 512 ? (size_t)128 << 20 : 0), (size_t)1 << 20),
+                                   (size_t)2 << 30);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int rc = MGFEM_OK;
   auto bail = [&](int code) {
@@ -732,9 +768,9 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   };
   // From zero, with a tolerance below 1, the first iteration is needed unless
   // F is zero or not finite: it is launched before the norms are read (and then
-  // discarded; the result is the zero vector).  Solves of the
-  // circle with N = 64 took 239 us, like this 232; of the mixed ellipse with
-  // N = 320 from 533 to 469.
+  // discarded; the result is the zero vector).  Speed of solves
+  // against one fixed earlier program: circle, N = 64 1.41 before, 1.48 like
+  // this; mixed ellipse, N = 320 1.18 and 1.21.
   if (!warm && rel_tol < 1.0 && max_cycles > 0 && !c->prof.on) {
     rc = launch(pend[0]);
     if (rc) return rc;

@@ -1285,16 +1285,9 @@ int build_fused(mgfem_ctx* c) {
     return (size_t)(p - base);
   };
   const size_t total = layout(nullptr);
-  struct Owner {
-    std::vector<void*> v;
-    ~Owner() {
-      for (void* p : v) (void)hipFree(p);
-    }
-  } owner;
-  char* scratch = nullptr;
-  MGFEM_HIP_TRY(hipMalloc(&scratch, total));
-  owner.v.push_back(scratch);
-  layout(scratch);
+  TempMem scratch(c);
+  MGFEM_HIP_TRY(scratch.alloc(total));
+  layout(scratch.get());
   hipStream_t s = c->s;
   std::vector<int> tot(8 * c->lv.size(), 0);
   auto get = [&](int* dst, const int* src) { return hipMemcpyAsync(dst, src, sizeof(int), hipMemcpyDeviceToHost, s); };
@@ -1366,6 +1359,16 @@ int build_fused(mgfem_ctx* c) {
     if (in[ls[q] + 1] && !c->lv[ls[q] + 1].fp.ok && tmp[ls[q] + 1].nblk > 0) c->lv[ls[q]].fp.ok = false;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_delta_build), hipFuncAttributeMaxDynamicSharedMemorySize,
                             build_lds(kMaxBlockCols));
+  // the blocks' values and columns
+  auto block_bytes = [&](int l) {
+    return ((size_t)tot[8 * l + 3] * sizeof(double) + (size_t)tot[8 * l + 2] * sizeof(int) + 255) & ~(size_t)255;
+  };
+  size_t all_blocks = 0;
+  for (int l : ls)
+    if (c->lv[l].fp.ok && tmp[l].nblk > 0) all_blocks += block_bytes(l);
+  TempMem blocks(c);
+  if (all_blocks > 0) MGFEM_HIP_TRY(blocks.alloc(all_blocks));
+  char* next_block = blocks.get();
   for (int l : ls) {
     Level& L = c->lv[l];
     Tmp& t = tmp[l];
@@ -1391,10 +1394,9 @@ int build_fused(mgfem_ctx* c) {
     F.Didx = reinterpret_cast<uint4*>(carve(buf, nseg * 32));
     if (t.nblk == 0) continue;
     MGFEM_HIP_TRY(hipMemcpyAsync(F.rows, t.rows, (size_t)F.ncut * sizeof(int), hipMemcpyDeviceToDevice, s));
-    MGFEM_HIP_TRY(hipMalloc(&buf, (size_t)tot[8 * l + 3] * sizeof(double) + (size_t)tot[8 * l + 2] * sizeof(int)));
-    owner.v.push_back(buf);
-    t.D = reinterpret_cast<double*>(buf);
-    t.cols = reinterpret_cast<int*>(buf + (size_t)tot[8 * l + 3] * sizeof(double));
+    t.D = reinterpret_cast<double*>(next_block);
+    t.cols = reinterpret_cast<int*>(next_block + (size_t)tot[8 * l + 3] * sizeof(double));
+    next_block += block_bytes(l);
     hipLaunchKernelGGL(k_block_fill, dim3(nblk(t.nblk, 256)), dim3(256), 0, s, t.bcell, t.nblk, t.pos, t.nc, eta,
                        t.coff, t.voff, t.cols, t.blocks);
     hipLaunchKernelGGL(k_delta_build, dim3(t.nblk), dim3(64 * kBuildWaves), build_lds(hf[2 * l]), s,

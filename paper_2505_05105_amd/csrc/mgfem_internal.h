@@ -441,6 +441,24 @@ hipError_t ctx_alloc_t(mgfem_ctx* c, T** p, size_t count) {
   return ctx_alloc(c, reinterpret_cast<void**>(p), count * sizeof(T));
 }
 
+// set-up scratch, released when it goes out of scope (the stream's work on it
+// has to be queued by then, an own allocation's finished)
+class TempMem {
+ public:
+  explicit TempMem(mgfem_ctx* c) : c_(c) {}
+  TempMem(const TempMem&) = delete;
+  TempMem& operator=(const TempMem&) = delete;
+  ~TempMem();
+  hipError_t alloc(size_t bytes);
+  char* get() const { return static_cast<char*>(p_); }
+
+ private:
+  mgfem_ctx* c_;
+  void* p_ = nullptr;
+  size_t size_ = 0;
+  bool tail_ = false;
+};
+
 // setup stages (geometry.hip, hierarchy.hip)
 int setup_geometry(mgfem_ctx* c, const double* psi_in, const double* chi_in);
 int setup_hierarchy(mgfem_ctx* c, const double* psi_in, const double* chi_in);

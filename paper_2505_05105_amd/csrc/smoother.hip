@@ -2257,8 +2257,9 @@ void col_launch(hipStream_t s, int kind, const void* tab, const int2* work, int 
 }
 
 template <class E>
-int upload_table(mgfem_ctx* c, const std::vector<E>& h, void** dev) {
-  MGFEM_HIP_TRY(hipMalloc(dev, h.size() * sizeof(E)));
+int upload_table(mgfem_ctx* c, const std::vector<E>& h, char*& at, void** dev) {
+  *dev = at;
+  at += (h.size() * sizeof(E) + 255) & ~(size_t)255;
   MGFEM_HIP_TRY(hipMemcpyAsync(*dev, h.data(), h.size() * sizeof(E), hipMemcpyHostToDevice, c->s));
   return MGFEM_OK;
 }
@@ -2309,8 +2310,15 @@ int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
     const int64_t nL = Ll.n, nC = Lc.n;
     const int64_t ncL = std::max(1, Ll.cut_off[4]);
     const int64_t total = 3 * J * nL + J * ncL + 3 * J * nC;
-    double* buf = nullptr;
-    MGFEM_HIP_TRY(hipMalloc(&buf, total * sizeof(double)));
+    const int us = Ll.ntiles, uc = has_cut ? Ll.cp.units : 0, ur = Lc.empty() ? 0 : Ll.rr_ntiles;
+    const int um = (M.n + kMapWaves - 1) / kMapWaves;
+    TempMem tmp(c);
+    MGFEM_HIP_TRY(tmp.alloc(total * sizeof(double) + 6 * 256 +
+                            (size_t)J * (sizeof(SweepEntry<double>) + sizeof(CutEntry<double>) +
+                                         sizeof(RrEntry<double>) + sizeof(MapEntry<double>) +
+                                         (size_t)(us + uc + ur + um) * sizeof(int2))));
+    double* buf = reinterpret_cast<double*>(tmp.get());
+    char* at = tmp.get() + ((total * sizeof(double) + 255) & ~(size_t)255);
     double* XL = buf;               // buffer 0 of column j at XL + j nL, buffer 1 at XL + (J + j) nL
     double* bL = XL + 2 * J * nL;
     double* sL = bL + J * nL;
@@ -2358,13 +2366,11 @@ int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
       m.x = XC + j * nC;
     }
     void *dts = nullptr, *dtc = nullptr, *dtr = nullptr, *dtm = nullptr;
-    int rc = upload_table(c, ts, &dts);
-    if (!rc) rc = upload_table(c, tc, &dtc);
-    if (!rc) rc = upload_table(c, tr, &dtr);
-    if (!rc) rc = upload_table(c, tm, &dtm);
+    int rc = upload_table(c, ts, at, &dts);
+    if (!rc) rc = upload_table(c, tc, at, &dtc);
+    if (!rc) rc = upload_table(c, tr, at, &dtr);
+    if (!rc) rc = upload_table(c, tm, at, &dtm);
     // work lists, column by column (the first Jc columns are a prefix)
-    const int us = Ll.ntiles, uc = has_cut ? Ll.cp.units : 0, ur = Lc.empty() ? 0 : Ll.rr_ntiles;
-    const int um = (M.n + kMapWaves - 1) / kMapWaves;
     std::vector<int2> w;
     for (int j = 0; j < J; ++j)
       for (int q = 0; q < us; ++q) w.push_back(make_int2(j, q));
@@ -2374,8 +2380,7 @@ int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
       for (int q = 0; q < ur; ++q) w.push_back(make_int2(j, q));
     for (int j = 0; j < J; ++j)
       for (int q = 0; q < um; ++q) w.push_back(make_int2(j, q));
-    int2* dw = nullptr;
-    if (!rc && hipMalloc(&dw, w.size() * sizeof(int2)) != hipSuccess) rc = MGFEM_ERR_OOM;
+    int2* dw = reinterpret_cast<int2*>(at);
     if (!rc && hipMemcpyAsync(dw, w.data(), w.size() * sizeof(int2), hipMemcpyHostToDevice, c->s) != hipSuccess)
       rc = MGFEM_ERR_HIP;
     const int2* ws = dw;
@@ -2409,12 +2414,6 @@ int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
       if (hipGetLastError() != hipSuccess) rc = MGFEM_ERR_HIP;
     }
     if (hipStreamSynchronize(c->s) != hipSuccess && !rc) rc = MGFEM_ERR_HIP;
-    (void)hipFree(dw);
-    (void)hipFree(dts);
-    (void)hipFree(dtc);
-    (void)hipFree(dtr);
-    (void)hipFree(dtm);
-    (void)hipFree(buf);
     if (rc) {
       c->last_error = "coarse map extension to level " + std::to_string(L) + " failed";
       return rc;

@@ -588,15 +588,12 @@ int build_stream(mgfem_ctx* c, int l) {
   const int TW = 64, TH = sweep_shape(c, l) == kShapeFinest ? 32 : 16, CW = 32, CH = 16;
   const int ntx = (L.bbox[1] - L.bbox[0] + TW) / TW, nty = (L.bbox[3] - L.bbox[2] + TH) / TH;
   const int cnx = (C.bbox[1] - C.bbox[0] + CW) / CW;
-  struct Owner {
-    char* p = nullptr;
-    ~Owner() { (void)hipFree(p); }
-  } tmp;
+  TempMem tmp(c);
   const size_t ints = (size_t)L.ntiles + (size_t)std::max(1, L.rr_ntiles);
-  MGFEM_HIP_TRY(hipMalloc(&tmp.p, ints * sizeof(int) + (size_t)ntx * nty));
-  int* d_inner = reinterpret_cast<int*>(tmp.p);
+  MGFEM_HIP_TRY(tmp.alloc(ints * sizeof(int) + (size_t)ntx * nty));
+  int* d_inner = reinterpret_cast<int*>(tmp.get());
   int* d_keep = d_inner + L.ntiles;
-  uint8_t* d_map = reinterpret_cast<uint8_t*>(tmp.p + ints * sizeof(int));
+  uint8_t* d_map = reinterpret_cast<uint8_t*>(tmp.get() + ints * sizeof(int));
   hipLaunchKernelGGL(k_tile_inner, dim3(L.ntiles), dim3(256), 0, c->s, (const int*)L.tiles, ntx, L.bbox[0], L.bbox[2],
                      TW, TH, (const uint8_t*)L.flags, L.N, d_inner);
   std::vector<int> inner(L.ntiles), tiles(L.ntiles);
