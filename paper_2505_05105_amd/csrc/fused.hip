@@ -555,10 +555,44 @@ __global__ void k_zero_int(int* p, int n) {
   for (int q = threadIdx.x; q < n; q += blockDim.x) p[q] = 0;
 }
 
+// The set-up kernels take every fused level in one launch: each is a chain of
+// dependent loads or phases that one level does not fill the chip with (the
+// flower with N = 1024: 2.5 ms level by level, 1.1 ms like this).
+struct SetLevel {
+  const uint8_t *fl, *flc;  // flags of the level and of the coarser one
+  const double* A;
+  int64_t n;
+  int N, nc, nt, cut;       // cells and tiles per side, cut vertices
+  int coarse;               // the coarser level's place in the list, or -1
+  int nblk;
+  int *cnt, *pos, *bid, *npos, *rows, *bcell, *ncol, *coff, *nval, *voff, *keep, *slot, *nst, *stoff, *nseg, *segoff;
+  FBlock* blocks;
+  int* cols;
+  double* D;
+  int* tot;                 // blocks, cut vertices, columns, values, tiles, stored rows, segments;
+                            // [8] columns of the largest block, [9] a record that does not fit
+  const int* cutpos;
+  FTile* tiles;
+  int* st_idx;
+  void* st_coef;
+  double *fD, *fDT;
+  uint16_t* fidx;
+};
+constexpr int kMaxSet = 12;
+struct SetLevels {
+  int n;
+  SetLevel v[kMaxSet];
+};
+static_assert(sizeof(SetLevels) <= 3584, "kernel arguments");
+
 // cut vertices per cell
-__global__ void k_cell_count(const uint8_t* __restrict__ fl, int N, int nc, int* __restrict__ cnt) {
+__global__ void k_cell_count(SetLevels S) {
+  const SetLevel& L = S.v[blockIdx.y];
+  const int N = L.N, nc = L.nc;
+  const uint8_t* __restrict__ fl = L.fl;
+  int* __restrict__ cnt = L.cnt;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc * nc) return;
+  if (c >= nc * nc || L.cut == 0) return;
   const int i0 = (c % nc) * kCell, j0 = (c / nc) * kCell;
   int n = 0;
   for (int q = 0; q < kCell * kCell; ++q) {
@@ -568,52 +602,92 @@ __global__ void k_cell_count(const uint8_t* __restrict__ fl, int N, int nc, int*
   cnt[c] = n;
 }
 
-// exclusive prefix sum over n values by one workgroup of 1024 threads:
-// out[0..n]; out2 (optional) counts the non-zero values before each
-__device__ void wg_scan(const int* in, int n, int* out, int* out2) {
-  __shared__ int sa[1024], sb2[1024];
-  const int t = threadIdx.x, per = (n + 1023) / 1024;
-  const int lo = min(n, t * per), hi = min(n, lo + per);
-  int a = 0, b = 0;
-  for (int q = lo; q < hi; ++q) {
-    a += in[q];
-    b += in[q] != 0;
-  }
-  sa[t] = a;
-  sb2[t] = b;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int va = t >= o ? sa[t - o] : 0, vb = t >= o ? sb2[t - o] : 0;
+// exclusive prefix sum over n values by one workgroup of 1024 threads, in runs
+// of eight values per thread: out[0..n], the total in *tot too; out2 (optional)
+// counts the non-zero values before each (-1: zero)
+__device__ void wg_scan(const int* in, int n, int* out, int* out2, int* tot, int* tot2) {
+  constexpr int U = 8;
+  __shared__ int wa[16], wb[16];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  int ca = 0, cb = 0;  // sums of the runs before
+  for (int base = 0; base < n; base += 1024 * U) {
+    const int q0 = base + t * U;
+    int v[U], a = 0, b = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = in[min(q0 + u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (q0 + u >= n) v[u] = 0;
+      a += v[u];
+      b += v[u] != 0;
+    }
+    int xa = a, xb = b;  // inclusive over the wave
+    for (int o = 1; o < 64; o <<= 1) {
+      const int ya = __shfl_up(xa, o), yb = __shfl_up(xb, o);
+      if (lane >= o) {
+        xa += ya;
+        xb += yb;
+      }
+    }
+    if (lane == 63) {
+      wa[wave] = xa;
+      wb[wave] = xb;
+    }
     __syncthreads();
-    sa[t] += va;
-    sb2[t] += vb;
+    xa += ca - a;
+    xb += cb - b;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) {
+        xa += wa[w];
+        xb += wb[w];
+      }
+      ca += wa[w];
+      cb += wb[w];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q0 + u < n) {
+        out[q0 + u] = xa;
+        if (out2) out2[q0 + u] = v[u] != 0 ? xb : -1;
+        xa += v[u];
+        xb += v[u] != 0;
+      }
     __syncthreads();
   }
-  int xa = sa[t] - a, xb = sb2[t] - b;
-  for (int q = lo; q < hi; ++q) {
-    const int v = in[q];
-    out[q] = xa;
-    if (out2) out2[q] = v != 0 ? xb : -1;
-    xa += v;
-    xb += v != 0;
+  if (t == 0) {
+    out[n] = ca;
+    *tot = ca;
+    if (out2) {
+      out2[n] = cb;
+      *tot2 = cb;
+    }
   }
-  if (t == 1023) {
-    out[n] = sa[1023];
-    if (out2) out2[n] = sb2[1023];
-  }
-  __syncthreads();
 }
-__global__ __launch_bounds__(1024) void k_scan_cells(const int* cnt, int n, int* pos, int* bid) {
-  wg_scan(cnt, n, pos, bid);
+__global__ __launch_bounds__(1024) void k_scan_cells(SetLevels S) {
+  const SetLevel& L = S.v[blockIdx.x];
+  if (L.cut > 0) wg_scan(L.cnt, L.nc * L.nc, L.pos, L.bid, L.tot + 1, L.tot);
 }
-__global__ __launch_bounds__(1024) void k_scan_plain(const int* cnt, int n, int* off) { wg_scan(cnt, n, off, nullptr); }
+__global__ __launch_bounds__(1024) void k_scan_blocks(SetLevels S) {
+  const SetLevel& L = S.v[blockIdx.x];
+  if (L.nblk > 0)
+    wg_scan(blockIdx.y ? L.nval : L.ncol, L.nblk, blockIdx.y ? L.voff : L.coff, nullptr, L.tot + 2 + blockIdx.y, nullptr);
+}
+__global__ __launch_bounds__(1024) void k_scan_tiles(SetLevels S) {
+  const SetLevel& L = S.v[blockIdx.x];
+  const int k = blockIdx.y;
+  wg_scan(k == 0 ? L.keep : k == 1 ? L.nst : L.nseg, L.nt * L.nt, k == 0 ? L.slot : k == 1 ? L.stoff : L.segoff,
+          nullptr, L.tot + 4 + k, nullptr);
+}
 
 // rows by position, positions by node, and the cell of every block
-__global__ void k_cell_fill(const uint8_t* __restrict__ fl, int N, int nc, const int* __restrict__ pos,
-                            const int* __restrict__ bid, int* __restrict__ rows, int* __restrict__ npos,
-                            int* __restrict__ bcell) {
+__global__ void k_cell_fill(SetLevels S) {
+  const SetLevel& L = S.v[blockIdx.y];
+  const int N = L.N, nc = L.nc;
+  const uint8_t* __restrict__ fl = L.fl;
+  const int *__restrict__ pos = L.pos, *__restrict__ bid = L.bid;
+  int *__restrict__ rows = L.rows, *__restrict__ npos = L.npos, *__restrict__ bcell = L.bcell;
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc * nc || bid[c] < 0) return;
+  if (L.cut == 0 || c >= nc * nc || bid[c] < 0) return;
   bcell[bid[c]] = c;
   const int i0 = (c % nc) * kCell, j0 = (c / nc) * kCell;
   int p = pos[c];
@@ -631,10 +705,12 @@ __global__ void k_cell_fill(const uint8_t* __restrict__ fl, int N, int nc, const
 // (one contiguous run of positions per row of cells), their number and the
 // values of its D
 __device__ inline int cell_reach_y(int eta) { return (2 * eta + kCell - 1) / kCell; }
-__global__ void k_block_size(const int* __restrict__ bcell, int nblk, const int* __restrict__ pos, int nc, int eta,
-                             int* __restrict__ ncol, int* __restrict__ nval, int* __restrict__ mx) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nblk) return;
+__global__ void k_block_size(SetLevels S, int eta) {
+  const SetLevel& L = S.v[blockIdx.y];
+  const int *__restrict__ bcell = L.bcell, *__restrict__ pos = L.pos;
+  int *__restrict__ ncol = L.ncol, *__restrict__ nval = L.nval, *__restrict__ mx = L.tot + 8;
+  const int nc = L.nc, b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= L.nblk) return;
   const int c = bcell[b], cx = c % nc, cy = c / nc, ry = cell_reach_y(eta);
   int n = 0;
   for (int y = max(0, cy - ry); y <= min(nc - 1, cy + ry); ++y)
@@ -644,11 +720,14 @@ __global__ void k_block_size(const int* __restrict__ bcell, int nblk, const int*
   atomicMax(mx, n);
 }
 
-__global__ void k_block_fill(const int* __restrict__ bcell, int nblk, const int* __restrict__ pos, int nc, int eta,
-                             const int* __restrict__ coff, const int* __restrict__ voff, int* __restrict__ cols,
-                             FBlock* __restrict__ blocks) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nblk) return;
+__global__ void k_block_fill(SetLevels S, int eta) {
+  const SetLevel& L = S.v[blockIdx.y];
+  const int *__restrict__ bcell = L.bcell, *__restrict__ pos = L.pos, *__restrict__ coff = L.coff,
+            *__restrict__ voff = L.voff;
+  int* __restrict__ cols = L.cols;
+  FBlock* __restrict__ blocks = L.blocks;
+  const int nc = L.nc, b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= L.nblk || !cols) return;
   const int c = bcell[b], cx = c % nc, cy = c / nc, ry = cell_reach_y(eta);
   int w = coff[b];
   for (int y = max(0, cy - ry); y <= min(nc - 1, cy + ry); ++y)
@@ -663,13 +742,18 @@ __global__ void k_block_fill(const int* __restrict__ bcell, int nblk, const int*
 // t_i = w_i / a_ii for the nodes of colour c, adds t_i to D[p][i], clears w_i
 // and subtracts a_ij t_i from w_j (A is symmetric: gathered by j from its own
 // row).  The waves never wait for one another after the staging.
-constexpr int kMaxBlockCols = 512, kBuildWaves = 4;
-__global__ __launch_bounds__(64 * kBuildWaves) void k_delta_build(
-    const FBlock* __restrict__ blocks, const int* __restrict__ cols, const int* __restrict__ rows,
-    const int* __restrict__ npos, const uint8_t* __restrict__ fl, const double* __restrict__ A, int64_t n, int N,
-    int eta, double* __restrict__ D) {
+constexpr int kMaxBlockCols = 512, kBuildWaves = 8;
+__global__ __launch_bounds__(64 * kBuildWaves) void k_delta_build(SetLevels S, int eta) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const FBlock B = blocks[blockIdx.x];
+  const SetLevel& L = S.v[blockIdx.y];
+  if ((int)blockIdx.x >= L.nblk || !L.D) return;
+  const int *__restrict__ cols = L.cols, *__restrict__ rows = L.rows, *__restrict__ npos = L.npos;
+  const uint8_t* __restrict__ fl = L.fl;
+  const double* __restrict__ A = L.A;
+  double* __restrict__ D = L.D;
+  const int64_t n = L.n;
+  const int N = L.N;
+  const FBlock B = L.blocks[blockIdx.x];
   const int nr = B.n & 0xff, nc = B.n >> 8;
   double* sA = reinterpret_cast<double*>(smem);  // 9 planes of nc: the row, 1/diagonal in plane 4
   double* sw = sA + 9 * nc;                      // one vector of nc per wave
@@ -775,6 +859,17 @@ struct PlanLevel {
   const double* D;
 };
 
+__device__ inline PlanLevel plan_view(const SetLevel& L) {
+  return PlanLevel{L.fl, L.N, L.nblk > 0 ? L.npos : nullptr, L.bid, L.nc, L.blocks, L.cols, L.rows, L.D};
+}
+__device__ inline PlanLevel coarse_view(const SetLevels& S, const SetLevel& L) {
+  if (L.coarse >= 0 && S.v[L.coarse].nblk > 0) return plan_view(S.v[L.coarse]);
+  PlanLevel P{};
+  P.fl = L.flc;
+  P.N = L.N >> 1;
+  return P;
+}
+
 // The rows and columns a box of a tile needs, in LDS: the cut vertices of the
 // W x H box at (x, y) are its rows, those within reach of it its columns.
 constexpr int kMaxReachX = 16, kMaxReachY = 8;
@@ -825,10 +920,11 @@ __device__ void plan_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
     B.len[e] = (int16_t)n;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     int n = 0;
-    for (int e = 0; e < B.nrow; ++e) n += (B.len[e] + 15) / 16;
-    B.nseg = n;
+    for (int e = threadIdx.x; e < B.nrow; e += 64) n += (B.len[e] + 15) / 16;
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if (threadIdx.x == 0) B.nseg = n;
   }
   __syncthreads();
 }
@@ -837,9 +933,12 @@ __device__ void plan_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
 // the stored rows of the region, the segments of D, and the
 // largest counts a record has to hold
 template <int FT>
-__global__ __launch_bounds__(256) void k_ftile_count(PlanLevel P, PlanLevel C, int nt, int eta, int* __restrict__ keep,
-                                                     int* __restrict__ nst, int* __restrict__ nseg,
-                                                     int* __restrict__ over) {
+__global__ __launch_bounds__(256) void k_ftile_count(SetLevels S, int first, int eta) {
+  const SetLevel& L = S.v[first + blockIdx.y];
+  const int nt = L.nt;
+  if ((int)blockIdx.x >= nt * nt) return;
+  const PlanLevel P = plan_view(L), C = coarse_view(S, L);
+  int *__restrict__ keep = L.keep, *__restrict__ nst = L.nst, *__restrict__ nseg = L.nseg, *__restrict__ over = L.tot + 9;
   using GE = Geo<FT>;
   constexpr int kRW = GE::RW, kRH = GE::RH, kRN = GE::RN, kCRW = GE::CRW, kCRH = GE::CRH;
   __shared__ int cnt;
@@ -885,16 +984,26 @@ __device__ void fill_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
   const int GW = W + 2 * ex, GH = H + 2 * ey, s = P.N + 1;
   for (int q = threadIdx.x; q < GW * GH; q += blockDim.x)
     if (B.local[q] >= 0) cols[B.local[q]] = P.npos[(x - ex + q % GW) + (int64_t)(y - ey + q / GW) * s];
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     int n = 0;
-    for (int e = 0; e < B.nrow; ++e) {
-      const int q = B.row[e], ri = q % W, rj = q / W, ns = (B.len[e] + 15) / 16;
-      const bool in = ri >= core_lo_x && ri < core_lo_x + core && rj >= core_lo_y && rj < core_lo_y + core;
-      rows[e].at = q | (int)in << 16;
-      rows[e].seg = n | ns << 16;
-      rows[e].pos = P.npos[(x + ri) + (int64_t)(y + rj) * s];
-      B.len[e] = (int16_t)n;  // now the row's first segment
-      n += ns;
+    for (int e0 = 0; e0 < B.nrow; e0 += 64) {
+      const int e = e0 + threadIdx.x;
+      const int ns = e < B.nrow ? (B.len[e] + 15) / 16 : 0;
+      int up = ns;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(up, o);
+        if ((int)threadIdx.x >= o) up += v;
+      }
+      const int at = n + up - ns;
+      n += __shfl(up, 63);
+      if (e < B.nrow) {
+        const int q = B.row[e], ri = q % W, rj = q / W;
+        const bool in = ri >= core_lo_x && ri < core_lo_x + core && rj >= core_lo_y && rj < core_lo_y + core;
+        rows[e].at = q | (int)in << 16;
+        rows[e].seg = at | ns << 16;
+        rows[e].pos = P.npos[(x + ri) + (int64_t)(y + rj) * s];
+        B.len[e] = (int16_t)at;  // now the row's first segment
+      }
     }
   }
   __syncthreads();
@@ -949,15 +1058,23 @@ __device__ void fill_box(const PlanLevel& P, int x, int y, int W, int H, int ex,
 
 // one workgroup per tile: stored rows in region order, then the rows, columns
 // and segments of its D on this level and of the coarser one under it
+// (1024 threads: a row's values cost a few dependent loads and a search, and
+// there are up to 300 rows)
 template <class T, int FT>
-__global__ __launch_bounds__(256) void k_ftile_fill(PlanLevel P, PlanLevel C, const double* __restrict__ A, int64_t n,
-                                                    int nt, int eta, const int* __restrict__ keep,
-                                                    const int* __restrict__ slot, const int* __restrict__ stoff,
-                                                    const int* __restrict__ nstp, const int* __restrict__ segoff,
-                                                    FTile* __restrict__ tiles, int* __restrict__ st_idx,
-                                                    T* __restrict__ st_coef, const int* __restrict__ cutpos,
-                                                    double* __restrict__ D, double* __restrict__ DT,
-                                                    uint16_t* __restrict__ idx) {
+__global__ __launch_bounds__(1024) void k_ftile_fill(SetLevels S, int first, int eta) {
+  const SetLevel& L = S.v[first + blockIdx.y];
+  const int nt = L.nt;
+  if ((int)blockIdx.x >= nt * nt || !L.tiles) return;
+  const PlanLevel P = plan_view(L), C = coarse_view(S, L);
+  const double* __restrict__ A = L.A;
+  const int64_t n = L.n;
+  const int *__restrict__ keep = L.keep, *__restrict__ slot = L.slot, *__restrict__ stoff = L.stoff,
+            *__restrict__ nstp = L.nst, *__restrict__ segoff = L.segoff, *__restrict__ cutpos = L.cutpos;
+  FTile* __restrict__ tiles = L.tiles;
+  int* __restrict__ st_idx = L.st_idx;
+  T* __restrict__ st_coef = static_cast<T*>(L.st_coef);
+  double *__restrict__ D = L.fD, *__restrict__ DT = L.fDT;
+  uint16_t* __restrict__ idx = L.fidx;
   using GE = Geo<FT>;
   constexpr int kRW = GE::RW, kRH = GE::RH, kRN = GE::RN, kCRW = GE::CRW, kCRH = GE::CRH;
   __shared__ BoxPlan B;
@@ -1242,44 +1359,47 @@ int build_fused(mgfem_ctx* c) {
   const int reach = f32 ? 0 : eta;  // float32 tiles hold no D, whatever eta is
   const char* env = std::getenv("MGFEM_NO_CUT_GROUPS");
   if ((env && env[0] && env[0] != '0') || (!f32 && 4 * eta > kMaxReachX) || c->p.nu2 < 1) return MGFEM_OK;
-  struct Tmp {
-    int nc = 0, nt = 0, nblk = 0;
-    int *cnt, *pos, *bid, *bcell, *npos, *rows, *ncol, *coff, *nval, *voff, *keep, *slot, *nst, *stoff, *nseg, *segoff;
-    FBlock* blocks;
-    int* cols = nullptr;
-    double* D = nullptr;
-  };
-  std::vector<Tmp> tmp(c->lv.size());
-  std::vector<int> ls;
+  std::vector<int> ls;  // the levels, by tile size: 32 x 32 tiles first
   const int64_t max_active = 1 << 19;
-  std::vector<char> in(c->lv.size(), 0);
   for (int l = 0; l < cl; ++l)
-    if (c->lv[l].N <= kMaxPlanN && c->lv[l].n_active <= max_active && !c->lv[l].empty()) {
-      ls.push_back(l);
-      in[l] = 1;
-    }
+    if (c->lv[l].N <= kMaxPlanN && c->lv[l].n_active <= max_active && !c->lv[l].empty()) ls.push_back(l);
   if (ls.empty()) return MGFEM_OK;
+  if (ls.size() > (size_t)kMaxSet) return MGFEM_OK;  // (N <= 2048 has fewer)
+  SetLevels S{};
+  S.n = (int)ls.size();
+  int big = 0;
+  for (int q = 0; q < S.n; ++q) big += tile_nodes(c->lv[ls[q]].N) == 32;
   auto carve = [](char*& p, size_t bytes) {
     char* q = p;
     p += (bytes + 255) & ~(size_t)255;
     return q;
   };
-  int* flags = nullptr;  // two ints per level: columns of the largest block, a record that does not fit
-  // scratch of the plan (freed below): sizes bounded by the level's counts
+  int* tot_dev = nullptr;  // kTot ints per level
+  constexpr int kTot = 16;
+  // scratch of the plan: sizes bounded by the level's counts
   auto layout = [&](char* base) {
     char* p = base;
     auto ints = [&](size_t n) { return reinterpret_cast<int*>(carve(p, n * sizeof(int))); };
-    flags = ints(2 * c->lv.size());
-    for (int l : ls) {
-      Level& L = c->lv[l];
-      Tmp& t = tmp[l];
+    tot_dev = ints(kTot * S.n);
+    for (int q = 0; q < S.n; ++q) {
+      const Level& L = c->lv[ls[q]];
+      SetLevel& t = S.v[q];
+      t.fl = L.flags;
+      t.flc = c->lv[ls[q] + 1].flags;
+      t.A = L.A;
+      t.n = L.n;
+      t.N = L.N;
       t.nc = L.N / kCell + 1;
       t.nt = L.N / tile_nodes(L.N) + 1;
-      const int ncell = t.nc * t.nc, ntile = t.nt * t.nt, cut = std::max(1, L.cut_off[4]);
-      for (int** q : {&t.cnt, &t.pos, &t.bid}) *q = ints(ncell + 1);
-      t.npos = ints(L.n);
-      for (int** q : {&t.bcell, &t.rows, &t.ncol, &t.coff, &t.nval, &t.voff}) *q = ints(cut + 1);
-      for (int** q : {&t.keep, &t.slot, &t.nst, &t.stoff, &t.nseg, &t.segoff}) *q = ints(ntile + 1);
+      t.cut = eta > 0 && !f32 ? L.cut_off[4] : 0;
+      t.coarse = q + 1 < S.n && ls[q + 1] == ls[q] + 1 ? q + 1 : -1;
+      t.cutpos = L.cutpos;
+      t.tot = tot_dev + kTot * q;
+      const int ncell = t.nc * t.nc, ntile = t.nt * t.nt, cut = std::max(1, t.cut);
+      for (int** w : {&t.cnt, &t.pos, &t.bid}) *w = ints(t.cut > 0 ? ncell + 1 : 1);
+      t.npos = ints(t.cut > 0 ? L.n : 1);
+      for (int** w : {&t.bcell, &t.rows, &t.ncol, &t.coff, &t.nval, &t.voff}) *w = ints(cut + 1);
+      for (int** w : {&t.keep, &t.slot, &t.nst, &t.stoff, &t.nseg, &t.segoff}) *w = ints(ntile + 1);
       t.blocks = reinterpret_cast<FBlock*>(carve(p, (size_t)cut * sizeof(FBlock)));
     }
     return (size_t)(p - base);
@@ -1289,95 +1409,77 @@ int build_fused(mgfem_ctx* c) {
   MGFEM_HIP_TRY(scratch.alloc(total));
   layout(scratch.get());
   hipStream_t s = c->s;
-  std::vector<int> tot(8 * c->lv.size(), 0);
-  auto get = [&](int* dst, const int* src) { return hipMemcpyAsync(dst, src, sizeof(int), hipMemcpyDeviceToHost, s); };
-  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, flags, 2 * (int)c->lv.size());
-  if (eta > 0 && !f32) {
-    // cells, positions, blocks
-    for (int l : ls) {
-      Level& L = c->lv[l];
-      Tmp& t = tmp[l];
-      if (L.cut_off[4] == 0) continue;
-      const int ncell = t.nc * t.nc;
-      hipLaunchKernelGGL(k_cell_count, dim3(nblk(ncell, 256)), dim3(256), 0, s, L.flags, L.N, t.nc, t.cnt);
-      hipLaunchKernelGGL(k_scan_cells, dim3(1), dim3(1024), 0, s, t.cnt, ncell, t.pos, t.bid);
-      hipLaunchKernelGGL(k_cell_fill, dim3(nblk(ncell, 256)), dim3(256), 0, s, L.flags, L.N, t.nc, t.pos, t.bid,
-                         t.rows, t.npos, t.bcell);
-      MGFEM_HIP_TRY(get(&tot[8 * l], t.bid + ncell));
-      MGFEM_HIP_TRY(get(&tot[8 * l + 1], t.pos + ncell));
-    }
+  std::vector<int> tot(kTot * S.n, 0);
+  auto totals = [&]() -> int {
     MGFEM_HIP_TRY(hipGetLastError());
+    MGFEM_HIP_TRY(hipMemcpyAsync(tot.data(), tot_dev, tot.size() * sizeof(int), hipMemcpyDeviceToHost, s));
     MGFEM_HIP_TRY(hipStreamSynchronize(s));
-    for (int l : ls) {
-      Tmp& t = tmp[l];
-      t.nblk = tot[8 * l];
-      c->lv[l].fp.ncut = tot[8 * l + 1];
-      if (t.nblk == 0) continue;
-      hipLaunchKernelGGL(k_block_size, dim3(nblk(t.nblk, 256)), dim3(256), 0, s, t.bcell, t.nblk, t.pos, t.nc, eta,
-                         t.ncol, t.nval, flags + 2 * l);
-      hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.ncol, t.nblk, t.coff);
-      hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.nval, t.nblk, t.voff);
-      MGFEM_HIP_TRY(get(&tot[8 * l + 2], t.coff + t.nblk));
-      MGFEM_HIP_TRY(get(&tot[8 * l + 3], t.voff + t.nblk));
+    return MGFEM_OK;
+  };
+  int max_cell = 0, max_tile16 = 0, max_tile32 = 0, max_blk = 0, any_cut = 0;
+  for (int q = 0; q < S.n; ++q) {
+    const SetLevel& t = S.v[q];
+    any_cut |= t.cut > 0;
+    max_cell = std::max(max_cell, t.nc * t.nc);
+    int& m = q < big ? max_tile32 : max_tile16;
+    m = std::max(m, t.nt * t.nt);
+  }
+  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, tot_dev, kTot * S.n);
+  if (any_cut) {
+    // cells, positions, blocks
+    hipLaunchKernelGGL(k_cell_count, dim3(nblk(max_cell, 256), S.n), dim3(256), 0, s, S);
+    hipLaunchKernelGGL(k_scan_cells, dim3(S.n), dim3(1024), 0, s, S);
+    hipLaunchKernelGGL(k_cell_fill, dim3(nblk(max_cell, 256), S.n), dim3(256), 0, s, S);
+    if (const int e = totals()) return e;
+    for (int q = 0; q < S.n; ++q) {
+      S.v[q].nblk = tot[kTot * q];
+      c->lv[ls[q]].fp.ncut = tot[kTot * q + 1];
+      max_blk = std::max(max_blk, S.v[q].nblk);
+    }
+    if (max_blk > 0) {
+      hipLaunchKernelGGL(k_block_size, dim3(nblk(max_blk, 256), S.n), dim3(256), 0, s, S, eta);
+      hipLaunchKernelGGL(k_scan_blocks, dim3(S.n, 2), dim3(1024), 0, s, S);
     }
   }
-  auto view = [&](int l) {
-    const Tmp& t = tmp[l];
-    return PlanLevel{c->lv[l].flags, c->lv[l].N, t.nblk > 0 ? t.npos : nullptr, t.bid, t.nc, t.blocks, t.cols, t.rows,
-                     t.D};
-  };
-  auto coarse_view = [&](int l) {
-    const bool cut = in[l + 1] && tmp[l + 1].nblk > 0;
-    if (cut) return view(l + 1);
-    PlanLevel P{};
-    P.fl = c->lv[l + 1].flags;
-    P.N = c->lv[l + 1].N;
-    return P;
-  };
-  for (int l : ls) {
-    Tmp& t = tmp[l];
-    const int ntile = t.nt * t.nt;
-    auto count = tile_nodes(c->lv[l].N) == 32 ? k_ftile_count<32> : k_ftile_count<16>;
-    hipLaunchKernelGGL(count, dim3(ntile), dim3(256), 0, s, view(l), coarse_view(l), t.nt, reach, t.keep, t.nst, t.nseg,
-                       flags + 2 * l + 1);
-    hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.keep, ntile, t.slot);
-    hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.nst, ntile, t.stoff);
-    hipLaunchKernelGGL(k_scan_plain, dim3(1), dim3(1024), 0, s, t.nseg, ntile, t.segoff);
-    MGFEM_HIP_TRY(get(&tot[8 * l + 4], t.slot + ntile));
-    MGFEM_HIP_TRY(get(&tot[8 * l + 5], t.stoff + ntile));
-    MGFEM_HIP_TRY(get(&tot[8 * l + 6], t.segoff + ntile));
-  }
-  std::vector<int> hf(2 * c->lv.size());
-  MGFEM_HIP_TRY(hipGetLastError());
-  MGFEM_HIP_TRY(hipMemcpyAsync(hf.data(), flags, hf.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  MGFEM_HIP_TRY(hipStreamSynchronize(s));
+  if (big > 0)
+    hipLaunchKernelGGL(k_ftile_count<32>, dim3(max_tile32, big), dim3(256), 0, s, S, 0, reach);
+  if (big < S.n)
+    hipLaunchKernelGGL(k_ftile_count<16>, dim3(max_tile16, S.n - big), dim3(256), 0, s, S, big, reach);
+  hipLaunchKernelGGL(k_scan_tiles, dim3(S.n, 3), dim3(1024), 0, s, S);
+  if (const int e = totals()) return e;
   // a level whose own plan, or whose coarser level's, does not fit keeps the
   // separate kernels (a stored row's record holds its position in 18 bits)
-  for (int l : ls)
-    c->lv[l].fp.ok = hf[2 * l] <= kMaxBlockCols && hf[2 * l + 1] == 0 && c->lv[l].cut_off[4] < (1 << 18);
-  for (size_t q = ls.size(); q-- > 0;)
-    if (in[ls[q] + 1] && !c->lv[ls[q] + 1].fp.ok && tmp[ls[q] + 1].nblk > 0) c->lv[ls[q]].fp.ok = false;
+  for (int q = 0; q < S.n; ++q)
+    c->lv[ls[q]].fp.ok = tot[kTot * q + 8] <= kMaxBlockCols && tot[kTot * q + 9] == 0 &&
+                         c->lv[ls[q]].cut_off[4] < (1 << 18);
+  for (int q = S.n; q-- > 0;)
+    if (S.v[q].coarse >= 0 && !c->lv[ls[q] + 1].fp.ok && S.v[q + 1].nblk > 0) c->lv[ls[q]].fp.ok = false;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_delta_build), hipFuncAttributeMaxDynamicSharedMemorySize,
                             build_lds(kMaxBlockCols));
   // the blocks' values and columns
-  auto block_bytes = [&](int l) {
-    return ((size_t)tot[8 * l + 3] * sizeof(double) + (size_t)tot[8 * l + 2] * sizeof(int) + 255) & ~(size_t)255;
+  auto block_bytes = [&](int q) {
+    return ((size_t)tot[kTot * q + 3] * sizeof(double) + (size_t)tot[kTot * q + 2] * sizeof(int) + 255) & ~(size_t)255;
   };
   size_t all_blocks = 0;
-  for (int l : ls)
-    if (c->lv[l].fp.ok && tmp[l].nblk > 0) all_blocks += block_bytes(l);
+  int max_cols = 0;
+  for (int q = 0; q < S.n; ++q)
+    if (c->lv[ls[q]].fp.ok && S.v[q].nblk > 0) {
+      all_blocks += block_bytes(q);
+      max_cols = std::max(max_cols, tot[kTot * q + 8]);
+    }
   TempMem blocks(c);
   if (all_blocks > 0) MGFEM_HIP_TRY(blocks.alloc(all_blocks));
   char* next_block = blocks.get();
-  for (int l : ls) {
+  for (int q = 0; q < S.n; ++q) {
+    const int l = ls[q];
     Level& L = c->lv[l];
-    Tmp& t = tmp[l];
+    SetLevel& t = S.v[q];
     FusedPlan& F = L.fp;
     if (!F.ok) continue;
-    F.ntiles = tot[8 * l + 4];
+    F.ntiles = tot[kTot * q + 4];
     // the second step carries the reduction of the first one's norm
     if (l == 0 && !f32 && c->p.nu1 >= 2) L.X[2] = c->lam;
-    const size_t nst = (size_t)tot[8 * l + 5], nseg = (size_t)tot[8 * l + 6], v = f32 ? 4 : 8;
+    const size_t nst = (size_t)tot[kTot * q + 5], nseg = (size_t)tot[kTot * q + 6], v = f32 ? 4 : 8;
     char* buf = nullptr;
     MGFEM_HIP_TRY(ctx_alloc(c, reinterpret_cast<void**>(&buf),
                             (size_t)F.ncut * (sizeof(int) + 4 * v) + (size_t)F.ntiles * sizeof(FTile) +
@@ -1386,38 +1488,36 @@ int build_fused(mgfem_ctx* c) {
     F.st_coef = carve(buf, nst * 10 * v);
     F.st_idx = reinterpret_cast<int*>(carve(buf, nst * sizeof(int)));
     F.rows = reinterpret_cast<int*>(carve(buf, (size_t)F.ncut * sizeof(int)));
-    for (double** q : {&F.r[0], &F.r[1], &F.r[2], &F.xs}) *q = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
+    for (double** w : {&F.r[0], &F.r[1], &F.r[2], &F.xs}) *w = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
     if (!f32) {
       F.D = reinterpret_cast<double2*>(carve(buf, nseg * 128));
       F.DT = reinterpret_cast<double2*>(carve(buf, nseg * 128));
     }
     F.Didx = reinterpret_cast<uint4*>(carve(buf, nseg * 32));
+    t.tiles = F.tiles;
+    t.st_idx = F.st_idx;
+    t.st_coef = F.st_coef;
+    t.fD = reinterpret_cast<double*>(F.D);
+    t.fDT = reinterpret_cast<double*>(F.DT);
+    t.fidx = reinterpret_cast<uint16_t*>(F.Didx);
     if (t.nblk == 0) continue;
     MGFEM_HIP_TRY(hipMemcpyAsync(F.rows, t.rows, (size_t)F.ncut * sizeof(int), hipMemcpyDeviceToDevice, s));
     t.D = reinterpret_cast<double*>(next_block);
-    t.cols = reinterpret_cast<int*>(next_block + (size_t)tot[8 * l + 3] * sizeof(double));
-    next_block += block_bytes(l);
-    hipLaunchKernelGGL(k_block_fill, dim3(nblk(t.nblk, 256)), dim3(256), 0, s, t.bcell, t.nblk, t.pos, t.nc, eta,
-                       t.coff, t.voff, t.cols, t.blocks);
-    hipLaunchKernelGGL(k_delta_build, dim3(t.nblk), dim3(64 * kBuildWaves), build_lds(hf[2 * l]), s,
-                       (const FBlock*)t.blocks, (const int*)t.cols, (const int*)t.rows, t.npos, L.flags, L.A, L.n, L.N,
-                       eta, t.D);
+    t.cols = reinterpret_cast<int*>(next_block + (size_t)tot[kTot * q + 3] * sizeof(double));
+    next_block += block_bytes(q);
   }
-  for (int l : ls) {
-    Level& L = c->lv[l];
-    Tmp& t = tmp[l];
-    FusedPlan& F = L.fp;
-    if (!F.ok) continue;
-    auto fill = [&](auto kern, auto zero) {
-      using T = decltype(zero);
-      hipLaunchKernelGGL(kern, dim3(t.nt * t.nt), dim3(256), 0, s, view(l), coarse_view(l), L.A, L.n, t.nt, reach,
-                         t.keep, t.slot, t.stoff, t.nst, t.segoff, F.tiles, F.st_idx, static_cast<T*>(F.st_coef),
-                         (const int*)L.cutpos, reinterpret_cast<double*>(F.D), reinterpret_cast<double*>(F.DT),
-                         reinterpret_cast<uint16_t*>(F.Didx));
-    };
-    const bool big = tile_nodes(L.N) == 32;
-    if (f32) big ? fill(k_ftile_fill<float, 32>, 0.0f) : fill(k_ftile_fill<float, 16>, 0.0f);
-    else big ? fill(k_ftile_fill<double, 32>, 0.0) : fill(k_ftile_fill<double, 16>, 0.0);
+  if (all_blocks > 0) {
+    hipLaunchKernelGGL(k_block_fill, dim3(nblk(max_blk, 256), S.n), dim3(256), 0, s, S, eta);
+    hipLaunchKernelGGL(k_delta_build, dim3(max_blk, S.n), dim3(64 * kBuildWaves), build_lds(max_cols), s, S, eta);
+  }
+  if (big > 0) {
+    if (f32) hipLaunchKernelGGL((k_ftile_fill<float, 32>), dim3(max_tile32, big), dim3(1024), 0, s, S, 0, reach);
+    else hipLaunchKernelGGL((k_ftile_fill<double, 32>), dim3(max_tile32, big), dim3(1024), 0, s, S, 0, reach);
+  }
+  if (big < S.n) {
+    const dim3 g(max_tile16, S.n - big);
+    if (f32) hipLaunchKernelGGL((k_ftile_fill<float, 16>), g, dim3(1024), 0, s, S, big, reach);
+    else hipLaunchKernelGGL((k_ftile_fill<double, 16>), g, dim3(1024), 0, s, S, big, reach);
   }
   MGFEM_HIP_TRY(hipGetLastError());
   MGFEM_HIP_TRY(hipStreamSynchronize(s));  // the scratch goes
