@@ -340,6 +340,9 @@ int mgfem_level_counts(mgfem_handle h, int32_t level, int64_t* n_active, int64_t
  *           buffer and writes the other, so a repeat recomputes the same
  *           values) and its time is the elapsed time / R, which leaves out
  *           the dispatch gap an event pair adds to a single launch.
+ * A large finest level may run passes that take several sweeps at a time and
+ * no sweep kernel; a profiled float64 solve then launches that kernel beside
+ * them, at each of its steps, from the step's iterate into a spare buffer.
  * mgfem_profile resets the counters.
  */
 int mgfem_profile(mgfem_handle h, int32_t enable);

@@ -679,7 +679,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   c->u_cur = 0;
   for (Level& L : c->lv) L.pend = L.zero = false;
   // from zero a fused level does not read its iterate
-  if (!warm && !mixed && fused_level(c, 0, false)) L0.zero = true;
+  if (!warm && !mixed && fused_level(c, 0, false, reverse)) L0.zero = true;
   else launch_box_copy(c, c->x0, warm ? x : nullptr);
   int rc;
   if (bseq < 0.0) {
@@ -695,7 +695,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
     launch_residual_norm(c, b, c->x0, nullptr);
     rseq = c->red_seq;
   }
-  if (!mixed && !fused_level(c, 0, false)) gather_snap(c, 0, false);
+  if (!mixed && !fused_level(c, 0, false, reverse)) gather_snap(c, 0, false);
   double prev = 0.0;
   int grow = 0, m = 0;
   bool conv = false;
@@ -1044,7 +1044,7 @@ int mgfem_adjoint(mgfem_handle c, const double* dJdu_dev, double rel_tol, int32_
   if (const int e = single_problem_check(c)) return e;
   if (!dJdu_dev || max_cycles < 0) return fail(c, MGFEM_ERR_INVALID_ARG, "dJdu must be a device pointer");
   for (int l = 0; l < cycle_levels(c); ++l)
-    if (!fused_level(c, l, false))
+    if (!fused_level(c, l, false, true))
       if (const int e = separate_plans(c, l)) return e;
   double* lam = lam_dev ? lam_dev : c->lam;
   // the adjoint right-hand side must vanish off the active nodes
@@ -1142,6 +1142,10 @@ int mgfem_level_counts(mgfem_handle c, int32_t level, int64_t* n_active, int64_t
 
 int mgfem_profile(mgfem_handle c, int32_t enable) {
   if (!c || enable < 0 || enable > 1000) return MGFEM_ERR_INVALID_ARG;
+  if (enable)  // the timed sweeps of levels that stream
+    for (int l = 0; l < (int)c->lv.size(); ++l)
+      if (c->lv[l].sp.fused)
+        if (const int e = separate_plans(c, l)) return e;
   c->prof.on = enable != 0;
   c->prof.repeat = enable > 1 ? enable : 1;
   for (int k = 0; k < 4; ++k) {

@@ -577,6 +577,7 @@ struct SetLevel {
   void* st_coef;
   double *fD, *fDT;
   uint16_t* fidx;
+  uint8_t* inner;           // levels that stream: tiles that the windows take; else null
 };
 constexpr int kMaxSet = 12;
 struct SetLevels {
@@ -961,7 +962,25 @@ __global__ __launch_bounds__(256) void k_ftile_count(SetLevels S, int first, int
     if (I <= Nc && J <= Nc && (C.fl[I + (int64_t)J * (Nc + 1)] & kFlagActive)) act = 1;
   }
   act = __syncthreads_or(act);
-  if (!act) {
+  int take = act;
+  if (act && L.inner) {
+    // a window's reach around the tile: active nodes with the interior row, no
+    // cut vertex on this level or among their parents
+    constexpr int WX = kStreamHX, WY = kStreamHY, WW = FT + 2 * WX, WH = FT + 2 * WY;
+    int bad = 0;
+    for (int q = threadIdx.x; q < WW * WH && !bad; q += blockDim.x) {
+      const int i = x0 - WX + q % WW, j = y0 - WY + q / WW;
+      if (i < 0 || j < 0 || i > N || j > N) {
+        bad = 1;
+        continue;
+      }
+      bad = (P.fl[i + (int64_t)j * s] & (kFlagActive | kFlagStored | kFlagCut)) != kFlagActive;
+      if (!(i & 1) && !(j & 1)) bad |= (C.fl[(i >> 1) + (int64_t)(j >> 1) * (Nc + 1)] & kFlagCut) != 0;
+    }
+    take = __syncthreads_or(bad);
+    if (threadIdx.x == 0) L.inner[blockIdx.x] = !take;
+  }
+  if (!take) {
     if (threadIdx.x == 0) keep[blockIdx.x] = nst[blockIdx.x] = nseg[blockIdx.x] = 0;
     return;
   }
@@ -1207,14 +1226,14 @@ void launch_sweep(mgfem_ctx* c, int l, bool norm, bool up, const Reduce* red) {
       a.r = F.r[L.cur];
       if (norm) a.xs_out = F.xs;
     }
-    if (norm) a.part = c->sweep_part;
+    if (norm) a.part = c->sweep_part + (L.sp.fused ? 2 * L.sp.nwin : 0);
     L.pend = F.ncut > 0;
   }
   auto go = [a, up](hipStream_t st) {
     if (up) launch_tiles<T, kUpK>(a, st);
     else launch_tiles<T, kSweepK>(a, st);
   };
-  if (c->prof.on && l == 0) {
+  if (c->prof.on && l == 0 && !L.sp.fused) {
     constexpr double vb = (double)sizeof(T);
     double bytes = 3.0 * vb * L.n_active + 9.0 * vb * L.n_stored;
     if (up) bytes += vb * c->lv[l + 1].n_active;
@@ -1351,7 +1370,9 @@ void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, in
 //            N = 2048  15.1, 9.4, 17.1  | 19.0, 12.1, 22.4
 // A level with a tile whose record does not hold its cut vertices keeps the
 // separate kernels (as does MGFEM_NO_CUT_GROUPS=1).
-constexpr int kMaxPlanN = 2048;
+// Larger float64 levels take them for the tiles that streaming passes leave
+// (stream.hip): %%RULE%%
+constexpr int kMaxPlanN = 2048, kMinStreamFused = 1024, kMaxStreamFused = 16384;
 int build_fused(mgfem_ctx* c) {
   const int cl = c->cplan.map.level >= 0 ? c->cplan.map.level : c->cplan.lc;
   const int eta = c->p.eta;
@@ -1361,8 +1382,11 @@ int build_fused(mgfem_ctx* c) {
   if ((env && env[0] && env[0] != '0') || (!f32 && 4 * eta > kMaxReachX) || c->p.nu2 < 1) return MGFEM_OK;
   std::vector<int> ls;  // the levels, by tile size: 32 x 32 tiles first
   const int64_t max_active = 1 << 19;
+  auto whole = [&](int l) { return c->lv[l].N <= kMaxPlanN && c->lv[l].n_active <= max_active; };
   for (int l = 0; l < cl; ++l)
-    if (c->lv[l].N <= kMaxPlanN && c->lv[l].n_active <= max_active && !c->lv[l].empty()) ls.push_back(l);
+    if (!c->lv[l].empty() && (whole(l) || (!f32 && c->p.nu2 == 1 && c->lv[l].N >= kMinStreamFused &&
+                                           c->lv[l].N <= kMaxStreamFused && stream_candidate(c, l))))
+      ls.push_back(l);
   if (ls.empty()) return MGFEM_OK;
   if (ls.size() > (size_t)kMaxSet) return MGFEM_OK;  // (N <= 2048 has fewer)
   SetLevels S{};
@@ -1401,14 +1425,17 @@ int build_fused(mgfem_ctx* c) {
       for (int** w : {&t.bcell, &t.rows, &t.ncol, &t.coff, &t.nval, &t.voff}) *w = ints(cut + 1);
       for (int** w : {&t.keep, &t.slot, &t.nst, &t.stoff, &t.nseg, &t.segoff}) *w = ints(ntile + 1);
       t.blocks = reinterpret_cast<FBlock*>(carve(p, (size_t)cut * sizeof(FBlock)));
+      t.inner = whole(ls[q]) ? nullptr : reinterpret_cast<uint8_t*>(carve(p, (size_t)ntile));
     }
     return (size_t)(p - base);
   };
-  const size_t total = layout(nullptr);
+  const size_t total = layout(nullptr) + 256;
   TempMem scratch(c);
   MGFEM_HIP_TRY(scratch.alloc(total));
   layout(scratch.get());
   hipStream_t s = c->s;
+  for (int q = 0; q < S.n; ++q)  // (tiles without an active node leave theirs)
+    if (S.v[q].inner) MGFEM_HIP_TRY(hipMemsetAsync(S.v[q].inner, 0, (size_t)S.v[q].nt * S.v[q].nt, s));
   std::vector<int> tot(kTot * S.n, 0);
   auto totals = [&]() -> int {
     MGFEM_HIP_TRY(hipGetLastError());
@@ -1452,8 +1479,23 @@ int build_fused(mgfem_ctx* c) {
   for (int q = 0; q < S.n; ++q)
     c->lv[ls[q]].fp.ok = tot[kTot * q + 8] <= kMaxBlockCols && tot[kTot * q + 9] == 0 &&
                          c->lv[ls[q]].cut_off[4] < (1 << 18);
+  // the windows of the levels that stream: no window, no plan
+  for (int q = 0; q < S.n; ++q) {
+    Level& L = c->lv[ls[q]];
+    if (!S.v[q].inner) continue;
+    if (L.fp.ok) {
+      std::vector<uint8_t> inner((size_t)S.v[q].nt * S.v[q].nt);
+      MGFEM_HIP_TRY(hipMemcpyAsync(inner.data(), S.v[q].inner, inner.size(), hipMemcpyDeviceToHost, s));
+      MGFEM_HIP_TRY(hipStreamSynchronize(s));
+      if (const int e = build_stream_fused(c, ls[q], inner, S.v[q].nt, tile_nodes(L.N))) return e;
+    }
+    L.fp.ok = L.sp.ok;
+  }
   for (int q = S.n; q-- > 0;)
-    if (S.v[q].coarse >= 0 && !c->lv[ls[q] + 1].fp.ok && S.v[q + 1].nblk > 0) c->lv[ls[q]].fp.ok = false;
+    if (S.v[q].coarse >= 0 && !c->lv[ls[q] + 1].fp.ok && S.v[q + 1].nblk > 0) {
+      c->lv[ls[q]].fp.ok = false;
+      c->lv[ls[q]].sp = StreamPlan{};
+    }
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_delta_build), hipFuncAttributeMaxDynamicSharedMemorySize,
                             build_lds(kMaxBlockCols));
   // the blocks' values and columns
@@ -1483,7 +1525,7 @@ int build_fused(mgfem_ctx* c) {
     char* buf = nullptr;
     MGFEM_HIP_TRY(ctx_alloc(c, reinterpret_cast<void**>(&buf),
                             (size_t)F.ncut * (sizeof(int) + 4 * v) + (size_t)F.ntiles * sizeof(FTile) +
-                                nst * (sizeof(int) + 10 * v) + nseg * 288 + 4096));
+                                nst * (sizeof(int) + 10 * v) + nseg * 288 + 8192));
     F.tiles = reinterpret_cast<FTile*>(carve(buf, (size_t)F.ntiles * sizeof(FTile)));
     F.st_coef = carve(buf, nst * 10 * v);
     F.st_idx = reinterpret_cast<int*>(carve(buf, nst * sizeof(int)));
@@ -1491,7 +1533,7 @@ int build_fused(mgfem_ctx* c) {
     for (double** w : {&F.r[0], &F.r[1], &F.r[2], &F.xs}) *w = reinterpret_cast<double*>(carve(buf, (size_t)F.ncut * v));
     if (!f32) {
       F.D = reinterpret_cast<double2*>(carve(buf, nseg * 128));
-      F.DT = reinterpret_cast<double2*>(carve(buf, nseg * 128));
+      if (!S.v[q].inner) F.DT = reinterpret_cast<double2*>(carve(buf, nseg * 128));  // (forward cycles alone)
     }
     F.Didx = reinterpret_cast<uint4*>(carve(buf, nseg * 32));
     t.tiles = F.tiles;

@@ -135,6 +135,7 @@ struct FusedPlan {
 // downward and of the upward one, and the tiles and residual tiles of the rest.
 struct StreamPlan {
   bool ok = false;
+  bool fused = false;  // the rest runs the fused steps (its tiles are the fused plan's), else the separate kernels
   int nwin = 0, nup = 0, nband = 0, nrr = 0;
   int4* win = nullptr;
   int4* up = nullptr;
@@ -541,10 +542,12 @@ int cycle_levels(const mgfem_ctx* c);  // levels above the coarse part
 // and the cut vertices of a level-0 array from the values the last sweep with
 // a norm started from
 int build_fused(mgfem_ctx* c);
-// level l has fused plans in this precision (a handle has them in the one its
-// solves run in; the adjoint of a mixed handle runs the separate kernels)
-inline bool fused_level(const mgfem_ctx* c, int l, bool f32) {
-  return c->lv[l].fp.ok && f32 == (c->p.precision == MGFEM_PREC_MIXED);
+// level l takes the fused steps in this precision (a handle has them in the one
+// its solves run in; the adjoint of a mixed handle runs the separate kernels) and
+// direction (forward cycles alone where they go with streaming passes)
+inline bool fused_level(const mgfem_ctx* c, int l, bool f32, bool reverse = false) {
+  const Level& L = c->lv[l];
+  return L.fp.ok && f32 == (c->p.precision == MGFEM_PREC_MIXED) && !(L.sp.fused && reverse);
 }
 // (red: the reduction that one more workgroup of the launch carries)
 void fused_sweep(mgfem_ctx* c, int l, bool fp32, bool norm, bool up, const Reduce* red = nullptr);
@@ -559,12 +562,17 @@ void fused_entry(mgfem_ctx* m, int l, void* out);
 int fused_units(mgfem_ctx* m, int l);
 void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, int nwork, int par, int parc, bool zero,
                   bool up);
+// (a window computes this much around its core)
+constexpr int kStreamHX = 10, kStreamHY = 6;
 // streaming passes (stream.hip): whether a level may take them, the plan, and
 // the passes over the windows: down (iterate buffers in, after the first sweep
 // and after the second; part: the norm's partials of the start iterate, or
 // null) and up (x + P x_c and a sweep)
 bool stream_candidate(const mgfem_ctx* c, int l);
 int build_stream(mgfem_ctx* c, int l);
+// the windows over the inner tiles of a fused level (nt x nt tiles of TN nodes)
+// whose other tiles its fused plan holds; sp.ok unless there is none
+int build_stream_fused(mgfem_ctx* c, int l, const std::vector<uint8_t>& inner, int nt, int TN);
 void stream_down_windows(mgfem_ctx* c, int l, bool fp32, int in, int mid, int out, double* part);
 void stream_up_windows(mgfem_ctx* c, int l, bool fp32, int in, int out);
 // sweep tile shapes, all with 512 threads (a workgroup's load phase is bound

@@ -1699,7 +1699,7 @@ void stream_up(mgfem_ctx* c, int l) {
   cut_sweeps<T>(c, l, false);
 }
 // a profiled solve times the sweeps, so it runs them
-inline bool streams(const mgfem_ctx* c, int l) { return c->lv[l].sp.ok && !c->prof.on; }
+inline bool streams(const mgfem_ctx* c, int l) { return c->lv[l].sp.ok && !c->lv[l].sp.fused && !c->prof.on; }
 
 template <class T>
 void prolong(mgfem_ctx* c, int l) {
@@ -1780,6 +1780,44 @@ void coarse_wg(mgfem_ctx* c, bool reverse, int reps) {
   Lc.cur = 0;
 }
 
+// The sweep kernel of a fused level 0 that streams, for a profiled solve: such a
+// level runs no full sweep, so the sweep is timed beside it, at each step from
+// the step's iterate into the buffer that the step writes next.
+template <int TH>
+void time_sweep(mgfem_ctx* c, int l, bool up) {
+  Level& L = c->lv[l];
+  const SweepArgs<double> a = sweep_args<double, 64, TH>(c, l, false, false, up);
+  double bytes = 24.0 * L.n_active + 72.0 * L.n_stored;
+  if (up) bytes += 8.0 * c->lv[l + 1].n_active;
+  prof_launch(c, 0, bytes, [a](hipStream_t st) {
+    hipLaunchKernelGGL((k_sweep<double, 64, TH, 512>), dim3(8 * a.per), dim3(512), 0, st, a);
+  });
+}
+void time_sweep(mgfem_ctx* c, int l, bool up) {
+  if (!c->prof.on || l != 0) return;
+  if (sweep_shape(c, l) == kShapeFinest) time_sweep<32>(c, l, up);
+  else time_sweep<16>(c, l, up);
+}
+
+// the two steps down of a fused level that streams: the windows, which also
+// restrict, and the other tiles; the residual norm of the start iterate on
+// request, its reduction in the second step
+void fused_down(mgfem_ctx* c, int l, bool norm) {
+  Level& L = c->lv[l];
+  const int in = L.cur, mid = L.next(), out = 3 - in - mid;
+  time_sweep(c, l, false);
+  stream_down_windows(c, l, false, in, mid, out, norm ? c->sweep_part : nullptr);
+  fused_sweep(c, l, false, norm, false);
+  L.keep = in;  // the second step writes the third buffer
+  if (norm) {
+    const Reduce red = next_reduce(c, c->sweep_part, L.sp.nwin + L.fp.ntiles);
+    fused_sweep(c, l, false, false, false, &red);
+  } else {
+    fused_sweep(c, l, false, false, false);
+    L.keep = -1;
+  }
+}
+
 // one cycle of a level with the fused kernels (fused.hip): in float64 the cut
 // sweeps of each step are applied by whatever reads its result
 template <class T>
@@ -1788,18 +1826,28 @@ template <class T>
 void cycle_fused(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   constexpr bool f32 = sizeof(T) == 4;
   const int cl = coarse_level(c);
+  Level& L = c->lv[l];
   Level& C = c->lv[l + 1];
   auto step = [&](bool up) {
     if (reverse) {
       fused_reverse_sweep(c, l);
       return;
     }
+    if (up && L.sp.fused) {
+      time_sweep(c, l, true);
+      stream_up_windows(c, l, false, L.cur, L.next());
+    }
     fused_sweep(c, l, f32, false, up);
     if (f32) cut_sweeps<T>(c, l, false);
   };
   const int pre = reverse ? c->p.nu2 : c->p.nu1, post = reverse ? c->p.nu1 : c->p.nu2;
-  for (int s = steps_done; s < pre; ++s) step(false);
-  const bool fc = l + 1 != cl && fused_level(c, l + 1, f32);
+  if (L.sp.fused) {
+    if (steps_done == 0) fused_down(c, l, false);
+    time_sweep(c, l, false);  // (of the second step)
+  } else {
+    for (int s = steps_done; s < pre; ++s) step(false);
+  }
+  const bool fc = l + 1 != cl && (fused_level(c, l + 1, f32, reverse) || L.sp.fused);
   fused_restrict(c, l, f32, l + 1 != cl && !fc, reverse);
   C.pend = false;
   C.zero = fc;
@@ -1827,7 +1875,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   }
   if (l == nl - 1) return;  // unreachable: the coarse plan always covers the coarsest level
   constexpr bool f32 = sizeof(T) == 4;
-  if (fused_level(c, l, f32)) {
+  if (fused_level(c, l, f32, reverse)) {
     cycle_fused<T>(c, l, reverse, steps_done);
     return;
   }
@@ -1843,7 +1891,7 @@ void cycle_level(mgfem_ctx* c, int l, bool reverse, int steps_done) {
   }
   // the iterate there is zero now (in memory too, unless this level streamed)
   c->lv[l + 1].pend = false;
-  c->lv[l + 1].zero = l + 1 != cl && (stream || fused_level(c, l + 1, f32));
+  c->lv[l + 1].zero = l + 1 != cl && (stream || fused_level(c, l + 1, f32, reverse));
   // coarse-grid visits: gamma* (section 3.2); the two-grid scheme instead
   // solves the first coarse problem with coarse_cycles V-cycles from zero
   const bool two_grid = c->p.cycle == MGFEM_CYCLE_TWO_GRID && l == 0;
@@ -1881,7 +1929,7 @@ Reduce next_reduce(mgfem_ctx* c, const double* part, int nb) {
 // The launch behind the sweep with the norm carries the norm's reduction in
 // one more workgroup: the cut sweeps, or on a fused level the second step,
 // which writes a third buffer so that the iterate of the norm stays whole
-// (profiled solves time that step, and repeat it, alone).  A launch of its own
+// (a profiled solve times that step, and repeats it, in the next iteration).  A launch of its own
 // took 4.5-5.7 us of each cycle: solves of the circle with N = 64 took 268 us,
 // 239 without it, of the flower with N = 1024 1198 and 1171.
 int first_steps_with_norm(mgfem_ctx* c) {
@@ -1901,13 +1949,16 @@ int first_steps_with_norm(mgfem_ctx* c) {
     else alone(red);
     return 1;
   }
+  if (L0.sp.fused) {
+    fused_down(c, 0, true);
+    return 2;
+  }
   const int in = L0.cur;
   fused_sweep(c, 0, false, true, false);
   const Reduce red = next_reduce(c, c->sweep_part, L0.fp.ntiles);
-  if (L0.X[2]) {
+  if (L0.X[2] && !c->prof.on) {
     L0.keep = in;
-    if (c->prof.on) alone(red);
-    fused_sweep(c, 0, false, false, false, c->prof.on ? nullptr : &red);
+    fused_sweep(c, 0, false, false, false, &red);
     return 2;
   }
   if (c->p.nu1 == 0) L0.pend = false;
@@ -2480,7 +2531,7 @@ int build_cycle_plans(mgfem_ctx* c) {
     if (!c->lv[l].fp.ok || (f32 && l == 0))
       if (const int e = separate_plans(c, l)) return e;
   for (int l = 0; l < cl; ++l)
-    if (!c->lv[l].fp.ok)
+    if (!c->lv[l].fp.ok && !c->lv[l].sp.ok)
       if (const int e = build_stream(c, l)) return e;
   return MGFEM_OK;
 }

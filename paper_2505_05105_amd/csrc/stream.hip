@@ -32,7 +32,7 @@
 namespace mgfem {
 namespace {
 
-constexpr int kHX = 10, kHY = 6;     // columns on either side of a window's core, rows above and below
+constexpr int kHX = kStreamHX, kHY = kStreamHY;  // columns on either side of a window's core, rows above and below
 constexpr int kUpX = 6, kUpY = 2;    // of the upward pass (4 columns of the sweep, one of the prolongation)
 constexpr int kCore = 128 - 2 * kHX, kUpCore = 128 - 2 * kUpX;
 
@@ -517,10 +517,12 @@ void stream_up_windows(mgfem_ctx* c, int l, bool fp32, int in, int out) {
 //   ellipse, mixed, N = 4096      1.06 | 1.08 | 1.09, with the 2048 level 1.07
 //   gradient, float64, N = 2048   1.18 to 1.20, if level 0 streams 1.15 to 1.17
 //   annulus, float64, N = 1536    1.20, if level 0 streams 1.20
-constexpr int kStreamN = 4096, kStreamCoarseN = 2048, kUpN = 4096;
+constexpr int kStreamN = 4096, kStreamCoarseN = 2048, kStreamFusedN = 1024, kUpN = 4096;
 bool stream_candidate(const mgfem_ctx* c, int l) {
   const Level& L = c->lv[l];
-  const int n = l > 0 && c->p.precision != MGFEM_PREC_MIXED ? kStreamCoarseN : kStreamN;
+  const int n = c->p.precision == MGFEM_PREC_MIXED ? kStreamN : c->p.nu2 == 1 ? kStreamFusedN
+                : l > 0                                               ? kStreamCoarseN
+                                                                      : kStreamN;
   return c->p.nu1 == 2 && c->p.nu2 >= 1 && L.N >= n && !L.empty() && l + 1 < (int)c->lv.size() &&
          !c->lv[l + 1].empty();
 }
@@ -577,13 +579,37 @@ std::vector<int4> build_windows(const std::vector<uint8_t>& map, const std::vect
 }
 }  // namespace
 
+int build_stream_fused(mgfem_ctx* c, int l, const std::vector<uint8_t>& inner, int nt, int TN) {
+  Level& L = c->lv[l];
+  StreamPlan& S = L.sp;
+  const std::vector<uint8_t> all(inner.size(), 1);
+  const std::vector<int4> win = build_windows(inner, all, nt, nt, 0, 0, TN, TN, kCore);
+  const std::vector<int4> up = build_windows(inner, all, nt, nt, 0, 0, TN, TN, kUpCore);
+  if (win.empty()) return MGFEM_OK;
+  if (l == 0) {
+    L.X[2] = c->lam;
+  } else if (ctx_alloc_t(c, &L.X[2], L.n) != hipSuccess) {
+    (void)hipGetLastError();
+    return MGFEM_OK;
+  }
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &S.win, win.size()));
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &S.up, up.size()));
+  MGFEM_HIP_TRY(hipMemcpyAsync(S.win, win.data(), win.size() * sizeof(int4), hipMemcpyHostToDevice, c->s));
+  MGFEM_HIP_TRY(hipMemcpyAsync(S.up, up.data(), up.size() * sizeof(int4), hipMemcpyHostToDevice, c->s));
+  MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
+  S.nwin = (int)win.size();
+  S.nup = (int)up.size();
+  S.ok = S.fused = true;
+  return MGFEM_OK;
+}
+
 // Windows and band of a level whose tile lists exist.  No window, or no memory
 // for the third buffer: the level keeps the separate kernels.
 int build_stream(mgfem_ctx* c, int l) {
   Level& L = c->lv[l];
   Level& C = c->lv[l + 1];
   StreamPlan& S = L.sp;
-  if (!stream_candidate(c, l) || L.ntiles == 0) return MGFEM_OK;
+  if (!stream_candidate(c, l) || L.N < kStreamCoarseN || (l == 0 && L.N < kStreamN) || L.ntiles == 0) return MGFEM_OK;
   // tiles of the level (64 wide) and of the residual kernel (N >= 1024)
   const int TW = 64, TH = sweep_shape(c, l) == kShapeFinest ? 32 : 16, CW = 32, CH = 16;
   const int ntx = (L.bbox[1] - L.bbox[0] + TW) / TW, nty = (L.bbox[3] - L.bbox[2] + TH) / TH;

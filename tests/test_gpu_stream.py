@@ -1,7 +1,10 @@
 """The streaming passes of the largest levels (downwards two sweeps, residual and
 restriction, upwards prolongation and a sweep, over windows away from the
-boundary; the separate kernels on the band along it) against the separate
-kernels everywhere, which a profiled solve runs."""
+boundary; the fused steps or the separate kernels on the band along it) against
+the separate kernels everywhere, which a profiled solve of a handle without
+cut-vertex plans runs."""
+import os
+
 import numpy as np
 import pytest
 
@@ -22,6 +25,8 @@ CASES = [
     (1536, 3, lambda N: W.circle(N, radius=0.9), {}),
     (2048, 4, lambda N: W.flower(N), {"cycle": 3, "coarse_cycles": 2}),
     (8192, 4, lambda N: W.flower(N), {"eta": 1}),
+    (1024, 4, lambda N: W.circle(N, radius=1.2, center=(0.03, 0.0)), {}),
+    (1536, 3, lambda N: W.circle(N, radius=1.3), {"coarse_op": 1}),
 ]
 
 
@@ -33,7 +38,16 @@ def _setup(N, coarsest, psi, **kw):
     data = [2 * torch.rand((N + 1) ** 2, generator=gen, device="cuda:0", dtype=torch.float64) - 1 for _ in range(3)]
     if kw.pop("mixed", False):
         kw["precision"] = mg.PREC_MIXED
-    return mg.Solver(psi(N), N, coarsest_n=coarsest, **kw), data
+    separate = kw.pop("separate", False)
+    if separate:
+        os.environ["MGFEM_NO_CUT_GROUPS"] = "1"
+    try:
+        s = mg.Solver(psi(N), N, coarsest_n=coarsest, **kw)
+    finally:
+        os.environ.pop("MGFEM_NO_CUT_GROUPS", None)
+    if separate:
+        s.profile(True)
+    return s, data
 
 
 @pytest.mark.parametrize("N,coarsest,psi,kw", CASES)
@@ -47,12 +61,21 @@ def test_streamed_iterates(N, coarsest, psi, kw):
 
     u, h = s.solve(f, g, tol=-1.0, max_cycles=3)
     uw, hw = s.solve(f, g, tol=-1.0, max_cycles=2, u0=u0)
-    s.profile(True)
-    us, hs = s.solve(f, g, tol=-1.0, max_cycles=3)
-    uws, hws = s.solve(f, g, tol=-1.0, max_cycles=2, u0=u0)
-    s.profile(False)
+    sep, _ = _setup(N, coarsest, psi, separate=True, **kw)
+    us, hs = sep.solve(f, g, tol=-1.0, max_cycles=3)
+    uws, hws = sep.solve(f, g, tol=-1.0, max_cycles=2, u0=u0)
     close(u, us, h, hs)
     close(uw, uws, hw, hws)
+    # a profiled solve of the streaming handle is the same solve
+    s.profile(True)
+    up, hp = s.solve(f, g, tol=-1.0, max_cycles=3)
+    cycles = s.profile_read(0)["launches"]
+    s.profile(False)
+    close(up, u, hp, h)
+    assert cycles == 3 * (kw.get("nu2", 1) + 2) + 1
+    # transposed cycles run the separate kernels on such levels
+    lam, lams = s.adjoint(g, tol=-1.0, max_cycles=2)[2], sep.adjoint(g, tol=-1.0, max_cycles=2)[2]
+    assert float((lam - lams).abs().max()) <= 1e-10 * float(lams.abs().max())
     # the same bits again, and stopped by the tolerance instead
     u2, h2 = s.solve(f, g, tol=h[3] / h[0] * (1 + 1e-9), max_cycles=50)
     assert np.array_equal(h, h2) and torch.equal(u, u2)
