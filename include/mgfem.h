@@ -349,7 +349,9 @@ int mgfem_profile(mgfem_handle h, int32_t enable);
 int mgfem_profile_read(mgfem_handle h, int32_t kernel_class, int64_t* launches, double* total_ms,
                        double* alg_bytes);
 
-/* Release the handle and all of its device memory. */
+/* Release the handle and its device memory.  The block that most of its arrays
+ * share (up to 6 GB) may stay for the next handle of the same size, one block per
+ * device: a set-up of another size or one that runs out of memory frees it. */
 int mgfem_destroy(mgfem_handle h);
 
 /* Static text for a status code. */

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <chrono>
+#include <mutex>
 #include <new>
 
 #include "mgfem_internal.h"
@@ -56,6 +57,103 @@ int check_params(const mgfem_params& p, int N, std::string& why) {
 namespace mgfem {
 void set_setup_error(const std::string& msg) { g_setup_error = msg; }
 
+// The first chunk of the last handle released on a device waits here for a
+// set-up that wants one of the same size.  The driver clears freed memory in the
+// background, and once some 150 GB have been freed without a pause every further
+// hipMalloc or hipFree waits for it (a loop over 3 GB: 2.7 ms a pass for the
+// first 49, then 90 ms), which the set-ups of a moving interface run into.  Set-up,
+// solve and release: N = 3072 11 ms and later 92, with the kept block 7.9; N = 1024
+// 5.0, with it 4.3.  One block per device, kPoolMin to
+// kFirstChunk bytes; a set-up that wants another size and an allocation that
+// fails give it back.
+constexpr size_t kPoolMin = (size_t)16 << 20, kFirstChunk = (size_t)6 << 30;
+struct Pool {
+  struct Block {
+    int device;
+    void* p;
+    size_t bytes;
+  };
+  std::mutex m;
+  std::vector<Block> blocks;
+  // the device's block out of the pool (null: none)
+  Block take(int device) {
+    std::lock_guard<std::mutex> lock(m);
+    for (size_t i = 0; i < blocks.size(); ++i)
+      if (blocks[i].device == device) {
+        const Block b = blocks[i];
+        blocks.erase(blocks.begin() + i);
+        return b;
+      }
+    return Block{device, nullptr, 0};
+  }
+  // keeps a block nothing uses any more; one that was there is released
+  void put(const Block& b) {
+    const Block old = take(b.device);
+    if (old.p) (void)hipFree(old.p);
+    {
+      std::lock_guard<std::mutex> lock(m);
+      bool there = false;
+      for (const Block& o : blocks) there |= o.device == b.device;
+      if (!there) {
+        blocks.push_back(b);
+        return;
+      }
+    }
+    (void)hipFree(b.p);  // another thread's came between
+  }
+};
+static Pool& pool() {
+  static Pool* const p = new Pool;  // (stays: the runtime may be gone before static objects are)
+  return *p;
+}
+// device memory; where there is none left, after the pool's block is released
+static hipError_t dev_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  int device = 0;
+  if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess) {
+    const Pool::Block b = pool().take(device);
+    if (b.p) {
+      (void)hipGetLastError();
+      (void)hipFree(b.p);
+      e = hipMalloc(p, bytes);
+    }
+  }
+  return e;
+}
+// a handle's first chunk: the pool's block of that size or new memory
+static hipError_t first_chunk(mgfem_ctx* c, void** p, size_t bytes) {
+  int device = 0;
+  if (bytes >= kPoolMin && bytes <= kFirstChunk && hipGetDevice(&device) == hipSuccess) {
+    const Pool::Block b = pool().take(device);
+    if (b.p && b.bytes != bytes) {
+      (void)hipFree(b.p);
+    } else if (b.p) {
+      *p = b.p;
+      c->pool_bytes = bytes;
+      c->pool_device = device;
+      return hipSuccess;
+    }
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) {
+      c->pool_bytes = bytes;
+      c->pool_device = device;
+    }
+    return e;
+  }
+  return dev_malloc(p, bytes);
+}
+static void free_allocs(mgfem_ctx* c) {
+  int device = -1;
+  if (c->pool_bytes > 0) (void)hipGetDevice(&device);
+  for (size_t i = 0; i < c->allocs.size(); ++i) {
+    // (hipFree waits for the device's work, and so does this)
+    if (i == 0 && c->pool_bytes > 0 && device == c->pool_device && hipDeviceSynchronize() == hipSuccess)
+      pool().put(Pool::Block{c->pool_device, c->allocs[0], c->pool_bytes});
+    else
+      (void)hipFree(c->allocs[i]);
+  }
+}
+
 // A handle holds some 300 arrays, most of them small; a hipMalloc, its fill
 // and its hipFree cost about 40 us each, and a hipFree of anything from 48 MB
 // 250 us whatever its size (a hipMalloc 140 to 300 us up to 48 MB, 35 us from
@@ -64,14 +162,14 @@ void set_setup_error(const std::string& msg) { g_setup_error = msg; }
 // doubling, within 2 and 64 MB.
 // An array that would waste more than a quarter of the next chunk gets its own.
 // Set-up and release of the flower with N = 1024: 10 ms with chunks doubling
-// from 1 MB, 5 ms like this.
+// from 1 MB, 5 ms like this (4.3 where the first chunk was there).
 hipError_t ctx_alloc(mgfem_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   bytes = (std::max<size_t>(bytes, 8) + 255) & ~(size_t)255;
   const size_t chunk = (c->chunk_next + 255) & ~(size_t)255;  // (scratch from its end is as aligned as the arrays)
   if (bytes > c->chunk_left && bytes <= chunk / 4 * 3) {
     void* q = nullptr;
-    const hipError_t e = hipMalloc(&q, chunk);
+    const hipError_t e = c->allocs.empty() ? first_chunk(c, &q, chunk) : dev_malloc(&q, chunk);
     const size_t next = c->allocs.empty() ? chunk / 8 : 2 * chunk;
     c->chunk_next = std::min<size_t>(std::max<size_t>(next, (size_t)2 << 20), (size_t)64 << 20);
     if (e == hipSuccess) {
@@ -90,7 +188,7 @@ hipError_t ctx_alloc(mgfem_ctx* c, void** p, size_t bytes) {
     c->chunk_left -= bytes;
     return hipSuccess;
   }
-  const hipError_t e = hipMalloc(p, bytes);
+  const hipError_t e = dev_malloc(p, bytes);
   if (e != hipSuccess) return e;
   c->allocs.push_back(*p);
   return hipMemsetAsync(*p, 0, bytes, c->s);
@@ -106,7 +204,7 @@ hipError_t TempMem::alloc(size_t bytes) {
     tail_ = true;
     return hipSuccess;
   }
-  return hipMalloc(&p_, size_);
+  return dev_malloc(&p_, size_);
 }
 TempMem::~TempMem() {
   if (!p_) return;
@@ -229,7 +327,7 @@ static void free_ctx(mgfem_ctx* c) {
   for (hipEvent_t e : c->prof.cap_ev) (void)hipEventDestroy(e);
   mgfem::drop_graphs(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  for (void* q : c->allocs) (void)hipFree(q);
+  mgfem::free_allocs(c);
   if (c->red_host) (void)hipHostFree(c->red_host);
   delete c;
 }
@@ -321,8 +419,8 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
   // the coarser levels, and the plans and the coarse map
   const size_t plane = (size_t)c->lv[0].n * sizeof(double);
   const size_t planes = (p.precision == MGFEM_PREC_MIXED ? 52 : 42) + (chi_dev ? 10 : 0);
-  c->chunk_next = std::min<size_t>(std::max<size_t>(plane * planes + (N >= 512 ? (size_t)128 << 20 : 0), (size_t)1 << 20),
-                                   (size_t)2 << 30);
+  const size_t first = std::max<size_t>(plane * planes + (N >= 512 ? (size_t)128 << 20 : 0), (size_t)1 << 20);
+  c->chunk_next = first <= mgfem::kFirstChunk ? first : (size_t)2 << 30;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int rc = MGFEM_OK;
   auto bail = [&](int code) {

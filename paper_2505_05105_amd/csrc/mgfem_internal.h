@@ -401,6 +401,8 @@ struct mgfem_ctx {
   mgfem::Stats* stats = nullptr;  // device
   mgfem_info info{};
   std::vector<void*> allocs;        // device memory to release: chunks and large arrays
+  size_t pool_bytes = 0;            // size of allocs[0] where a later handle may take it over
+  int pool_device = 0;
   char* chunk = nullptr;            // the current chunk's free part
   size_t chunk_left = 0, chunk_next = (size_t)1 << 20;
   mgfem::Profiler prof;
