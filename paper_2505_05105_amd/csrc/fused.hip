@@ -1370,8 +1370,11 @@ void fused_launch(hipStream_t s, int kind, const void* tab, const int2* work, in
 //            N = 2048  15.1, 9.4, 17.1  | 19.0, 12.1, 22.4
 // A level with a tile whose record does not hold its cut vertices keeps the
 // separate kernels (as does MGFEM_NO_CUT_GROUPS=1).
-// Larger float64 levels take them for the tiles that streaming passes leave
-// (stream.hip): %%RULE%%
+// Larger float64 levels, and 1024 to 2048 above that count, take them only for
+// the tiles that streaming passes leave (stream.hip), where one sweep goes up
+// (the upward pass does one; a second would take a plan of every tile).  Up to
+// N = 16384, the largest measured (solves with the band on the separate kernels
+// | on the fused steps: N = 4096 3.7 | 3.1 ms, N = 16384 20.9 | 20.0).
 constexpr int kMaxPlanN = 2048, kMinStreamFused = 1024, kMaxStreamFused = 16384;
 int build_fused(mgfem_ctx* c) {
   const int cl = c->cplan.map.level >= 0 ? c->cplan.map.level : c->cplan.lc;
@@ -1388,7 +1391,7 @@ int build_fused(mgfem_ctx* c) {
                                            c->lv[l].N <= kMaxStreamFused && stream_candidate(c, l))))
       ls.push_back(l);
   if (ls.empty()) return MGFEM_OK;
-  if (ls.size() > (size_t)kMaxSet) return MGFEM_OK;  // (N <= 2048 has fewer)
+  if (ls.size() > (size_t)kMaxSet) return MGFEM_OK;  // (N = 16384 has 7 or so)
   SetLevels S{};
   S.n = (int)ls.size();
   int big = 0;

@@ -1,4 +1,6 @@
-// The multigrid cycle on the device (sections 3 and 5 of the paper).
+// The multigrid cycle on the device (sections 3 and 5 of the paper), in separate
+// kernels: float32 cycles' cut sweeps, transposed cycles, levels without a plan
+// of fused steps (fused.hip) or streaming windows (stream.hip), batches.
 //
 // Smoothing step = one Gauss-Seidel sweep over the four colours
 // c(i,j) = (i mod 2) + 2 (j mod 2), then eta sweeps restricted to the
@@ -16,8 +18,9 @@
 //               are numbered so that consecutive tiles land on one XCD
 //               (workgroups are dealt to the 8 XCDs round robin), which keeps
 //               shared halos in that XCD's L2.
-//  k_cut        all 4 eta phases of the extra smoothing of one group of cut
-//               vertices in LDS (the group carries its dependency closure).
+//  k_cut        all 4 eta phases of the extra smoothing of the cut vertices of
+//               one group in LDS (the group carries its dependency closure),
+//               groups of one wave where they are small enough.
 //               Cut-vertex values are read from the snapshot the preceding
 //               kernel wrote, so no workgroup reads a value another one
 //               is writing.

@@ -13,17 +13,18 @@
 // another one.  A window's values are exact on its core; the columns and rows
 // around it are computed again by the windows beside it.
 //
-// The windows are runs of sweep tiles away from the boundary.  The other tiles,
-// the band, run the separate kernels, cut sweeps included.  The iterate goes
-// through three buffers: the band's first sweep, and the windows that touch the
-// band, write the second one, the second sweep the third.
+// The windows are runs of tiles away from the boundary.  The other tiles, the
+// band, run the fused steps (fused.hip, on 32 x 32 tiles) where the level has
+// their plan, float64 with one sweep up, and else the separate kernels, cut
+// sweeps included.  The iterate goes through three buffers: the band's first
+// sweep, and the windows that touch the band, write the second one, the second
+// sweep the third.
 //
 // Measured (flower, float64, MI355X).  N = 16384 (54 million unknowns, 1.4 GB
 // per pass): down 320 us (4.4 TB/s; a large copy reaches 5.2) where two sweeps
-// and the residual took 400 + 400 + 300, up 308 (before 386); the band's
-// launches 13 to 40.  A solve went from 31.3 to 20 ms.  N = 4096 (90 MB per
-// pass, in the last-level cache): down 20-21 us and the band 10 + 11 + 10 where
-// the three launches took 22 + 22 + 19, up 20 and 17 (before 32).
+// and the residual took 400 + 400 + 300, up 308 (before 386).  N = 4096 (90 MB
+// per pass, in the last-level cache): down 20-21 us where the three launches
+// took 22 + 22 + 19, up 20.  The table at the rule below has whole solves.
 #include <algorithm>
 
 #include "mgfem_internal.h"
@@ -509,14 +510,17 @@ void stream_up_windows(mgfem_ctx* c, int l, bool fp32, int in, int out) {
   else launch_up<double>(c, l, in, out);
 }
 
-// Levels that stream: forward cycles with two sweeps down, N >= 4096, and in
-// float64 the coarser levels with N >= 2048, whose start iterate is zero and
-// is not read.  The upward pass from N >= 4096.  Speed of solves against one
-// fixed earlier program, with separate kernels | downward pass | both:
-//   flower, float64, N = 4096     1.12 | 1.19 | 1.19, with the 2048 level 1.22
-//   ellipse, mixed, N = 4096      1.06 | 1.08 | 1.09, with the 2048 level 1.07
-//   gradient, float64, N = 2048   1.18 to 1.20, if level 0 streams 1.15 to 1.17
-//   annulus, float64, N = 1536    1.20, if level 0 streams 1.20
+// Levels that stream: forward cycles with two sweeps down.  In float64 with one
+// sweep up from N = 1024, the band on the fused steps; otherwise (the band on the
+// separate kernels) from N = 4096, in float64 also the coarser levels with
+// N >= 2048, whose start iterate is zero and is not read.  The upward pass from
+// N >= 4096, and with the fused band.  Speed of solves against one fixed earlier
+// program, with separate kernels | downward pass | both | both and the fused band:
+//   flower, float64, N = 4096     1.12 | 1.19 | 1.19, with the 2048 level 1.22 | 1.43
+//   flower, float64, N = 16384           |      | 1.63 | 1.70
+//   ellipse, mixed, N = 4096      1.06 | 1.08 | 1.09, with the 2048 level 1.07 |
+//   gradient, float64, N = 2048   1.18 to 1.20, if level 0 streams 1.15 to 1.17 | | 1.26
+//   annulus, float64, N = 1536    1.20, if level 0 streams 1.20 | | 1.30
 constexpr int kStreamN = 4096, kStreamCoarseN = 2048, kStreamFusedN = 1024, kUpN = 4096;
 bool stream_candidate(const mgfem_ctx* c, int l) {
   const Level& L = c->lv[l];
