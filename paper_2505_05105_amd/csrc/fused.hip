@@ -565,6 +565,7 @@ struct SetLevel {
   int N, nc, nt, cut;       // cells and tiles per side, cut vertices
   int coarse;               // the coarser level's place in the list, or -1
   int nblk;
+  int* sums;                // four arrays over runs of 256 cells (run_sums)
   int *cnt, *pos, *bid, *npos, *rows, *bcell, *ncol, *coff, *nval, *voff, *keep, *slot, *nst, *stoff, *nseg, *segoff;
   FBlock* blocks;
   int* cols;
@@ -586,112 +587,133 @@ struct SetLevels {
 };
 static_assert(sizeof(SetLevels) <= 3584, "kernel arguments");
 
-// cut vertices per cell
-__global__ void k_cell_count(SetLevels S) {
+__host__ __device__ inline int cell_runs(int nc) { return (nc * nc + 255) / 256; }
+// 0 cut vertices, 1 cells with one per run of 256 cells; 2, 3 those before it
+__device__ inline int* run_sums(const SetLevel& L, int k) { return L.sums + k * (cell_runs(L.nc) + 1); }
+
+// Cut vertices per cell, their number and that of the cells with one over the
+// block's 256 cells (sums of a block fit in 16 bits).
+__global__ __launch_bounds__(256) void k_cell_count(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.y];
   const int N = L.N, nc = L.nc;
   const uint8_t* __restrict__ fl = L.fl;
-  int* __restrict__ cnt = L.cnt;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc * nc || L.cut == 0) return;
-  const int i0 = (c % nc) * kCell, j0 = (c / nc) * kCell;
+  if (L.cut == 0 || blockIdx.x * 256 >= nc * nc) return;
+  const int c = blockIdx.x * 256 + threadIdx.x;
   int n = 0;
-  for (int q = 0; q < kCell * kCell; ++q) {
-    const int i = i0 + q % kCell, j = j0 + q / kCell;
-    if (i <= N && j <= N && (fl[i + (int64_t)j * (N + 1)] & kFlagCut)) ++n;
+  if (c < nc * nc) {
+    const int i0 = (c % nc) * kCell, j0 = (c / nc) * kCell;
+    for (int q = 0; q < kCell * kCell; ++q) {
+      const int i = i0 + q % kCell, j = j0 + q / kCell;
+      if (i <= N && j <= N && (fl[i + (int64_t)j * (N + 1)] & kFlagCut)) ++n;
+    }
+    L.cnt[c] = n;
   }
-  cnt[c] = n;
+  __shared__ int wsum[4];
+  int x = n | (n != 0) << 16;
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    x = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    run_sums(L, 0)[blockIdx.x] = x & 0xffff;
+    run_sums(L, 1)[blockIdx.x] = x >> 16;
+  }
 }
 
 // exclusive prefix sum over n values by one workgroup of 1024 threads, in runs
-// of eight values per thread: out[0..n], the total in *tot too; out2 (optional)
-// counts the non-zero values before each (-1: zero)
-__device__ void wg_scan(const int* in, int n, int* out, int* out2, int* tot, int* tot2) {
+// of eight values per thread: out[0..n], the total in *tot too
+__device__ void wg_scan(const int* in, int n, int* out, int* tot) {
   constexpr int U = 8;
-  __shared__ int wa[16], wb[16];
+  __shared__ int wa[16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  int ca = 0, cb = 0;  // sums of the runs before
+  int ca = 0;  // sum of the runs before
   for (int base = 0; base < n; base += 1024 * U) {
     const int q0 = base + t * U;
-    int v[U], a = 0, b = 0;
+    int v[U], a = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = in[min(q0 + u, n - 1)];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (q0 + u >= n) v[u] = 0;
       a += v[u];
-      b += v[u] != 0;
     }
-    int xa = a, xb = b;  // inclusive over the wave
+    int xa = a;  // inclusive over the wave
     for (int o = 1; o < 64; o <<= 1) {
-      const int ya = __shfl_up(xa, o), yb = __shfl_up(xb, o);
-      if (lane >= o) {
-        xa += ya;
-        xb += yb;
-      }
+      const int ya = __shfl_up(xa, o);
+      if (lane >= o) xa += ya;
     }
-    if (lane == 63) {
-      wa[wave] = xa;
-      wb[wave] = xb;
-    }
+    if (lane == 63) wa[wave] = xa;
     __syncthreads();
     xa += ca - a;
-    xb += cb - b;
     for (int w = 0; w < 16; ++w) {
-      if (w < wave) {
-        xa += wa[w];
-        xb += wb[w];
-      }
+      if (w < wave) xa += wa[w];
       ca += wa[w];
-      cb += wb[w];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (q0 + u < n) {
         out[q0 + u] = xa;
-        if (out2) out2[q0 + u] = v[u] != 0 ? xb : -1;
         xa += v[u];
-        xb += v[u] != 0;
       }
     __syncthreads();
   }
   if (t == 0) {
     out[n] = ca;
     *tot = ca;
-    if (out2) {
-      out2[n] = cb;
-      *tot2 = cb;
-    }
   }
 }
+// Positions and blocks in three steps: sums per 256 cells, their scan, the scan
+// within 256 cells where they are used.  (One workgroup over all cells: 1.4 ms at
+// N = 4096, 22.7 at 16384.  Set-up of the flower: N = 4096 8.1 ms, like this 6.7;
+// N = 2048 4.1, 3.75.)
 __global__ __launch_bounds__(1024) void k_scan_cells(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.x];
-  if (L.cut > 0) wg_scan(L.cnt, L.nc * L.nc, L.pos, L.bid, L.tot + 1, L.tot);
+  const int k = blockIdx.y;
+  if (L.cut > 0) wg_scan(run_sums(L, k), cell_runs(L.nc), run_sums(L, 2 + k), L.tot + 1 - k);
 }
 __global__ __launch_bounds__(1024) void k_scan_blocks(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.x];
   if (L.nblk > 0)
-    wg_scan(blockIdx.y ? L.nval : L.ncol, L.nblk, blockIdx.y ? L.voff : L.coff, nullptr, L.tot + 2 + blockIdx.y, nullptr);
+    wg_scan(blockIdx.y ? L.nval : L.ncol, L.nblk, blockIdx.y ? L.voff : L.coff, L.tot + 2 + blockIdx.y);
 }
 __global__ __launch_bounds__(1024) void k_scan_tiles(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.x];
   const int k = blockIdx.y;
   wg_scan(k == 0 ? L.keep : k == 1 ? L.nst : L.nseg, L.nt * L.nt, k == 0 ? L.slot : k == 1 ? L.stoff : L.segoff,
-          nullptr, L.tot + 4 + k, nullptr);
+          L.tot + 4 + k);
 }
 
 // rows by position, positions by node, and the cell of every block
-__global__ void k_cell_fill(SetLevels S) {
+__global__ __launch_bounds__(256) void k_cell_fill(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.y];
   const int N = L.N, nc = L.nc;
   const uint8_t* __restrict__ fl = L.fl;
-  const int *__restrict__ pos = L.pos, *__restrict__ bid = L.bid;
   int *__restrict__ rows = L.rows, *__restrict__ npos = L.npos, *__restrict__ bcell = L.bcell;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (L.cut == 0 || c >= nc * nc || bid[c] < 0) return;
-  bcell[bid[c]] = c;
+  if (L.cut == 0 || blockIdx.x * 256 >= nc * nc) return;
+  const int c = blockIdx.x * 256 + threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int v = c < nc * nc ? L.cnt[c] : 0, own = v | (v != 0) << 16;
+  __shared__ int wsum[4];
+  int x = own;  // inclusive over the wave
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  x -= own;
+  for (int w = 0; w < wave; ++w) x += wsum[w];
+  int p = run_sums(L, 2)[blockIdx.x] + (x & 0xffff);
+  const int b = run_sums(L, 3)[blockIdx.x] + (x >> 16);
+  if (c >= nc * nc) return;
+  L.pos[c] = p;
+  L.bid[c] = v != 0 ? b : -1;
+  if (c == nc * nc - 1) {
+    L.pos[c + 1] = p + v;
+    L.bid[c + 1] = b + (v != 0);
+  }
+  if (v == 0) return;
+  bcell[b] = c;
   const int i0 = (c % nc) * kCell, j0 = (c / nc) * kCell;
-  int p = pos[c];
   for (int q = 0; q < kCell * kCell; ++q) {
     const int i = i0 + q % kCell, j = j0 + q / kCell;
     if (i > N || j > N) continue;
@@ -1424,6 +1446,7 @@ int build_fused(mgfem_ctx* c) {
       t.tot = tot_dev + kTot * q;
       const int ncell = t.nc * t.nc, ntile = t.nt * t.nt, cut = std::max(1, t.cut);
       for (int** w : {&t.cnt, &t.pos, &t.bid}) *w = ints(t.cut > 0 ? ncell + 1 : 1);
+      t.sums = ints(t.cut > 0 ? 4 * (size_t)cell_runs(t.nc) + 4 : 1);
       t.npos = ints(t.cut > 0 ? L.n : 1);
       for (int** w : {&t.bcell, &t.rows, &t.ncol, &t.coff, &t.nval, &t.voff}) *w = ints(cut + 1);
       for (int** w : {&t.keep, &t.slot, &t.nst, &t.stoff, &t.nseg, &t.segoff}) *w = ints(ntile + 1);
@@ -1458,7 +1481,7 @@ int build_fused(mgfem_ctx* c) {
   if (any_cut) {
     // cells, positions, blocks
     hipLaunchKernelGGL(k_cell_count, dim3(nblk(max_cell, 256), S.n), dim3(256), 0, s, S);
-    hipLaunchKernelGGL(k_scan_cells, dim3(S.n), dim3(1024), 0, s, S);
+    hipLaunchKernelGGL(k_scan_cells, dim3(S.n, 2), dim3(1024), 0, s, S);
     hipLaunchKernelGGL(k_cell_fill, dim3(nblk(max_cell, 256), S.n), dim3(256), 0, s, S);
     if (const int e = totals()) return e;
     for (int q = 0; q < S.n; ++q) {
