@@ -798,8 +798,7 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   int grow = 0, m = 0;
   bool conv = false;
   int status = MGFEM_OK;
-  const bool fused = !mixed && !reverse;  // norm of u_m from the first sweep of cycle m + 1
-  int steps_done = 0;
+  int steps_done = 0;  // (float64 forward: the norm of u_m comes from the first sweep of cycle m + 1)
   // The mixed loop queues its next iteration before reading the norm it
   // waits for (when that iteration will most likely be needed): the outer
   // update writes the other float64 buffer, so the iterate whose norm is
@@ -859,9 +858,9 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
     step_inner.push_back(inner);
     out.seq = c->red_seq;
     out.g = g;
-    // fused: the closing steps read the next iterate and wrote the other buffers
-    out.result = L0.X[mixed ? c->u_cur : !fused ? L0.cur : L0.keep >= 0 ? L0.keep : 1 - L0.cur];
-    out.patch = fused && fused_level(c, 0, false) && L0.fp.ncut > 0;
+    // with steps of the next cycle: they read the iterate and wrote the other buffers
+    out.result = L0.X[mixed ? c->u_cur : steps_done == 0 ? L0.cur : L0.keep >= 0 ? L0.keep : 1 - L0.cur];
+    out.patch = steps_done > 0 && fused_level(c, 0, false) && L0.fp.ncut > 0;
     return MGFEM_OK;
   };
   // From zero, with a tolerance below 1, the first iteration is needed unless

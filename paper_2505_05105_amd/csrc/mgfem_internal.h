@@ -512,7 +512,8 @@ struct CycleOpts {
   int steps_done = 0;       // level-0 pre-smoothing steps that ran already (first_steps_with_norm)
 };
 // the first pre-smoothing steps of level 0 (float64, forward), whose first sweep
-// also takes the residual norm of its incoming iterate; returns their number
+// also takes the residual norm of its incoming iterate; returns their number (nu1 = 0:
+// the norm alone, 0)
 int first_steps_with_norm(mgfem_ctx* c);
 struct Reduce;
 Reduce next_reduce(mgfem_ctx* c, const double* part, int nb);  // the next reduction in sequence (reduce.h)

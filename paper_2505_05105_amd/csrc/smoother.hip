@@ -1937,8 +1937,12 @@ Reduce next_reduce(mgfem_ctx* c, const double* part, int nb) {
 // 239 without it, of the flower with N = 1024 1198 and 1171.
 int first_steps_with_norm(mgfem_ctx* c) {
   Level& L0 = c->lv[0];
-  auto alone = [&](const Reduce& r) { hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, r); };
   if (L0.empty()) return 1;
+  if (c->p.nu1 == 0) {  // no step to take it in: the norm alone, of the iterate with its cut sweeps
+    fused_apply(c, 0);
+    launch_residual_norm(c, L0.b, L0.X[L0.cur], nullptr);
+    return 0;
+  }
   if (streams(c, 0)) {  // all of the downward half
     const int in = L0.cur;
     stream_down<double>(c, 0, true);
@@ -1948,8 +1952,7 @@ int first_steps_with_norm(mgfem_ctx* c) {
   if (!fused_level(c, 0, false)) {
     sweep<double>(c, 0, false, true);
     const Reduce red = next_reduce(c, c->sweep_part, L0.ntiles);
-    if (c->p.nu1 > 0) cut_sweeps<double>(c, 0, false, &red);
-    else alone(red);
+    cut_sweeps<double>(c, 0, false, &red);
     return 1;
   }
   if (L0.sp.fused) {
@@ -1964,8 +1967,7 @@ int first_steps_with_norm(mgfem_ctx* c) {
     fused_sweep(c, 0, false, false, false, &red);
     return 2;
   }
-  if (c->p.nu1 == 0) L0.pend = false;
-  alone(red);
+  hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(1024), 0, c->s, red);
   return 1;
 }
 
