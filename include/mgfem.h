@@ -236,7 +236,8 @@ int mgfem_adjoint_neumann(mgfem_handle h, const double* lam_dev, double* dJdgN_d
 
 /*
  * Misfit J = 1/2 (u - u_t)^T M (u - u_t) (nodal interpolants) and
- * dJ/du = M (u - u_t).  J_host: host scalar; dJdu_dev: device (N+1)^2 or NULL.
+ * dJ/du = M (u - u_t).  J_host: host scalar; dJdu_dev: device (N+1)^2 or NULL
+ * (it may lie over u or u_t).
  */
 int mgfem_misfit(mgfem_handle h, const double* u_dev, const double* ut_dev, double* J_host,
                  double* dJdu_dev);
@@ -244,12 +245,12 @@ int mgfem_misfit(mgfem_handle h, const double* u_dev, const double* ut_dev, doub
 /*
  * mgfem_misfit for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops): same arguments, results and
- * errors, computed by one fused pass whose only scratch (one partial sum per
- * 256 x 4 block of the grid) lives in a static 2 MiB device array of the
- * library instead of memory it allocates.  The call allocates nothing:
- * no hipMalloc, hipFree or allocating library routine.
- *  Limit: (N/256 + 1)(N/4 + 1) partial sums of 8 bytes must fit in 2 MiB
- *         (every N below 16384); a larger N returns INVALID_ARG with the sizes.
+ * errors, computed by one fused pass whose partial sums live in a static
+ * 2 MiB device array of the library instead of memory it allocates.  The call
+ * allocates nothing: no hipMalloc, hipFree or allocating library routine.
+ *  Limit: (N/256 + 1)(N/4 + 1) values of 8 bytes must fit in 2 MiB (every N
+ *         below 16384; the pass takes half as many); a larger N returns
+ *         INVALID_ARG with the sizes.
  *  Every call on one device shares that array and leaves its partials in
  *  it: calls that overlap on one device (other streams, other host
  *  threads) race.  Synchronises the handle's stream.

@@ -1171,13 +1171,8 @@ int mgfem_misfit(mgfem_handle c, const double* u_dev, const double* ut_dev, doub
                  double* dJdu_dev) {
   if (const int e = single_problem_check(c)) return e;
   if (!u_dev || !ut_dev || !J_host) return fail(c, MGFEM_ERR_INVALID_ARG, "u, ut and J must be given");
-  // e = u - u_t, M e and e^T M e in one pass; a gradient over one of its inputs
-  // (blocks still read what others would have written) goes through scratch
-  const int64_t n = c->lv[0].n;
-  auto meets = [&](const double* p) { return dJdu_dev && dJdu_dev < p + n && p < dJdu_dev + n; };
-  const bool over = meets(u_dev) || meets(ut_dev);
-  const int nb = launch_misfit(c, u_dev, ut_dev, over ? c->F64tmp : dJdu_dev, c->red_partial, 2);
-  if (over) launch_copy(c, dJdu_dev, c->F64tmp, n);
+  // e = u - u_t, M e and e^T M e in one pass
+  const int nb = launch_misfit(c, u_dev, ut_dev, dJdu_dev, c->red_partial, 2);
   launch_pair_reduce(c, nb);
   MGFEM_HIP_TRY(hipGetLastError());
   double mx, l2, sum;

@@ -494,8 +494,8 @@ void launch_residual_norm(mgfem_ctx* c, const double* F, const double* u, double
 void launch_dot_reduce(mgfem_ctx* c, const double* a, const double* b);
 // the nb (max, sum) pairs of red_partial as the next reduction
 void launch_pair_reduce(mgfem_ctx* c, int nb);
-// dJ/du = M (u - u_t) (null: not written) and the blocks' shares of
-// (u - u_t)^T M (u - u_t) in part (noalloc.hip); returns the number of blocks
+// dJ/du = M (u - u_t) (null: not written; may lie over u or u_t) and the blocks'
+// shares of (u - u_t)^T M (u - u_t) in part (noalloc.hip); returns the number of blocks
 int launch_misfit(mgfem_ctx* c, const double* u, const double* ut, double* dJdu, double* part, int stride);
 void launch_zero(mgfem_ctx* c, double* p, int64_t n);
 void launch_copy(mgfem_ctx* c, double* dst, const double* src, int64_t n);

@@ -162,9 +162,14 @@ int launch_misfit(mgfem_ctx* c, const double* u, const double* ut, double* dJdu,
   const Level& L = c->lv[0];
   const int N = c->N;
   const dim3 grid((unsigned)((N + kMX) / kMX), (unsigned)((N + kMY) / kMY));  // (N+1) nodes per side
+  // a gradient over one of its inputs (blocks still read what others would have
+  // written) goes through the handle's scratch
+  auto meets = [&](const double* p) { return dJdu && dJdu < p + L.n && p < dJdu + L.n; };
+  double* y = meets(u) || meets(ut) ? c->F64tmp : dJdu;
   hipLaunchKernelGGL(k_misfit_partial, grid, dim3(256), 0, c->s, u, ut, (const uint8_t*)L.flags,
-                     (const int*)L.cutpos, (const double*)c->cut_rows, (const double*)c->M, dJdu, N,
+                     (const int*)L.cutpos, (const double*)c->cut_rows, (const double*)c->M, y, N,
                      c->h * c->h / 36.0, L.bbox[0], L.bbox[2], L.bbox[1], L.bbox[3], part, stride);
+  if (y != dJdu) launch_copy(c, dJdu, y, L.n);
   return (int)(grid.x * grid.y);
 }
 
@@ -214,12 +219,12 @@ int mgfem_misfit_noalloc(mgfem_handle c, const double* u_dev, const double* ut_d
     return MGFEM_ERR_HIP;
   }
   const int N = c->N;
-  // the documented limit: one partial sum per 256 x 4 nodes
+  // the documented limit: one value per 256 x 4 nodes (the pass takes half of that)
   const int64_t nb = (int64_t)((N + 256) / 256) * ((N + 4) / 4);
   if (nb * (int64_t)sizeof(double) > (int64_t)kScratchBytes) {
-    c->last_error = "N = " + std::to_string(N) + " needs " + std::to_string(nb * sizeof(double)) +
-                    " bytes of partial sums; the static scratch array holds " + std::to_string(kScratchBytes) +
-                    " bytes (every N below 16384 fits)";
+    c->last_error = "N = " + std::to_string(N) + ": 8 bytes per 256 x 4 nodes, " +
+                    std::to_string(nb * sizeof(double)) + ", are more than the limit of " +
+                    std::to_string(kScratchBytes) + " bytes (every N below 16384 is within it)";
     return MGFEM_ERR_INVALID_ARG;
   }
   double* part = static_cast<double*>(base);

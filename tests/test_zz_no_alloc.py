@@ -78,3 +78,26 @@ def test_noalloc_misfit_rejects_bad_arguments():
     assert L.mgfem_misfit_noalloc(s.handle, None, ut.data_ptr(), C.byref(J), None) == _lib.ERR_INVALID_ARG
     assert L.mgfem_misfit_noalloc(s.handle, u.data_ptr(), ut.data_ptr(), None, None) == _lib.ERR_INVALID_ARG
     assert L.mgfem_misfit_noalloc(None, u.data_ptr(), ut.data_ptr(), C.byref(J), None) == _lib.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("call", ["mgfem_misfit", "mgfem_misfit_noalloc"])
+@pytest.mark.parametrize("over,shift", [("u", 0), ("ut", 0), ("u", 5), ("ut", -300)])
+def test_gradient_over_an_input(call, over, shift):
+    """dJ/du written over u or u_t, or a part of it: J and dJ/du of separate
+    arrays, bit for bit."""
+    mg = _gpu()
+    from paper_2505_05105_amd import _lib
+    s, u, ut = _case(mg, 512, 4)
+    n = u.numel()
+    fn = getattr(_lib.lib(), call)
+    want = torch.empty_like(u)
+    J0, J1 = C.c_double(0.0), C.c_double(0.0)
+    _lib.check(fn(s.handle, u.data_ptr(), ut.data_ptr(), C.byref(J0), want.data_ptr()), s.handle)
+    buf = torch.zeros(n + 600, dtype=torch.float64, device=u.device)
+    at = buf[300:300 + n]
+    at.copy_(u if over == "u" else ut)
+    a, b = (at, ut) if over == "u" else (u, at)
+    y = buf[300 + shift:300 + shift + n]
+    _lib.check(fn(s.handle, a.data_ptr(), b.data_ptr(), C.byref(J1), y.data_ptr()), s.handle)
+    assert J1.value == J0.value and torch.equal(y, want)
+    assert not buf[:min(300, 300 + shift)].any()
