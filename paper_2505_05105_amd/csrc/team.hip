@@ -144,11 +144,17 @@ int read_red(mgfem_ctx* b, TeamPlan& T, const std::vector<int>& active, int slot
   mgfem_ctx* c = b;
   const auto t0 = std::chrono::steady_clock::now();
   for (int p : active) {
-    volatile const double* r = T.rec + 4 * ((size_t)slot * T.P + p);
-    while (r[2] != seq)
+    const double* at = T.rec + 4 * ((size_t)slot * T.P + p) + 2;
+    // acquire: the caller's reads of the norms stay behind that of their number
+    auto arrived = [&] {
+      double q;
+      __atomic_load(at, &q, __ATOMIC_ACQUIRE);
+      return q == seq;
+    };
+    while (!arrived())
       if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200)) {
         MGFEM_HIP_TRY(hipStreamSynchronize(b->s));
-        if (r[2] != seq) {
+        if (!arrived()) {
           c->last_error = "residual norms of the batch did not arrive";
           return MGFEM_ERR_HIP;
         }
