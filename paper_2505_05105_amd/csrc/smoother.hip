@@ -1623,7 +1623,7 @@ ResArgs<T> rr_args(mgfem_ctx* c, int l) {
   a.bc = Bp<T>(C);
   a.xc = Xp<T>(C, C.cur);
   a.flc = C.flags;
-  a.cutposc = C.cutpos;
+  a.cutposc = Sp<T>(C) ? C.cutpos : nullptr;  // (a plan that ran out of memory may hold the positions alone)
   a.snapc = Sp<T>(C);
   a.Nc = C.N;
   a.sc = C.stride;
