@@ -288,7 +288,9 @@ int32_t mgfem_level_n(mgfem_handle h, int32_t level);
 /*
  * Apply `steps` smoothing steps of level `level` to x_dev for the right-hand
  * side b_dev (both device, (N_l+1)^2 float64; x is updated in place).
- * reverse != 0 applies the transposed step.  For tests of single sweeps.
+ * reverse != 0 applies the transposed step.  For tests of single sweeps: the
+ * first call on a level whose solves run other kernels builds that level's
+ * plans for this one (it allocates device memory then; OOM).
  */
 int mgfem_smooth(mgfem_handle h, int32_t level, double* x_dev, const double* b_dev,
                  int32_t steps, int32_t reverse);

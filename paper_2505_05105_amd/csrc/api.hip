@@ -506,7 +506,7 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
   if (rc != MGFEM_OK) return bail(rc);
   rc = build_coarse_map(c, member);  // batch members run forward float cycles only
   if (rc != MGFEM_OK) return bail(rc);
-  rc = build_cycle_plans(c);
+  rc = build_cycle_plans(c, member || op_kind != kOpAssembled);  // no adjoint of those
   if (rc != MGFEM_OK) return bail(rc);
   SETUP_TRY(hipStreamSynchronize(c->s));
   mgfem_info& I = c->info;
@@ -1140,9 +1140,6 @@ int mgfem_adjoint(mgfem_handle c, const double* dJdu_dev, double rel_tol, int32_
                   int32_t* n_cycles) {
   if (const int e = single_problem_check(c)) return e;
   if (!dJdu_dev || max_cycles < 0) return fail(c, MGFEM_ERR_INVALID_ARG, "dJdu must be a device pointer");
-  for (int l = 0; l < cycle_levels(c); ++l)
-    if (!fused_level(c, l, false, true))
-      if (const int e = separate_plans(c, l)) return e;
   double* lam = lam_dev ? lam_dev : c->lam;
   // the adjoint right-hand side must vanish off the active nodes
   launch_sub_active(c, c->F, dJdu_dev, c->zero);
@@ -1234,10 +1231,6 @@ int mgfem_level_counts(mgfem_handle c, int32_t level, int64_t* n_active, int64_t
 
 int mgfem_profile(mgfem_handle c, int32_t enable) {
   if (!c || enable < 0 || enable > 1000) return MGFEM_ERR_INVALID_ARG;
-  if (enable)  // the timed sweeps of levels that stream
-    for (int l = 0; l < (int)c->lv.size(); ++l)
-      if (c->lv[l].sp.fused)
-        if (const int e = separate_plans(c, l)) return e;
   c->prof.on = enable != 0;
   c->prof.repeat = enable > 1 ? enable : 1;
   for (int k = 0; k < 4; ++k) {

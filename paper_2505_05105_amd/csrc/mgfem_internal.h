@@ -537,8 +537,7 @@ int build_tile_list(mgfem_ctx* c, int l);
 // a level's cut groups, and with them its tile lists, built once
 int cut_plan(mgfem_ctx* c, int l);
 int separate_plans(mgfem_ctx* c, int l);
-int build_cycle_plans(mgfem_ctx* c);
-int cycle_levels(const mgfem_ctx* c);  // levels above the coarse part
+int build_cycle_plans(mgfem_ctx* c, bool forward_only);
 // fused smoothing steps (fused.hip): plans, one sweep (of x, or with `up` of
 // x + P x_c; norm: the residual norm of its incoming iterate), residual and
 // restriction, the pending cut sweeps applied in place (no-op when none are),

@@ -112,8 +112,8 @@ void by_square(const std::vector<uint32_t>& xy, int sh, int n, std::vector<int>&
 
 // recursively split the rectangle [x0,x1) x [y0,y1) until each closure fits.  The
 // host's part of a plan is this: one grid pass per colour instead of a sort, no
-// allocation and no division per group (plans of N = 2048 and 1024, built by the
-// first transposed cycle: 2.7 ms before, 2.1 like this).
+// allocation and no division per group (plans of N = 2048 and 1024: 2.7 ms before,
+// 2.1 like this).
 bool build_groups(GroupLevel& G, int x0, int x1, int y0, int y1, const int* owned_q, int nowned, GroupBuild& gb) {
   if (nowned == 0) return true;
   const std::vector<uint32_t>& xy = G.xy;

@@ -2497,7 +2497,6 @@ int extend_coarse_map(mgfem_ctx* c, int max_nodes) {
   return MGFEM_OK;
 }
 
-int cycle_levels(const mgfem_ctx* c) { return coarse_level(c); }
 int separate_plans(mgfem_ctx* c, int l) {
   if (const int e = cut_plan(c, l)) return e;
   Level& L = c->lv[l];
@@ -2515,10 +2514,12 @@ int cut_plan(mgfem_ctx* c, int l) {
 }
 
 // The plans of a handle's cycles: the fused levels' tiles, and the cut groups
-// and tile lists of the separate kernels where they run (the other levels;
-// in mixed precision the cut groups everywhere, and level 0's tiles for the
-// outer step).  mgfem_smooth and an unfused batch build the rest on first use.
-int build_cycle_plans(mgfem_ctx* c) {
+// and tile lists of the separate kernels where they run: the other levels; in
+// mixed precision the cut groups everywhere, and level 0's tiles for the outer
+// step; and, unless forward_only, the levels whose transposed cycles they run
+// (an adjoint builds nothing).  mgfem_smooth and an unfused batch build the rest
+// on first use.
+int build_cycle_plans(mgfem_ctx* c, bool forward_only) {
   const int cl = coarse_level(c);
   const bool f32 = c->p.precision == MGFEM_PREC_MIXED;
   // (a window's columns and rows come in pairs from an even one)
@@ -2533,7 +2534,7 @@ int build_cycle_plans(mgfem_ctx* c) {
       if (const int e = cut_plan(c, l)) return e;
   if (const int e = build_fused(c)) return e;
   for (int l = 0; l < cl; ++l)
-    if (!c->lv[l].fp.ok || (f32 && l == 0))
+    if (!c->lv[l].fp.ok || (f32 && l == 0) || (!forward_only && !fused_level(c, l, false, true)))
       if (const int e = separate_plans(c, l)) return e;
   for (int l = 0; l < cl; ++l)
     if (!c->lv[l].fp.ok && !c->lv[l].sp.ok)
