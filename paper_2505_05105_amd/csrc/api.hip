@@ -416,10 +416,12 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
     c->lv.push_back(L);
   }
   // the first chunk: planes and vectors of level 0, a third of them again for
-  // the coarser levels, and the plans and the coarse map
+  // the coarser levels, and the plans and the coarse map (a batch's problems do
+  // not extend it: N = 512 takes 123 MB of 126)
   const size_t plane = (size_t)c->lv[0].n * sizeof(double);
   const size_t planes = (p.precision == MGFEM_PREC_MIXED ? 52 : 42) + (chi_dev ? 10 : 0);
-  const size_t first = std::max<size_t>(plane * planes + (N >= 512 ? (size_t)128 << 20 : 0), (size_t)1 << 20);
+  const size_t first = std::max<size_t>(plane * planes + (N >= 512 ? (size_t)(member ? 16 : 128) << 20 : 0),
+                                        (size_t)1 << 20);
   c->chunk_next = first <= mgfem::kFirstChunk ? first : (size_t)2 << 30;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int rc = MGFEM_OK;
