@@ -353,9 +353,15 @@ int mgfem_profile_read(mgfem_handle h, int32_t kernel_class, int64_t* launches, 
                        double* alg_bytes);
 
 /* Release the handle and its device memory.  The block that most of its arrays
- * share (up to 6 GB) may stay for the next handle of the same size, one block per
- * device: a set-up of another size or one that runs out of memory frees it. */
+ * share may stay for the next handle of the same size, one block of 16 MB to 6 GB
+ * per device: a set-up that wants a block of another such size or runs out of
+ * memory frees it, and so does mgfem_empty_cache. */
 int mgfem_destroy(mgfem_handle h);
+
+/* Give the blocks that released handles left (mgfem_destroy) back to the devices,
+ * for other allocators of the process.  Live handles keep theirs.  Any host thread
+ * may call it; waits for the device like hipFree.  Errors: HIP. */
+int mgfem_empty_cache(void);
 
 /* Static text for a status code. */
 const char* mgfem_status_string(int code);

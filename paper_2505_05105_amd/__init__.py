@@ -28,7 +28,8 @@ from ._lib import (COARSE_GALERKIN, COARSE_REDISCRETISED, CYCLE_TWO_GRID, CYCLE_
                    PREC_FP64, PREC_MIXED, STAB_FIXED, STAB_GLOBAL, STAB_LOCAL_EIG, STAB_PAPER, MgfemError,
                    default_params)
 
-__all__ = ["Solver", "BatchedSolver", "GhostFEMSolve", "GhostFEMSolveMixed", "MgfemError", "default_params"]
+__all__ = ["Solver", "BatchedSolver", "GhostFEMSolve", "GhostFEMSolveMixed", "MgfemError", "default_params",
+           "empty_cache"]
 
 CELL_TYPES = ("external", "triangle", "quadrilateral", "pentagon", "internal",
               "saddle_split", "saddle_hexagon")
@@ -44,6 +45,12 @@ def _dev(x, device, n=None):
     if n is not None and x.numel() != n:
         raise ValueError(f"expected {n} values, got {x.numel()}")
     return x
+
+
+def empty_cache():
+    """Give the device memory that closed solvers left for the next one of their
+    size (at most 6 GB per device) back, for torch or another library."""
+    _lib.check(_lib.lib().mgfem_empty_cache())
 
 
 class Solver:

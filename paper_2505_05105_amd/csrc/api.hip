@@ -64,8 +64,8 @@ void set_setup_error(const std::string& msg) { g_setup_error = msg; }
 // first 49, then 90 ms), which the set-ups of a moving interface run into.  Set-up,
 // solve and release: N = 3072 11 ms and later 92, with the kept block 7.9; N = 1024
 // 5.0, with it 4.3.  One block per device, kPoolMin to
-// kFirstChunk bytes; a set-up that wants another size and an allocation that
-// fails give it back.
+// kFirstChunk bytes; a set-up that wants another size within them, an allocation
+// that fails and mgfem_empty_cache give it back.
 constexpr size_t kPoolMin = (size_t)16 << 20, kFirstChunk = (size_t)6 << 30;
 struct Pool {
   struct Block {
@@ -100,6 +100,22 @@ struct Pool {
       }
     }
     (void)hipFree(b.p);  // another thread's came between
+  }
+  // every device's block released
+  hipError_t clear() {
+    std::vector<Block> old;
+    {
+      std::lock_guard<std::mutex> lock(m);
+      old.swap(blocks);
+    }
+    int device = 0;
+    hipError_t e = old.empty() ? hipSuccess : hipGetDevice(&device);
+    for (const Block& b : old) {
+      const hipError_t s = hipSetDevice(b.device), f = s == hipSuccess ? hipFree(b.p) : s;
+      if (e == hipSuccess) e = f;
+    }
+    if (!old.empty()) (void)hipSetDevice(device);
+    return e;
   }
 };
 static Pool& pool() {
@@ -561,6 +577,8 @@ int32_t mgfem_level_n(mgfem_handle h, int32_t level) {
   if (!h || level < 0 || level >= (int)h->lv.size()) return -1;
   return h->lv[level].N;
 }
+
+int mgfem_empty_cache(void) { return pool().clear() == hipSuccess ? MGFEM_OK : MGFEM_ERR_HIP; }
 
 int mgfem_destroy(mgfem_handle h) {
   if (!h) return MGFEM_ERR_INVALID_ARG;
