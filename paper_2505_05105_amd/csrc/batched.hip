@@ -27,6 +27,8 @@ namespace {
 std::mutex g_tune_mu;
 std::map<std::string, int> g_tune;
 
+// (paths counts the forms of the candidates: a choice that was timed with other
+// kernels is timed again)
 std::string tune_key(const std::vector<int>& Ns, const mgfem_params& p) {
   int dev = 0;
   (void)hipGetDevice(&dev);
@@ -36,7 +38,7 @@ std::string tune_key(const std::vector<int>& Ns, const mgfem_params& p) {
   long long sum = 0;
   for (int n : Ns) sum += (long long)(n + 1) * (n + 1);
   char buf[256];
-  std::snprintf(buf, sizeof buf, "%s|paths=2|count=%zu|nodes=%lld|eta=%d|nu=%d,%d|inner=%d", arch.c_str(), Ns.size(),
+  std::snprintf(buf, sizeof buf, "%s|paths=3|count=%zu|nodes=%lld|eta=%d|nu=%d,%d|inner=%d", arch.c_str(), Ns.size(),
                 sum, p.eta, p.nu1, p.nu2, p.inner_cycles);
   return buf;
 }
