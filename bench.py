@@ -26,16 +26,18 @@ sys.path.insert(0, ROOT)
 METRIC = "fine-grid DOF/s to 1e-10 rel. residual at N=4096 (FP64 vs mixed); HBM GB/s"
 HBM_PEAK_GBS = 8000.0
 SWEEP_KERNEL = "k_sweep<double, 64, 32, 512>"
+DOWN_KERNEL = "k_stream<double, false, true>"  # and, from the zero iterate, <double, true, ...>
+UP_KERNEL = "k_stream_up<double>"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
 
 
-def source_hash():
-    """Hash of the code of the profiled kernel's sources, comments and blank
+def source_hash(names=("smoother.hip", "mgfem_internal.h")):
+    """Hash of the code of the profiled kernels' sources, comments and blank
     space left out (counters go stale when the code changes)."""
     import hashlib
     import re
     h = hashlib.sha256()
-    for name in ("smoother.hip", "mgfem_internal.h"):
+    for name in names:
         with open(os.path.join(ROOT, "paper_2505_05105_amd", "csrc", name)) as fh:
             text = fh.read()
         text = re.sub(r"//[^\n]*", "", text)
@@ -44,9 +46,10 @@ def source_hash():
     return h.hexdigest()[:16]
 
 
-def measured_traffic(domain="flower", N=4096):
-    """HBM bytes per launch of the sweep kernel from the committed counter runs,
-    or None when they were taken on other sources or another workload."""
+def measured_traffic(domain="flower", N=4096, kernel=SWEEP_KERNEL):
+    """HBM bytes per launch of the sweep kernel or of a streaming pass from the
+    committed counter runs, or None when they were taken on other sources or
+    another workload."""
     try:
         with open(TRAFFIC_FILE) as fh:
             t = json.load(fh)
@@ -56,7 +59,10 @@ def measured_traffic(domain="flower", N=4096):
         return None
     for rec in t.get("records", []):
         if rec.get("workload") == {"domain": domain, "N": N}:
-            return rec.get("bytes_per_launch")
+            if kernel == SWEEP_KERNEL:
+                return rec.get("bytes_per_launch")
+            own = rec.get("passes", {}).get(kernel, {})
+            return own.get("bytes_per_launch") if own.get("source_hash") == source_hash(("stream.hip",)) else None
     return None
 
 
@@ -322,17 +328,23 @@ def bench_next(args, mg, W, torch, dev, N=4096, oracle_N=1024, with_oracle=True)
     return out
 
 
-def sweep_roofline(solver, solve, kernel_class, steps, repeat, traffic):
-    """Roofline of the finest-level sweep (class 0 float64, class 1 the float32
-    sweep of the mixed cycles), measured live: the solves again with HIP events
-    on the solver's stream around every launch of that kernel, each launch
-    issued `repeat` times back to back between its two events (the sweep
-    reads one iterate buffer and writes the other, so a repeat recomputes the
-    same values) so that the event pair's dispatch gap is spread over the
-    repeats.  Algorithmic bytes per launch (matrix-free count): 3 values per
-    active row (iterate read and written, right-hand side), 9 per stored row,
-    1 per active coarse row when the prolongation is fused; the one flag byte
-    per node the kernel also reads is reported apart."""
+def rooflines(solver, solve, steps, repeat, domain, N, mixed=False):
+    """Rooflines of the finest level's kernels, measured live: the solves again
+    with HIP events on the solver's stream around every launch of the profiled
+    classes, each launch issued `repeat` times back to back between its two
+    events (they read one iterate buffer and write others, so a repeat
+    recomputes the same values) so that the event pair's dispatch gap is spread
+    over the repeats.  Returns the figures of the kernel with the most bytes of
+    the solves (the downward streaming pass, or the sweep where the level does
+    not stream), and under "others" those of the upward pass and of the full
+    sweep, which a solve of a streaming level does not launch (in_solve false):
+    it is run beside the passes.
+
+    Algorithmic bytes per launch (matrix-free count): sweeps 3 values per active
+    row (iterate read and written, right-hand side), 9 per stored row, 1 per
+    active coarse row when the prolongation is fused (the one flag byte per node
+    is reported apart); passes 3.25 values per node of their windows (2.25 from
+    the zero iterate)."""
     solver.profile(True, repeat=repeat)
     solve()  # captures the profiled graphs
     torch_sync()
@@ -342,24 +354,35 @@ def sweep_roofline(solver, solve, kernel_class, steps, repeat, traffic):
         solve()
     torch_sync()
     prof_ms = (time.perf_counter() - t0) * 1e3 / steps
-    prof = solver.profile_read(kernel_class)
+    prof = {k: solver.profile_read(k) for k in ((1,) if mixed else (0, 2, 3))}
     solver.profile(False)
-    launches = max(prof["launches"], 1)
-    avg_ms = prof["total_ms"] / launches
-    alg = prof["alg_bytes"] / launches
-    achieved = alg / (avg_ms * 1e-3) / 1e9
-    vb = 8 if kernel_class == 0 else 4
-    kernel = SWEEP_KERNEL if kernel_class == 0 else SWEEP_KERNEL.replace("double", "float")
-    log(f"[bench] {kernel}: {prof['launches']} launches, avg {avg_ms * 1e3:.2f} us "
-        f"(x{repeat} back to back), {alg / 1e6:.1f} MB algorithmic -> {achieved:.0f} GB/s")
-    return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kernel,
-            "avg_launch_us": avg_ms * 1e3, "alg_bytes_per_launch": alg,
-            "flag_bytes_per_launch": solver.level_counts(0)["n_active"],
-            "byte_model": f"{3 * vb} B per active row + {9 * vb} B per stored row + {vb} B per active "
-                          f"coarse row when the prolongation is fused (matrix-free interior rows)",
-            "launches": prof["launches"], "repeat_per_event_pair": repeat,
-            "profiled_ms_per_step": prof_ms}
+    # (mixed-precision levels stream from N = 4096 on unless profiled)
+    streams = N >= 4096 if mixed else prof[2]["launches"] > 0
+    vb = 4 if mixed else 8
+    out = {}
+    for k, p in prof.items():
+        if not p["launches"]:
+            continue
+        sweep = k < 2
+        kernel = {0: SWEEP_KERNEL, 1: SWEEP_KERNEL.replace("double", "float"), 2: DOWN_KERNEL, 3: UP_KERNEL}[k]
+        avg_ms, alg = p["total_ms"] / p["launches"], p["alg_bytes"] / p["launches"]
+        achieved = alg / (avg_ms * 1e-3) / 1e9
+        log(f"[bench] {kernel}: {p['launches']} launches, avg {avg_ms * 1e3:.2f} us "
+            f"(x{repeat} back to back), {alg / 1e6:.1f} MB algorithmic -> {achieved:.0f} GB/s")
+        out[k] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                  "frac": achieved / HBM_PEAK_GBS, "traffic": None if mixed else measured_traffic(domain, N, kernel),
+                  "kernel": kernel, "in_solve": not (sweep and streams),
+                  "avg_launch_us": avg_ms * 1e3, "alg_bytes_per_launch": alg,
+                  "byte_model": (f"{3 * vb} B per active row + {9 * vb} B per stored row + {vb} B per active "
+                                 f"coarse row when the prolongation is fused (matrix-free interior rows)") if sweep else
+                  f"{3.25 * vb:g} B per node of the windows ({2.25 * vb:g} B from the zero iterate)",
+                  "launches": p["launches"], "repeat_per_event_pair": repeat, "profiled_ms_per_step": prof_ms}
+        if sweep:
+            out[k]["flag_bytes_per_launch"] = solver.level_counts(0)["n_active"]
+    head = out.pop(2) if 2 in out else out.pop(min(out))
+    if out:
+        head["others"] = [out[k] for k in sorted(out)]
+    return head
 
 
 def torch_sync():
@@ -396,7 +419,7 @@ def bench_hbm(args, mg, W, torch, dev):
     ms = (time.perf_counter() - t0) * 1e3 / steps
     dof = s.info()["n_active"]
     log(f"[bench] hbm leg N={N}: {ms:.2f} ms/solve, {len(hist) - 1} cycles, {dof / (ms * 1e-3) / 1e9:.3f} GDOF/s")
-    roof = sweep_roofline(s, run, 0, steps, args.profile_repeat, measured_traffic("flower", N))
+    roof = rooflines(s, run, steps, args.profile_repeat, "flower", N)
     roof.update({"workload": f"flower ghost-FEM Poisson, N={N}, V(2,1), eta=4, gamma=2, rel_tol={args.tol:g}",
                  "N": N, "active_dof": dof, "cycles": len(hist) - 1, "ms_per_solve": ms,
                  "dof_per_s": dof / (ms * 1e-3), "setup_s": setup_s,
@@ -561,8 +584,7 @@ def main():
     ms = (t1 - t0) * 1e3 / args.steps
     cycles = len(hist) - 1
     log(f"[bench] fp64: {ms:.3f} ms/solve, {cycles} cycles, {dof / (ms * 1e-3) / 1e9:.3f} GDOF/s")
-    roof = sweep_roofline(s64, lambda: run(s64, u), 0, args.steps, args.profile_repeat,
-                          measured_traffic(args.domain, N))
+    roof = rooflines(s64, lambda: run(s64, u), args.steps, args.profile_repeat, args.domain, N)
     out = {
         "metric": METRIC, "value": dof / (ms * 1e-3), "unit": "DOF/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
@@ -604,8 +626,8 @@ def main():
         step_cycles = [int(k) for k in smx.step_cycles()]
         err = float((um - u).abs().max() / u.abs().max())
         u_mixed = um.cpu().numpy()
-        # the float32 finest sweep timed the same way
-        roof32 = sweep_roofline(smx, lambda: run(smx, um), 1, args.steps, args.profile_repeat, None)
+        # the float32 finest sweep timed the same way (profiled, the level does not stream)
+        roof32 = rooflines(smx, lambda: run(smx, um), args.steps, args.profile_repeat, args.domain, N, mixed=True)
         out["mixed"] = {"value": dof / (msm * 1e-3), "unit": "DOF/s", "ms_per_step": msm,
                         "cycles": len(hm) - 1, "inner_cycles": args.inner_cycles,
                         "float_cycles": sum(step_cycles), "step_cycles": step_cycles,

@@ -329,7 +329,7 @@ int mgfem_level_counts(mgfem_handle h, int32_t level, int64_t* n_active, int64_t
 
 /*
  * Kernel timing inside solves, for roofline measurements.  While enabled,
- * every launch of the profiled kernel class is bracketed by HIP events on the
+ * every launch of the profiled kernel classes is bracketed by HIP events on the
  * handle's stream; after each solve the durations, the launch count and the
  * algorithmic bytes of those launches are accumulated.  Class 0 is the
  * float64 full-sweep kernel of the finest level, class 1 the float32 one of
@@ -343,9 +343,16 @@ int mgfem_level_counts(mgfem_handle h, int32_t level, int64_t* n_active, int64_t
  *           buffer and writes the other, so a repeat recomputes the same
  *           values) and its time is the elapsed time / R, which leaves out
  *           the dispatch gap an event pair adds to a single launch.
- * A large finest level may run passes that take several sweeps at a time and
- * no sweep kernel; a profiled float64 solve then launches that kernel beside
- * them, at each of its steps, from the step's iterate into a spare buffer.
+ * A large finest level in float64 runs streaming passes over windows away from
+ * the boundary, which take several sweeps at a time, and no sweep kernel.  They
+ * are classes 2 (downwards: two sweeps, residual and restriction) and 3
+ * (upwards: prolongation and a sweep), timed where they run, with 3.25 w bytes
+ * per node of the windows (iterate read and written, right-hand side, a coarse
+ * node in four).  Class 0 is then launched beside them, at each step of the
+ * solve, from the step's iterate into a spare buffer: a figure to compare, of no
+ * launch that the solve makes.  Levels that stream in mixed precision (N >= 4096),
+ * with more than one post-smoothing step or with eta > 4 run the sweep kernel
+ * instead of the passes while profiled.
  * mgfem_profile resets the counters.
  */
 int mgfem_profile(mgfem_handle h, int32_t enable);

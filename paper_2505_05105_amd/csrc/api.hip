@@ -711,8 +711,9 @@ int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used, int*
     // the capture stream starts after the work already queued on the caller's
     // stream only through the graph launch below, which is stream-ordered
     if (c->prof.on && c->prof.cap_ev.empty()) {
-      // timed launches per iteration: three finest sweeps (W-cycle: the same)
-      for (int q = 0; q < 8; ++q) {
+      // timed launches per iteration: up to four finest sweeps (W-cycle: the
+      // same) and three streaming passes
+      for (int q = 0; q < 14; ++q) {
         hipEvent_t e;
         MGFEM_HIP_TRY(hipEventCreate(&e));
         c->prof.cap_ev.push_back(e);

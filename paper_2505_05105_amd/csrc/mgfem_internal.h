@@ -137,6 +137,7 @@ struct StreamPlan {
   bool ok = false;
   bool fused = false;  // the rest runs the fused steps (its tiles are the fused plan's), else the separate kernels
   int nwin = 0, nup = 0, nband = 0, nrr = 0;
+  double down_nodes = 0.0, up_nodes = 0.0;  // fused: nodes that the windows write
   int4* win = nullptr;
   int4* up = nullptr;
   int* band = nullptr;     // their tmeta entries

@@ -477,6 +477,13 @@ StreamArgs<T> stream_args(mgfem_ctx* c, int l, int in, int out, const int4* win,
   a.nwin = nwin;
   return a;
 }
+// a pass of level 0 in a profiled solve is timed where it runs (it reads one
+// buffer and writes others, so that it can be repeated)
+template <class F>
+void run_pass(mgfem_ctx* c, int l, int kernel_class, double bytes, const F& go) {
+  if (c->prof.on && l == 0) prof_launch(c, kernel_class, bytes, go);
+  else go(c->s);
+}
 inline dim3 stream_grid(int nwin) { return dim3(8u * (unsigned)((((nwin + 3) / 4) + 7) / 8)); }
 template <class T>
 void launch_down(mgfem_ctx* c, int l, int in, int mid, int out, double* part) {
@@ -486,10 +493,13 @@ void launch_down(mgfem_ctx* c, int l, int in, int mid, int out, double* part) {
   a.bc = Of<T>::B(c->lv[l + 1]);
   a.part = part;
   const dim3 g = stream_grid(a.nwin), bs(256);
-  if (L.zero && part) hipLaunchKernelGGL((k_stream<T, true, true>), g, bs, 0, c->s, a);
-  else if (L.zero) hipLaunchKernelGGL((k_stream<T, true, false>), g, bs, 0, c->s, a);
-  else if (part) hipLaunchKernelGGL((k_stream<T, false, true>), g, bs, 0, c->s, a);
-  else hipLaunchKernelGGL((k_stream<T, false, false>), g, bs, 0, c->s, a);
+  const bool zero = L.zero;
+  run_pass(c, l, 2, sizeof(T) * (zero ? 2.25 : 3.25) * L.sp.down_nodes, [a, g, bs, zero](hipStream_t st) {
+    if (zero && a.part) hipLaunchKernelGGL((k_stream<T, true, true>), g, bs, 0, st, a);
+    else if (zero) hipLaunchKernelGGL((k_stream<T, true, false>), g, bs, 0, st, a);
+    else if (a.part) hipLaunchKernelGGL((k_stream<T, false, true>), g, bs, 0, st, a);
+    else hipLaunchKernelGGL((k_stream<T, false, false>), g, bs, 0, st, a);
+  });
 }
 template <class T>
 void launch_up(mgfem_ctx* c, int l, int in, int out) {
@@ -497,7 +507,9 @@ void launch_up(mgfem_ctx* c, int l, int in, int out) {
   const Level& C = c->lv[l + 1];
   StreamArgs<T> a = stream_args<T>(c, l, in, out, L.sp.up, L.sp.nup);
   a.xc = Of<T>::X(C, C.cur);
-  hipLaunchKernelGGL(k_stream_up<T>, stream_grid(a.nwin), dim3(256), 0, c->s, a);
+  run_pass(c, l, 3, sizeof(T) * 3.25 * L.sp.up_nodes, [a](hipStream_t st) {
+    hipLaunchKernelGGL(k_stream_up<T>, stream_grid(a.nwin), dim3(256), 0, st, a);
+  });
 }
 }  // namespace
 
@@ -581,6 +593,11 @@ std::vector<int4> build_windows(const std::vector<uint8_t>& map, const std::vect
     }
   return win;
 }
+double core_nodes(const std::vector<int4>& win) {
+  double n = 0.0;
+  for (const int4& w : win) n += (double)(w.z & 0xffff) * (w.z >> 16);
+  return n;
+}
 }  // namespace
 
 int build_stream_fused(mgfem_ctx* c, int l, const std::vector<uint8_t>& inner, int nt, int TN) {
@@ -603,6 +620,8 @@ int build_stream_fused(mgfem_ctx* c, int l, const std::vector<uint8_t>& inner, i
   MGFEM_HIP_TRY(hipStreamSynchronize(c->s));
   S.nwin = (int)win.size();
   S.nup = (int)up.size();
+  S.down_nodes = core_nodes(win);
+  S.up_nodes = core_nodes(up);
   S.ok = S.fused = true;
   return MGFEM_OK;
 }

@@ -90,3 +90,41 @@ def test_streamed_float_cycles_keep_their_bits(N, coarsest, psi, kw):
     us, hs = s.solve(f, g, tol=-1.0, max_cycles=3)
     s.profile(False)
     assert np.array_equal(h, hs) and torch.equal(u, us)
+
+
+@pytest.mark.parametrize("N,coarsest,psi,kw,streams", [
+    (2048, 4, lambda N: W.flower(N), {}, True),
+    (1536, 3, lambda N: W.circle(N, radius=1.1), {"cycle": 2}, True),
+    (512, 4, lambda N: W.flower(N), {}, False),
+    (2048, 4, lambda N: W.flower(N), {"nu2": 2}, False),
+])
+def test_profiled_passes_are_those_of_the_solve(N, coarsest, psi, kw, streams):
+    """One downward pass per cycle and one behind the last, one upward pass per
+    cycle, timed where they run: the solve's bits stay, repeated launches too."""
+    s, (f, g, _) = _setup(N, coarsest, psi, **kw)
+    u, h = s.solve(f, g, tol=-1.0, max_cycles=3)
+    for repeat in (1, 3):
+        s.profile(True, repeat=repeat)
+        up, hp = s.solve(f, g, tol=-1.0, max_cycles=3)
+        down, upward = s.profile_read(2), s.profile_read(3)
+        s.profile(False)
+        assert np.array_equal(h, hp) and torch.equal(u, up)
+        assert down["launches"] == (4 if streams else 0) and upward["launches"] == (3 if streams else 0)
+        n = s.level_counts(0)["n_active"]
+        if streams:  # the first pass starts from zero and does not read its iterate
+            assert 0 < down["alg_bytes"] <= (3 * 26 + 18) * n and down["total_ms"] > 0.0
+            assert 0 < upward["alg_bytes"] <= 3 * 26 * n and upward["total_ms"] > 0.0
+
+
+def test_streamed_float_cycles_from_an_odd_column():
+    """float32 windows start at an even column and row, the active nodes here at odd ones."""
+    N = 4608
+    s, (f, g, _) = _setup(N, 9, lambda N: W.circle(N, radius=0.8995), mixed=True)
+    import paper_2505_05105_amd as mg
+    on = (s.export(mg._lib.EXPORT_NODE_FLAGS) > 0).view(N + 1, N + 1)
+    assert int(on.any(0).nonzero()[0]) % 2 == 1 and int(on.any(1).nonzero()[0]) % 2 == 1
+    u, h = s.solve(f, g, tol=-1.0, max_cycles=2)
+    s.profile(True)
+    us, hs = s.solve(f, g, tol=-1.0, max_cycles=2)
+    s.profile(False)
+    assert np.array_equal(h, hs) and torch.equal(u, us)
