@@ -711,9 +711,10 @@ int run_iteration(mgfem_ctx* c, const IterKind& k, const GraphEntry** used, int*
     // the capture stream starts after the work already queued on the caller's
     // stream only through the graph launch below, which is stream-ordered
     if (c->prof.on && c->prof.cap_ev.empty()) {
-      // timed launches per iteration: up to four finest sweeps (W-cycle: the
-      // same) and three streaming passes
-      for (int q = 0; q < 14; ++q) {
+      // timed launches per iteration: the sweeps of its cycles and of the next
+      // one's first steps, and three streaming passes
+      const int cycles = c->p.precision == MGFEM_PREC_MIXED ? c->p.inner_cycles : 1;
+      for (int q = 0; q < 2 * (cycles * (c->p.nu1 + c->p.nu2) + 5); ++q) {
         hipEvent_t e;
         MGFEM_HIP_TRY(hipEventCreate(&e));
         c->prof.cap_ev.push_back(e);

@@ -128,3 +128,17 @@ def test_streamed_float_cycles_from_an_odd_column():
     us, hs = s.solve(f, g, tol=-1.0, max_cycles=2)
     s.profile(False)
     assert np.array_equal(h, hs) and torch.equal(u, us)
+
+
+@pytest.mark.parametrize("kw", [{"mixed": True}, {"nu1": 4, "nu2": 3}, {"mixed": True, "inner_cycles": 16, "nu2": 2}])
+def test_profiled_iterations_are_captured(kw, capfd):
+    """However many launches an iteration times, it is still replayed as a graph
+    (a capture that fails is reported, and ends the handle's replays)."""
+    s, (f, g, _) = _setup(256, 4, lambda N: W.flower(N), **kw)
+    s.profile(True, repeat=2)
+    s.solve(f, g, tol=-1.0, max_cycles=3)
+    n = s.profile_read(1 if kw.get("mixed") else 0)["launches"]
+    per_cycle = s.params.nu1 + s.params.nu2
+    assert n == (3 * s.params.inner_cycles * per_cycle if kw.get("mixed") else 3 * per_cycle + 1)
+    s.close()
+    assert "graph capture" not in capfd.readouterr().err
