@@ -123,17 +123,19 @@ static Pool& pool() {
   return *p;
 }
 // device memory; where there is none left, after the pool's block is released
+// (the runtime's last error is cleared: the next call to look at it would take
+// the failure for its own)
 static hipError_t dev_malloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
   int device = 0;
   if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess) {
     const Pool::Block b = pool().take(device);
     if (b.p) {
-      (void)hipGetLastError();
       (void)hipFree(b.p);
       e = hipMalloc(p, bytes);
     }
   }
+  if (e != hipSuccess) (void)hipGetLastError();
   return e;
 }
 // a handle's first chunk: the pool's block of that size or new memory

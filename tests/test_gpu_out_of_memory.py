@@ -1,0 +1,42 @@
+"""A set-up that the device has no memory for."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def test_failed_setup():
+    """N = 32768 with 100 GB of the device left: its vectors and the level set take
+    some 52 GB, then nine planes of 77 GB do not fit, with half of the 100 free.
+    The call says so, and neither the next set-up nor torch sees the error again."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_05105_amd as mg
+    N = 512
+    psi, f, g = W.flower_mms_device(N, "cuda:0")
+    mg.empty_cache()
+    torch.cuda.synchronize()
+    base = torch.cuda.mem_get_info()[0]
+    s = mg.Solver(psi, N)
+    want, hist = s.solve(f, g, tol=1e-9)
+    s.close()
+    assert base - torch.cuda.mem_get_info()[0] >= 64 << 20  # its block is kept
+    big = torch.full((32769 ** 2,), -1.0, dtype=torch.float64, device="cuda:0")
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - 100 * 10 ** 9, dtype=torch.uint8, device="cuda:0")
+    code = None
+    try:
+        mg.Solver(big, 32768)
+    except mg.MgfemError as e:  # (its traceback, which holds psi, ends here)
+        code = e.code
+    assert code == mg._lib.ERR_OOM
+    del big, rest
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    assert float(torch.ones(1000, device="cuda:0").sum()) == 1000.0
+    s = mg.Solver(psi, N)
+    u, h = s.solve(f, g, tol=1e-9)
+    assert torch.equal(u, want) and np.array_equal(h, hist)
+    s.close()
