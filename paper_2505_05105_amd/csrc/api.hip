@@ -447,6 +447,7 @@ int setup_impl(const double* psi_dev, const double* chi_dev, int32_t N, const mg
     std::string msg = c->last_error;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    if (code == MGFEM_ERR_OOM) c->pool_bytes = 0;  // a device that is short of memory gets all of it back
     free_ctx(c);
     return fail(nullptr, code, msg);
   };

@@ -11,7 +11,8 @@ torch = pytest.importorskip("torch")
 def test_failed_setup():
     """N = 32768 with 100 GB of the device left: its vectors and the level set take
     some 52 GB, then nine planes of 77 GB do not fit, with half of the 100 free.
-    The call says so, and neither the next set-up nor torch sees the error again."""
+    The call says so, the block an earlier handle left is given back for it, nothing
+    stays allocated, and neither the next set-up nor torch sees the error again."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2505_05105_amd as mg
@@ -35,6 +36,7 @@ def test_failed_setup():
     del big, rest
     torch.cuda.empty_cache()
     torch.cuda.synchronize()
+    assert base - torch.cuda.mem_get_info()[0] <= 64 << 20
     assert float(torch.ones(1000, device="cuda:0").sum()) == 1000.0
     s = mg.Solver(psi, N)
     u, h = s.solve(f, g, tol=1e-9)
