@@ -103,6 +103,7 @@ int mgfem_setup_batched(int32_t count, const double* const* psi_dev, const int32
     team_free(b);
     for (void* q : b->allocs) (void)hipFree(q);
     delete b;
+    if (code == MGFEM_ERR_OOM) (void)mgfem_empty_cache();  // (what its problems left)
     set_setup_error(msg);
     return code;
   };
