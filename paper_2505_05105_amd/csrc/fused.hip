@@ -1163,7 +1163,6 @@ __global__ __launch_bounds__(1024) void k_ftile_fill(SetLevels S, int first, int
     R->seg = base;
     R->nseg = nseg;
     R->nrow = B.nrow;
-    R->ncol = B.ncol;
   }
   fill_box(P, x0 - kHX, y0 - kHY, kRW, kRH, 4 * eta, 2 * eta, B, base, kHX, kHY, FT, R->cols, R->rows, D, DT,
            idx);
@@ -1172,7 +1171,6 @@ __global__ __launch_bounds__(1024) void k_ftile_fill(SetLevels S, int first, int
     R->cseg = base + nseg;
     R->ncseg = B.nseg;
     R->ncrow = B.nrow;
-    R->nccol = B.ncol;
   }
   fill_box(C, x0 / 2 - 3, y0 / 2 - 2, kCRW, kCRH, 4 * eta, 2 * eta, B, base + nseg, 0, 0, 0, R->ccols, R->crows, D,
            nullptr, idx);

@@ -383,12 +383,12 @@ int setup_hierarchy(mgfem_ctx* c, const double* psi_in, const double* chi_in) {
   // coarsest factorisation
   Level& Lc = c->lv[nl - 1];
   const int cmax = (int)Lc.n;
-  MGFEM_HIP_TRY(ctx_alloc_t(c, &c->coarse_L, (int64_t)cmax * cmax));
   MGFEM_HIP_TRY(ctx_alloc_t(c, &c->coarse_idx, cmax));
   MGFEM_HIP_TRY(ctx_alloc_t(c, &c->cplan.inv, (int64_t)cmax * cmax));
-  double* cols = nullptr;  // the inverse's columns where they do not fit in LDS
-  MGFEM_HIP_TRY(ctx_alloc_t(c, &cols, cmax > kFactorLds ? (int64_t)cmax * cmax : 1));
-  hipLaunchKernelGGL(k_coarse_factor, dim3(1), dim3(256), 0, c->s, Lc.A, Lc.flags, Lc.N, c->coarse_L, cols,
+  double* work = nullptr;  // the factor and the inverse's columns where they do not fit in LDS
+  const int64_t block = cmax > kFactorLds ? (int64_t)cmax * cmax : 1;
+  MGFEM_HIP_TRY(ctx_alloc_t(c, &work, 2 * block));
+  hipLaunchKernelGGL(k_coarse_factor, dim3(1), dim3(256), 0, c->s, Lc.A, Lc.flags, Lc.N, work, work + block,
                      c->coarse_idx, c->cplan.inv, c->stats);
   MGFEM_HIP_TRY(hipGetLastError());
   return MGFEM_OK;

@@ -56,7 +56,6 @@ struct CutPlan {
   int* ext_src = nullptr;   // >= 0 node read from x; < 0 -(1+q) read from the cut-value snapshot
   double* cl_coef = nullptr;  // 9 per closure node: 8 off-diagonals, 1/diagonal
   float* cl_coef32 = nullptr;
-  int max_cl = 0, max_ext = 0;
   int lds64 = 0, lds32 = 0;   // dynamic LDS of a workgroup
   int units = 0;              // workgroups
   // The same with one wave per group, four groups per workgroup, where no group
@@ -111,9 +110,9 @@ struct FRow {
 struct FTile {
   static constexpr int kRows = 384, kCols = 1024, kCRows = 256, kSegs = 2048;
   int x0, y0, st, nst;
-  int seg, nseg, nrow, ncol;
-  int cseg, ncseg, ncrow, nccol;
-  int inner, pad[3];  // inner: every region node is active with the interior row
+  int seg, nseg, nrow;
+  int cseg, ncseg, ncrow;
+  int inner, pad[5];  // inner: every region node is active with the interior row
   int cols[kCols], ccols[kCols];
   FRow rows[kRows], crows[kCRows];
 };
@@ -386,7 +385,6 @@ struct mgfem_ctx {
   double* lam = nullptr;     // adjoint state when the caller passes none; in forward solves level 0's third
                              // iterate buffer (zero at the inactive nodes, as every iterate)
   // coarsest exact solve
-  double* coarse_L = nullptr;  // cn x cn lower Cholesky factor, then its inverse
   int* coarse_idx = nullptr;   // cn node indices
   int coarse_n = 0;
   mgfem::CoarsePlan cplan;

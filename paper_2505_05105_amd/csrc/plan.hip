@@ -74,7 +74,7 @@ struct GroupBuild {
   std::vector<int> info, node, q, ext;
   std::vector<uint8_t> own;
   std::vector<int16_t> nbr;
-  int max_cl = 0, max_ext = 0, lds64 = 0, lds32 = 0;
+  int lds64 = 0, lds32 = 0;
 };
 
 // The cut vertices of one level by 16 x 16-node bucket and by tile (the list
@@ -233,8 +233,6 @@ bool build_groups(GroupLevel& G, int x0, int x1, int y0, int y1, const int* owne
   gb.lds64 = std::max(gb.lds64, cut_lds_layout((int)cl.size(), (int)ext.size(), 8).total);
   gb.lds32 = std::max(gb.lds32, cut_lds_layout((int)cl.size(), (int)ext.size(), 4).total);
   gb.ext.insert(gb.ext.end(), ext.begin(), ext.end());
-  gb.max_cl = std::max(gb.max_cl, (int)cl.size());
-  gb.max_ext = std::max(gb.max_ext, (int)ext.size());
   return true;
 }
 
@@ -374,8 +372,6 @@ int build_cut_groups(mgfem_ctx* c, int l) {
   L.cp.ok = build(0, tiles.size(), gb);
   if (!L.cp.ok) return MGFEM_OK;
   L.cp.ngroups = L.cp.units = (int)gb.info.size() / 9;
-  L.cp.max_cl = gb.max_cl;
-  L.cp.max_ext = gb.max_ext;
   L.cp.lds64 = gb.lds64;
   L.cp.lds32 = gb.lds32;
   int rc;
