@@ -828,11 +828,13 @@ int iterate(mgfem_ctx* c, double* x, const double* b, double rel_tol, int max_cy
   // waits for (when that iteration will most likely be needed): the outer
   // update writes the other float64 buffer, so the iterate whose norm is
   // pending survives it and the queued iteration can be discarded.  The
-  // float64 forward cycle writes both level-0 buffers (a third buffer, which
-  // would make it safe, pushed the level-0 vectors out of the last-level
-  // cache and cost more than the launch gaps it saved) and the transposed
-  // cycle smooths its incoming iterate in place, so they wait for every norm;
-  // so do profiled solves, whose events are read per iteration.
+  // float64 forward loop waits for every norm.  Its levels with a third buffer
+  // run the next cycle's first steps meanwhile, which hides the wait; queueing
+  // the whole cycle leaves the gap between two graphs as it is (us per cycle
+  // queued and not: N = 64 34.1, 34.3; 1024 104.9, 106.2; 2048 177, 176.7), and
+  // levels with two buffers write both.  The transposed cycle smooths its
+  // incoming iterate in place, so it waits too, as do profiled solves, whose
+  // events are read per iteration.
   const bool ahead = mixed && !c->prof.on;
   struct Pending {
     double seq;          // the iteration's last reduction: the norm of `result`
