@@ -2532,13 +2532,25 @@ int build_cycle_plans(mgfem_ctx* c, bool forward_only) {
   if (f32)
     for (int l = 0; l < cl; ++l)
       if (const int e = cut_plan(c, l)) return e;
-  if (const int e = build_fused(c)) return e;
+  // (levels that there is no memory for a plan of keep the separate kernels)
+  if (const int e = build_fused(c)) {
+    if (e != MGFEM_ERR_OOM) return e;
+    c->last_error.clear();
+    for (Level& L : c->lv) {
+      L.fp = FusedPlan{};
+      L.sp = StreamPlan{};
+    }
+  }
   for (int l = 0; l < cl; ++l)
     if (!c->lv[l].fp.ok || (f32 && l == 0) || (!forward_only && !fused_level(c, l, false, true)))
       if (const int e = separate_plans(c, l)) return e;
   for (int l = 0; l < cl; ++l)
     if (!c->lv[l].fp.ok && !c->lv[l].sp.ok)
-      if (const int e = build_stream(c, l)) return e;
+      if (const int e = build_stream(c, l)) {
+        if (e != MGFEM_ERR_OOM) return e;
+        c->last_error.clear();
+        c->lv[l].sp = StreamPlan{};
+      }
   return MGFEM_OK;
 }
 

@@ -42,3 +42,48 @@ def test_failed_setup():
     u, h = s.solve(f, g, tol=1e-9)
     assert torch.equal(u, want) and np.array_equal(h, hist)
     s.close()
+
+
+def test_levels_without_memory_for_a_plan_keep_the_separate_kernels():
+    """N = 16384 with 0.2 GB more than a handle holds in the end: the scratch that
+    builds the fused plans (1.7 GB: positions of every node of the levels, three
+    numbers per 4 x 4 cell) does not fit beside what is allocated by then.  The
+    set-up goes on without those plans, and the iterates are the same to rounding:
+    the residual's, through the inverse of A, which grows as N^2 (1e-10 of the
+    largest entry is the streaming levels' bound up to N = 8192)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_05105_amd as mg
+    N = 16384
+    psi, f, g = W.flower_mms_device(N, "cuda:0")
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    s = mg.Solver(psi, N)
+    s.close()
+    mg.empty_cache()
+    base = free()
+    s = mg.Solver(psi, N)
+    held = base - free()
+    u, h = s.solve(f, g, tol=-1.0, max_cycles=2)
+    s.profile(True)
+    up, _ = s.solve(f, g, tol=-1.0, max_cycles=1, raise_on_fail=False)
+    assert s.profile_read(2)["launches"] > 0  # it streams
+    s.close()
+    mg.empty_cache()
+    del up
+    torch.cuda.empty_cache()
+    rest = torch.empty(free() - held - 2 * 10 ** 8, dtype=torch.uint8, device="cuda:0")
+    s = mg.Solver(psi, N)
+    del rest
+    torch.cuda.empty_cache()
+    us, hs = s.solve(f, g, tol=-1.0, max_cycles=2)
+    s.profile(True)
+    s.solve(f, g, tol=-1.0, max_cycles=1, raise_on_fail=False)
+    assert s.profile_read(2)["launches"] == 0 and s.profile_read(0)["launches"] > 0  # no fused band
+    s.close()
+    mg.empty_cache()
+    assert float((u - us).abs().max()) <= 4e-10 * float(u.abs().max())
+    np.testing.assert_allclose(hs, h, rtol=1e-9, atol=1e-12 * h[0])
