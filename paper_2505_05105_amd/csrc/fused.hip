@@ -665,7 +665,7 @@ __device__ void wg_scan(const int* in, int n, int* out, int* tot) {
 // Positions and blocks in three steps: sums per 256 cells, their scan, the scan
 // within 256 cells where they are used.  (One workgroup over all cells: 1.4 ms at
 // N = 4096, 22.7 at 16384.  Set-up of the flower: N = 4096 8.1 ms, like this 6.7;
-// N = 2048 4.1, 3.75.)
+// N = 2048 4.1, 3.75; both without the plans of the separate kernels.)
 __global__ __launch_bounds__(1024) void k_scan_cells(SetLevels S) {
   const SetLevel& L = S.v[blockIdx.x];
   const int k = blockIdx.y;
