@@ -201,8 +201,10 @@ class Solver:
         return {"n_active": a.value, "n_stored": s.value, "n_cut": c.value}
 
     def profile(self, enable=True, repeat=1):
-        """Enable HIP-event timing of the profiled kernel class (resets the
-        counters); repeat > 1 times each profiled launch repeated back to back."""
+        """Enable HIP-event timing of the profiled kernel classes (resets the
+        counters): 0 and 1 the finest level's full sweep in float64 and float32, 2
+        and 3 its streaming passes down and up; repeat > 1 times each profiled
+        launch repeated back to back."""
         _lib.check(_lib.lib().mgfem_profile(self.handle, (max(1, int(repeat)) if enable else 0)), self.handle)
 
     def profile_read(self, kernel_class=0):
